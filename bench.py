@@ -217,7 +217,7 @@ def eb_leg(sht, args, precs, alm, maps, alm_out):
 # applies only while the family's sources hash to the profiled version.
 LEG_COMMON = ["paper_2208_10154_amd/csrc/leg_rec.h", "paper_2208_10154_amd/csrc/leg_common.h",
               "paper_2208_10154_amd/csrc/sht_internal.h"]
-LEG_SOURCES = {"fp": ["paper_2208_10154_amd/csrc/k_leg.hip"] + LEG_COMMON,
+LEG_SOURCES = {"fp": ["paper_2208_10154_amd/csrc/k_leg.hip", "paper_2208_10154_amd/csrc/k_leg_reg.hip"] + LEG_COMMON,
                "bf": ["paper_2208_10154_amd/csrc/k_leg_bf16.hip"] + LEG_COMMON}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 MFMA_FILE = os.path.join(ROOT, "profiles", "mfma.json")

@@ -457,11 +457,8 @@ __global__ __launch_bounds__(NT, 2) void k_a2m_spin0(LegArgs a)
             e.e1 = e.e0 + CLS;
             return e;
         };
-        // coefficient operands, loaded PD K-steps ahead: two for FP64, one for
-        // FP32 (whose widest tiling has no registers for more)
-        constexpr int PD = sizeof(T) == 8 ? 2 : 1, NB = 2 * PD;
-        static_assert(KS % NB == 0, "the operand buffers cycle with the K-step index");
-        T bb[NB][2][NU];  // [K-step mod NB][even, odd class row][column tile]
+        // coefficient operands, loaded one K-step ahead
+        T bb[2][2][NU];  // [K-step parity][even, odd class row][column tile]
         auto load_a = [&](int c, int ks, T (&d)[2][NU]) {
             const int le = lfirst + TL * c + 2 * (4 * ks + (lane >> 4));
             const T* pe = Am + (int64_t)(min(le, L) - lb) * a.ldx;
@@ -490,8 +487,7 @@ __global__ __launch_bounds__(NT, 2) void k_a2m_spin0(LegArgs a)
         }
 #pragma unroll
         for (int i = 0; i < 2; ++i) seed_of(sd[i], min(1, nch - 1), i);
-#pragma unroll
-        for (int k = 0; k < PD; ++k) load_a(0, k, bb[k]);
+        load_a(0, 0, bb[0]);
         __syncthreads();
         for (int c = 0; c < nch; ++c) {
             const int b = c & 1;
@@ -504,25 +500,10 @@ __global__ __launch_bounds__(NT, 2) void k_a2m_spin0(LegArgs a)
             auto em0 = emit_to(b ^ 1, 0);
             auto em1 = emit_to(b ^ 1, 1);
             const T* lb_ = lam + b * BUF;
-            // recursion operands of one K-step from the LDS tile, read one K-step
-            // ahead within the chunk where the registers allow (wide FP64 tiles)
-            constexpr bool RA = sizeof(T) == 8 && !NW;
-            T aw[RA ? 2 : 1][4][2];  // [K-step parity][ring tile][even, odd class row]
-            auto read_lam = [&](int ks, T (&d)[4][2]) {
-                const int kl = 4 * ks + (lane >> 4);
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    if (!mine(t)) continue;
-                    d[t][0] = lb_[kl * RS + 16 * t + (lane & 15)];
-                    d[t][1] = lb_[CLS + kl * RS + 16 * t + (lane & 15)];
-                }
-            };
-            if constexpr (RA) read_lam(0, aw[0]);
             static_for<0, KS>([&](auto ki) {
                 constexpr int ks = decltype(ki)::v;
-                if constexpr (ks + PD < KS) load_a(c, ks + PD, bb[(ks + PD) % NB]);
-                else load_a(cn, ks + PD - KS, bb[(ks + PD) % NB]);
-                if constexpr (RA && ks + 1 < KS) read_lam(ks + 1, aw[(ks + 1) & 1]);
+                if constexpr (ks + 1 < KS) load_a(c, ks + 1, bb[(ks + 1) & 1]);
+                else load_a(cn, 0, bb[0]);
                 if constexpr (ks == KS / 2) {
 #pragma unroll
                     for (int i = 0; i < 2; ++i) seed_of(sd[i], min(c + 2, nch - 1), i);
@@ -532,19 +513,13 @@ __global__ __launch_bounds__(NT, 2) void k_a2m_spin0(LegArgs a)
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
                     if (!mine(t)) continue;
-                    T aE, aO;
-                    if constexpr (RA) {
-                        aE = aw[ks & 1][t][0];
-                        aO = aw[ks & 1][t][1];
-                    } else {
-                        const int kl = 4 * ks + (lane >> 4);
-                        aE = lb_[kl * RS + 16 * t + (lane & 15)];
-                        aO = lb_[CLS + kl * RS + 16 * t + (lane & 15)];
-                    }
+                    const int kl = 4 * ks + (lane >> 4);
+                    const T aE = lb_[kl * RS + 16 * t + (lane & 15)];
+                    const T aO = lb_[CLS + kl * RS + 16 * t + (lane & 15)];
 #pragma unroll
                     for (int u = 0; u < NU; ++u) {
-                        accE[t][u] = MF::run(aE, bb[ks % NB][0][u], accE[t][u]);
-                        accO[t][u] = MF::run(aO, bb[ks % NB][1][u], accO[t][u]);
+                        accE[t][u] = MF::run(aE, bb[ks & 1][0][u], accE[t][u]);
+                        accO[t][u] = MF::run(aO, bb[ks & 1][1][u], accO[t][u]);
                     }
                 }
                 rec_group<ks, RPK>(f[0], cp0, cnt0, em0);
@@ -790,8 +765,13 @@ hipError_t launch_m2a_t(const LegArgs& a, hipStream_t st)
         const int nu = pick_nu(4, a.ldx);
         b.ctiles = (int)(a.ldx / (64 * nu));
         const dim3 grid(b.ntiles * b.ctiles * kparts(a));
-        if (narrow(a)) hipLaunchKernelGGL((k_m2a_spin0<T, 1, true>), grid, blk, 0, st, b);
-        else if (nu == 4) hipLaunchKernelGGL((k_m2a_spin0<T, 4>), grid, blk, 0, st, b);
+        if constexpr (sizeof(T) == 4) {
+            if (narrow(a)) {
+                hipLaunchKernelGGL((k_m2a_spin0<T, 1, true>), grid, blk, 0, st, b);
+                return hipGetLastError();
+            }
+        }
+        if (nu == 4) hipLaunchKernelGGL((k_m2a_spin0<T, 4>), grid, blk, 0, st, b);
         else if (nu == 2) hipLaunchKernelGGL((k_m2a_spin0<T, 2>), grid, blk, 0, st, b);
         else hipLaunchKernelGGL((k_m2a_spin0<T, 1>), grid, blk, 0, st, b);
     } else {
@@ -815,41 +795,34 @@ hipError_t launch_m2a_t(const LegArgs& a, hipStream_t st)
     return hipGetLastError();
 }
 
-template <typename T>
-hipError_t launch_a2m_t(const LegArgs& a, hipStream_t st)
+hipError_t launch_a2m_f32(const LegArgs& a, hipStream_t st)
 {
     LegArgs b = a;
-    constexpr bool F64 = sizeof(T) == 8;
     const dim3 blk(NT);
     if (a.spin == 0) {
-        const int nu = pick_nu(F64 ? 2 : 4, a.ldx);
+        const int nu = pick_nu(4, a.ldx);
         b.ctiles = (int)(a.ldx / (64 * nu));
         const dim3 grid(nm_rows(a) * b.ctiles * ((a.rn + A0_TR - 1) / A0_TR) * kparts(a));
-        if constexpr (!F64) {
-            if (nu == 4) {
-                hipLaunchKernelGGL((k_a2m_spin0<T, 4>), grid, blk, 0, st, b);
-                return hipGetLastError();
-            }
-        }
-        if (narrow(a)) hipLaunchKernelGGL((k_a2m_spin0<T, 1, true>), grid, blk, 0, st, b);
-        else if (nu == 1) hipLaunchKernelGGL((k_a2m_spin0<T, 1>), grid, blk, 0, st, b);
-        else hipLaunchKernelGGL((k_a2m_spin0<T, 2>), grid, blk, 0, st, b);
+        if (nu == 4) hipLaunchKernelGGL((k_a2m_spin0<float, 4>), grid, blk, 0, st, b);
+        else if (narrow(a)) hipLaunchKernelGGL((k_a2m_spin0<float, 1, true>), grid, blk, 0, st, b);
+        else if (nu == 1) hipLaunchKernelGGL((k_a2m_spin0<float, 1>), grid, blk, 0, st, b);
+        else hipLaunchKernelGGL((k_a2m_spin0<float, 2>), grid, blk, 0, st, b);
     } else {
         const int nu = pick_nu(2, a.ldx);
         b.ctiles = (int)(a.ldx / (64 * nu));
         const dim3 grid(nm_rows(a) * b.ctiles * ((a.rn + A2_TR - 1) / A2_TR) * kparts(a));
         if (nu == 2) {
-            if (a.eb == 1) hipLaunchKernelGGL((k_a2m_spin2<T, 2, 1>), grid, blk, 0, st, b);
-            else if (a.eb == 2) hipLaunchKernelGGL((k_a2m_spin2<T, 2, 2>), grid, blk, 0, st, b);
-            else hipLaunchKernelGGL((k_a2m_spin2<T, 2, 0>), grid, blk, 0, st, b);
+            if (a.eb == 1) hipLaunchKernelGGL((k_a2m_spin2<float, 2, 1>), grid, blk, 0, st, b);
+            else if (a.eb == 2) hipLaunchKernelGGL((k_a2m_spin2<float, 2, 2>), grid, blk, 0, st, b);
+            else hipLaunchKernelGGL((k_a2m_spin2<float, 2, 0>), grid, blk, 0, st, b);
         } else if (narrow(a)) {
-            if (a.eb == 1) hipLaunchKernelGGL((k_a2m_spin2<T, 1, 1, true>), grid, blk, 0, st, b);
-            else if (a.eb == 2) hipLaunchKernelGGL((k_a2m_spin2<T, 1, 2, true>), grid, blk, 0, st, b);
-            else hipLaunchKernelGGL((k_a2m_spin2<T, 1, 0, true>), grid, blk, 0, st, b);
+            if (a.eb == 1) hipLaunchKernelGGL((k_a2m_spin2<float, 1, 1, true>), grid, blk, 0, st, b);
+            else if (a.eb == 2) hipLaunchKernelGGL((k_a2m_spin2<float, 1, 2, true>), grid, blk, 0, st, b);
+            else hipLaunchKernelGGL((k_a2m_spin2<float, 1, 0, true>), grid, blk, 0, st, b);
         } else {
-            if (a.eb == 1) hipLaunchKernelGGL((k_a2m_spin2<T, 1, 1>), grid, blk, 0, st, b);
-            else if (a.eb == 2) hipLaunchKernelGGL((k_a2m_spin2<T, 1, 2>), grid, blk, 0, st, b);
-            else hipLaunchKernelGGL((k_a2m_spin2<T, 1, 0>), grid, blk, 0, st, b);
+            if (a.eb == 1) hipLaunchKernelGGL((k_a2m_spin2<float, 1, 1>), grid, blk, 0, st, b);
+            else if (a.eb == 2) hipLaunchKernelGGL((k_a2m_spin2<float, 1, 2>), grid, blk, 0, st, b);
+            else hipLaunchKernelGGL((k_a2m_spin2<float, 1, 0>), grid, blk, 0, st, b);
         }
     }
     return hipGetLastError();
@@ -859,6 +832,7 @@ hipError_t launch_a2m_t(const LegArgs& a, hipStream_t st)
 
 hipError_t launch_leg_m2a(const LegArgs& a, int prec, hipStream_t st)
 {
+    if (a.ksplit <= 1 && leg_m2a_reg(a, prec)) return launch_leg_m2a_reg(a, prec, st);
     if (prec == 2) return launch_leg_m2a_bf16(a, st);
     if (prec == 0) return launch_m2a_t<double>(a, st);
     return launch_m2a_t<float>(a, st);
@@ -866,9 +840,9 @@ hipError_t launch_leg_m2a(const LegArgs& a, int prec, hipStream_t st)
 
 hipError_t launch_leg_a2m(const LegArgs& a, int prec, hipStream_t st)
 {
+    if (prec == 0) return launch_leg_a2m_reg(a, st);
     if (prec == 2) return launch_leg_a2m_bf16(a, st);
-    if (prec == 0) return launch_a2m_t<double>(a, st);
-    return launch_a2m_t<float>(a, st);
+    return launch_a2m_f32(a, st);
 }
 
 }  // namespace sht

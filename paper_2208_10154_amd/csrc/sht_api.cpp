@@ -1037,7 +1037,8 @@ int run_level(sht_plan p, double* alm, int nm, int d)
     }
     // A level holds a few m, so its Legendre grids would cover a fraction of the
     // chip with long serial reductions: split each reduction over several
-    // workgroups (about 1024 per launch) that add into cleared outputs.
+    // workgroups (about 1024 per launch) that add into cleared outputs.  The FP64
+    // kernels of k_leg_reg.hip split within a workgroup and write each row once.
     const int ct = (int)std::max<int64_t>(1, p->ldx_cur / 128);
     auto parts = [](int64_t wgs) { return (int)std::min<int64_t>(8, std::max<int64_t>(1, 1024 / std::max<int64_t>(1, wgs))); };
     for (int spin : {0, 2}) {
@@ -1060,7 +1061,7 @@ int run_level(sht_plan p, double* alm, int nm, int d)
         b.accumulate = 1;
         {
             StageTimer t(p, spin == 0 ? SHT_STAGE_M2A_SPIN0 : SHT_STAGE_M2A_SPIN2);
-            a.ksplit = parts((int64_t)nt * ct);
+            a.ksplit = leg_m2a_reg(a, p->prec) ? 1 : parts((int64_t)nt * ct);
             if (a.ksplit > 1) {
                 b.scale = 0.0;  // clear the rows the split map2alm adds into
                 HIPCHK(launch_level_rows(b, ncompl, p->prec, p->stream));
@@ -1075,7 +1076,7 @@ int run_level(sht_plan p, double* alm, int nm, int d)
         {
             StageTimer t(p, spin == 0 ? SHT_STAGE_A2M_SPIN0 : SHT_STAGE_A2M_SPIN2);
             const int tr = spin == 0 ? 64 : 32;  // rings per alm2map tile
-            a.ksplit = parts((int64_t)nl * ct * ((p->rn + tr - 1) / tr));
+            a.ksplit = p->prec == SHT_FP64 ? 1 : parts((int64_t)nl * ct * ((p->rn + tr - 1) / tr));
             if (a.ksplit > 1) {  // clear this spin's rows the split alm2map adds into
                 FftArgs z = f;
                 z.comp0 = spin == 0 ? 0 : 1;

@@ -183,5 +183,10 @@ hipError_t launch_leg_m2a(const LegArgs& a, int prec, hipStream_t st);
 hipError_t launch_leg_a2m(const LegArgs& a, int prec, hipStream_t st);
 hipError_t launch_leg_m2a_bf16(const LegArgs& a, hipStream_t st);
 hipError_t launch_leg_a2m_bf16(const LegArgs& a, hipStream_t st);
+// kernels whose recursion feeds the MFMAs from registers (k_leg_reg.hip): every FP64
+// alm2map, and the map2alm calls leg_m2a_reg picks
+bool leg_m2a_reg(const LegArgs& a, int prec);
+hipError_t launch_leg_m2a_reg(const LegArgs& a, int prec, hipStream_t st);
+hipError_t launch_leg_a2m_reg(const LegArgs& a, hipStream_t st);
 
 }  // namespace sht
