@@ -24,16 +24,11 @@ struct FftLen {
     int ldsc;               // complex values per workgroup = nseq * (blue ? m : n)
     int lstride;            // LDS stride between sequences: >= len + len/16, = 16/nseq mod 16 (see k_fft.hip)
     int lds;                // complex LDS slots per workgroup = nseq * lstride
-    int p2;                 // log2(n) when n is a power of two handled by k_fft_p2.hip, else 0
-    int bp2;                // log2(m) when a Bluestein length m = 2^bp2 is handled by k_fft_p2.hip, else 0
+    int p2;                 // log2(n) when n is a power of two handled by fft_p2.h, else 0
+    int bp2;                // log2(m) when a Bluestein length m = 2^bp2 is handled by fft_p2.h, else 0
     int four;               // 1: n = 4j, four Bluestein DFTs of length j and a radix-4 step (Bluestein of
                             // length n would need a convolution beyond the LDS); k_fft_four.hip
     int sub;                // four: index of the length-j Bluestein entry (chirp, kernel spectrum, twiddles)
-};
-
-struct FftItem {
-    int ring;
-    int pair0;
 };
 
 // ----------------------------------------------------------------------------
@@ -42,7 +37,6 @@ struct FftItem {
 struct FftArgs {
     const RingDev* rings;
     const FftLen* lens;
-    const FftItem* items;
     const double2* tw;      // twiddle pool
     const double2* bhat;    // Bluestein spectra pool
     const double* maps_in;  // forward: maps of the chunk (component stride npix, map-set stride ncomp*npix)
@@ -73,22 +67,37 @@ struct FftArgs {
 // ----------------------------------------------------------------------------
 // Launch wrappers (defined in the .hip files)
 // ----------------------------------------------------------------------------
-// FFT work is launched per LDS class so that small rings are not held to the
-// occupancy of the largest ones.  Workgroups have FFT_THREADS threads;
-// elems = complex values per thread per FFT stage (lds / FFT_THREADS).
+// Rings are grouped into classes that run the same code on the same LDS layout: kind
+// and map pairs per workgroup.  A launch covers, per class, component and ring, only
+// the pair groups that hold map sets of the chunk, so no work list depends on the
+// batch and no workgroup is launched for padding alone.
 constexpr int FFT_THREADS = 512;
+enum FftKind {
+    FFT_GEN2 = 0,    // runtime length, 2, 8 or 16 values per thread and stage
+    FFT_GEN8 = 1,
+    FFT_GEN16 = 2,
+    FFT_FOUR = 3,    // FftLen::four (k_fft_four.hip)
+    FFT_P2 = 16,     // + log2 of the length
+    FFT_BLUE = 32,   // + log2 of the Bluestein convolution length
+};
 struct FftClass {
-    const FftItem* items;
-    int nitems;
-    int lds;     // complex LDS elements per workgroup
-    int elems;   // 2, 8 or 16
-    int p2;      // 0: runtime-length kernels; else log2 of the (convolution) length (k_fft_p2.hip)
-    int blue;    // with p2: Bluestein rings through a power-of-two convolution
-    int four;    // rings of FftLen::four, one map pair per workgroup
+    int kind;
+    const int* rings;  // device: rings of the class
+    int nrings;
+    int nseq;          // map pairs per workgroup
+    int lds;           // complex LDS elements per workgroup (compile-time kinds: their own)
+    int lds_rt;        // the same of the runtime-length code on these rings (k_residual)
+};
+// what a workgroup needs to find its ring and pairs
+struct FftWork {
+    const int* rings;
+    int nrings;
+    int groups;        // pair groups with map sets
+    int nseq;
 };
 // power-of-two ring lengths 2^6 .. 2^12: map pairs per workgroup (0: not handled)
 int p2_seqs_per_group(int logn);
-hipError_t launch_fft_p2(bool forward, const FftArgs& a, const FftClass& c, int ncompl, hipStream_t st);
+int p2_lds(int logn);  // complex LDS elements of the power-of-two and Bluestein kinds
 // the four-step class (FftLen::four): forward and inverse only
 hipError_t launch_fft_four(bool forward, const FftArgs& a, const FftClass& c, int ncompl, hipStream_t st);
 hipError_t launch_fft_forward(const FftArgs& a, const FftClass* cls, int ncls, int ncompl, hipStream_t st);

@@ -23,19 +23,16 @@
 // sequence sq, element i at sq * lstride + i + i / 16: the pad slot every 16
 // values and the sequence stride (congruent to 16/nseq modulo 16) spread
 // power-of-two strides over the banks.
-#include "fft_internal.h"
+#include "fft_p2.h"
+
+#include <algorithm>
+#include <climits>
 
 namespace sht {
 namespace {
 
 constexpr int NT = FFT_THREADS;
 
-__device__ __forceinline__ double2 cmul(double2 a, double2 b)
-{
-    return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-__device__ __forceinline__ double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
-__device__ __forceinline__ double2 csub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
 __device__ __forceinline__ double2 conjd(double2 a) { return make_double2(a.x, -a.y); }
 
 // exact x / d for 0 <= x < 2^16 and 1 <= d < 2^16: with mul = ceil(2^32 / d),
@@ -320,11 +317,6 @@ __device__ __forceinline__ void load_x4(const FftArgs& a, int64_t idx, double2& 
     }
 }
 
-// m values a thread handles per batch in the (un)folding: the global loads of a
-// batch (phase factors, and coefficients when folding) are all issued before
-// the first is used, so a thread waits for memory once per batch, not per m.
-constexpr int MB = 8;
-
 // Unfold the packed spectrum Z = A + i B (both Hermitian) of each sequence onto
 // T_m = e^{-i m phi0} F_{m mod n} for m = 0..lmax and store m-major.  Lanes run
 // over (m, sequence, part): an FP64 row takes two 16-byte parts per map pair
@@ -471,7 +463,7 @@ __device__ __forceinline__ void add_norms(double* ssum, int sq, double va, doubl
 }
 
 struct RingCtx {
-    FftItem it;
+    Item it;
     int comp;
     RingDev rg;
     const FftLen* L;
@@ -480,19 +472,11 @@ struct RingCtx {
     const double2* chirp;
     const double2* bhat;
 };
-// Work item of this workgroup.  The grid is one-dimensional over (component,
-// item); workgroups are dealt to the 8 XCDs round-robin, so the linear index is
-// remapped to give each XCD one contiguous range: the pair groups of a ring,
-// which write neighbouring columns of the same m-major rows, then share an L2.
-__device__ __forceinline__ RingCtx ring_ctx(const FftArgs& a, const FftItem* items, int nitems)
+__device__ __forceinline__ RingCtx ring_ctx(const FftArgs& a, const Item& it)
 {
-    const int nb = (int)gridDim.x, b = (int)blockIdx.x;
-    const int q = nb >> 3, r = nb & 7, x = b & 7;
-    const int idx = x * q + min(x, r) + (b >> 3);
-    const int comp = idx / nitems;
     RingCtx c;
-    c.it = items[idx - comp * nitems];
-    c.comp = a.comp0 + comp;
+    c.it = it;
+    c.comp = it.comp;
     c.rg = a.rings[c.it.ring];
     c.L = a.lens + c.rg.len;
     c.tw_n = a.tw + c.L->tw;
@@ -503,11 +487,9 @@ __device__ __forceinline__ RingCtx ring_ctx(const FftArgs& a, const FftItem* ite
 }
 
 template <int ELEMS>
-__global__ __launch_bounds__(NT, ELEMS == 16 ? 2 : 4) void k_fft_fwd(FftArgs a, const FftItem* items, int nitems)
+__device__ __forceinline__ void gen_fwd(const FftArgs& a, const Item& it, double2* lds)
 {
-    extern __shared__ double2 lds[];
-    const RingCtx c = ring_ctx(a, items, nitems);
-    if (2 * c.it.pair0 >= a.nmaps) return;  // only padding map sets (see k_fft_p2.hip)
+    const RingCtx c = ring_ctx(a, it);
     const int n = c.rg.n, nseq = c.L->nseq, ls = c.L->lstride;
     const FastDiv dn(n);
 
@@ -557,11 +539,9 @@ __global__ __launch_bounds__(NT, ELEMS == 16 ? 2 : 4) void k_fft_fwd(FftArgs a, 
 }
 
 template <int ELEMS>
-__global__ __launch_bounds__(NT, ELEMS == 16 ? 2 : 4) void k_fft_inv(FftArgs a, const FftItem* items, int nitems)
+__device__ __forceinline__ void gen_inv(const FftArgs& a, const Item& it, double2* lds)
 {
-    extern __shared__ double2 lds[];
-    const RingCtx c = ring_ctx(a, items, nitems);
-    if (2 * c.it.pair0 >= a.nmaps) return;  // only padding map sets (see k_fft_p2.hip)
+    const RingCtx c = ring_ctx(a, it);
     const int n = c.rg.n, nseq = c.L->nseq, ls = c.L->lstride;
     const FastDiv dn(n);
 
@@ -582,11 +562,12 @@ __global__ __launch_bounds__(NT, ELEMS == 16 ? 2 : 4) void k_fft_inv(FftArgs a, 
 // T^res_m = e^{-i m phi0} R_{m mod n} written over X; sum |r|^2 = (1/n) sum_j |R_j|^2
 // is accumulated per map (Parseval).
 template <int ELEMS>
-__global__ __launch_bounds__(NT, ELEMS == 16 ? 2 : 4) void k_residual(FftArgs a, const FftItem* items, int nitems)
+__global__ __launch_bounds__(NT, ELEMS == 16 ? 2 : 4) void k_residual(FftArgs a, FftWork w, int cnt)
 {
     extern __shared__ double2 lds[];
-    const RingCtx c = ring_ctx(a, items, nitems);
-    if (2 * c.it.pair0 >= a.nmaps) return;  // only padding map sets (see k_fft_p2.hip)
+    Item it;
+    if (!work_item(w, cnt, blockIdx.x, a.comp0, it)) return;
+    const RingCtx c = ring_ctx(a, it);
     const int n = c.rg.n, nseq = c.L->nseq, ls = c.L->lstride;
     const FastDiv dn(n);
 
@@ -692,56 +673,178 @@ __global__ __launch_bounds__(NT) void k_bluestein_init(const FftLen* lens, const
     }
 }
 
-enum class Kind { Fwd, Inv, Res };
-
-template <int E>
-hipError_t launch_one(Kind kind, const FftArgs& a, const FftClass& c, int ncompl, hipStream_t st)
+// One class of the runtime-length code whose LDS or registers the shared launch below
+// does not hold (16 values per thread)
+template <bool FWD, int ELEMS>
+__global__ __launch_bounds__(NT, 2) void k_fft_gen(FftArgs a, FftWork w, int cnt)
 {
-    size_t sh = (size_t)c.lds * sizeof(double2);
-    dim3 grid(c.nitems * ncompl);
-    if (sh > 65536) {
-        const void* f = (kind == Kind::Fwd) ? (const void*)k_fft_fwd<E>
-                        : (kind == Kind::Inv) ? (const void*)k_fft_inv<E> : (const void*)k_residual<E>;
-        hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
-        if (e != hipSuccess) return e;
+    extern __shared__ double2 lds[];
+    Item it;
+    if (!work_item(w, cnt, blockIdx.x, a.comp0, it)) return;
+    if constexpr (FWD) gen_fwd<ELEMS>(a, it, lds);
+    else gen_inv<ELEMS>(a, it, lds);
+}
+
+// All other classes in one launch: the workgroups of class c are blocks start[c] ..
+// start[c + 1] - 1.  A plan has 10 to 16 classes, most of them a handful of short
+// rings; as launches of their own, one after another, the short classes cost a small
+// batch 10-20 us each (one workgroup's latency), 60% of the FFT time of one IQU triple
+// at nside 128.  Every class holds at most 4608 values in LDS (two workgroups per CU)
+// and 128 registers, so sharing a launch costs the wide classes nothing.  FFT time
+// forward / inverse, launches per class -> one: nside 128, 1 IQU set, 160 / 200 -> 48 /
+// 64 us; nside 512, 1 set, 0.66 / 0.75 -> 0.23 / 0.29 ms; nside 512, 125 sets, 8.9 / 9.2
+// -> 9.0 / 9.3 ms.
+constexpr int MAX_CLASSES = 24;
+struct FftTable {
+    int start[MAX_CLASSES];  // multiples of 8; past the last class INT_MAX
+    int kind[MAX_CLASSES];
+    FftWork work[MAX_CLASSES];
+};
+
+template <bool FWD, int LOGN, bool BLUE, typename XT>
+__device__ __forceinline__ void run_p2(const FftArgs& a, const Item& it, double2* lds)
+{
+    // whole waves past the kind's threads end here (the barriers count the others)
+    if (__builtin_amdgcn_readfirstlane((int)threadIdx.x) >= P2<LOGN>::NTH) return;
+    if constexpr (FWD) {
+        if constexpr (BLUE) fwd_item_blue<LOGN, XT>(a, it, lds);
+        else fwd_item<LOGN, XT>(a, it, lds);
+    } else {
+        if constexpr (BLUE) inv_item_blue<LOGN, XT>(a, it, lds);
+        else inv_item<LOGN, XT>(a, it, lds);
     }
-    if (kind == Kind::Fwd) hipLaunchKernelGGL(k_fft_fwd<E>, grid, dim3(NT), sh, st, a, c.items, c.nitems);
-    else if (kind == Kind::Inv) hipLaunchKernelGGL(k_fft_inv<E>, grid, dim3(NT), sh, st, a, c.items, c.nitems);
-    else hipLaunchKernelGGL(k_residual<E>, grid, dim3(NT), sh, st, a, c.items, c.nitems);
+}
+
+template <bool FWD, typename XT>
+__global__ __launch_bounds__(NT, 4) void k_fft_rings(FftArgs a, FftTable t, int ncompl)
+{
+    extern __shared__ double2 lds[];
+    int c = 0;
+#pragma unroll
+    for (int i = 1; i < MAX_CLASSES; ++i) c += (int)blockIdx.x >= t.start[i] ? 1 : 0;
+    const FftWork w = t.work[c];
+    Item it;
+    if (!work_item(w, work_count(w, ncompl), (int)blockIdx.x - t.start[c], a.comp0, it)) return;
+    switch (t.kind[c]) {
+        case FFT_GEN2: FWD ? gen_fwd<2>(a, it, lds) : gen_inv<2>(a, it, lds); break;
+        case FFT_GEN8: FWD ? gen_fwd<8>(a, it, lds) : gen_inv<8>(a, it, lds); break;
+#define SHT_FFT_KIND(LG)                                                    \
+    case FFT_P2 + LG: run_p2<FWD, LG, false, XT>(a, it, lds); break;        \
+    case FFT_BLUE + LG: run_p2<FWD, LG, true, XT>(a, it, lds); break;
+        SHT_FFT_KIND(6)
+        SHT_FFT_KIND(7)
+        SHT_FFT_KIND(8)
+        SHT_FFT_KIND(9)
+        SHT_FFT_KIND(10)
+        SHT_FFT_KIND(11)
+        SHT_FFT_KIND(12)
+#undef SHT_FFT_KIND
+        default: break;
+    }
+}
+
+hipError_t allow_lds(const void* f, size_t bytes)
+{
+    return bytes > 65536 ? hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) : hipSuccess;
+}
+
+template <bool FWD, typename XT>
+hipError_t launch_rings(const FftArgs& a, const FftClass* cls, int ncls, int ncompl, hipStream_t st)
+{
+    FftTable t;
+    int n = 0, blocks = 0, lds = 0;
+    for (int i = 0; i < ncls; ++i) {
+        const FftClass& c = cls[i];
+        if (c.kind == FFT_FOUR) {
+            hipError_t e = launch_fft_four(FWD, a, c, ncompl, st);
+            if (e != hipSuccess) return e;
+            continue;
+        }
+        const FftWork w = work_of(a, c);
+        const int cnt = work_count(w, ncompl);
+        if (c.kind == FFT_GEN16) {
+            const size_t sh = (size_t)c.lds * sizeof(double2);
+            hipError_t e = allow_lds((const void*)k_fft_gen<FWD, 16>, sh);
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL((k_fft_gen<FWD, 16>), dim3(cnt), dim3(NT), sh, st, a, w, cnt);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+            continue;
+        }
+        if (n == MAX_CLASSES) return hipErrorInvalidValue;
+        t.start[n] = blocks;
+        t.kind[n] = c.kind;
+        t.work[n] = w;
+        ++n;
+        blocks += (cnt + 7) / 8 * 8;
+        lds = std::max(lds, c.lds);
+    }
+    if (!n) return hipSuccess;
+    for (int i = n; i < MAX_CLASSES; ++i) {
+        t.start[i] = INT_MAX;
+        t.kind[i] = 0;
+        t.work[i] = FftWork{};
+    }
+    const size_t sh = (size_t)lds * sizeof(double2);
+    const hipError_t e = allow_lds((const void*)k_fft_rings<FWD, XT>, sh);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_fft_rings<FWD, XT>), dim3(blocks), dim3(NT), sh, st, a, t, ncompl);
     return hipGetLastError();
 }
 
-hipError_t launch_classes(Kind kind, const FftArgs& a, const FftClass* cls, int ncls, int ncompl, hipStream_t st)
+template <int E>
+hipError_t launch_res(const FftArgs& a, const FftClass& c, int ncompl, hipStream_t st)
 {
-    for (int i = 0; i < ncls; ++i) {
-        if (cls[i].nitems <= 0) continue;
-        hipError_t e;
-        if (cls[i].four)  // the residual kernel of the iteration does not cover these rings
-            e = kind == Kind::Res ? hipErrorNotSupported : launch_fft_four(kind == Kind::Fwd, a, cls[i], ncompl, st);
-        else if (cls[i].p2 && kind != Kind::Res) e = launch_fft_p2(kind == Kind::Fwd, a, cls[i], ncompl, st);
-        else if (cls[i].elems <= 2) e = launch_one<2>(kind, a, cls[i], ncompl, st);
-        else if (cls[i].elems <= 8) e = launch_one<8>(kind, a, cls[i], ncompl, st);
-        else e = launch_one<16>(kind, a, cls[i], ncompl, st);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    const FftWork w = work_of(a, c);
+    const int cnt = work_count(w, ncompl);
+    const size_t sh = (size_t)c.lds_rt * sizeof(double2);
+    const hipError_t e = allow_lds((const void*)k_residual<E>, sh);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_residual<E>, dim3(cnt), dim3(NT), sh, st, a, w, cnt);
+    return hipGetLastError();
 }
 
 }  // namespace
 
+int p2_seqs_per_group(int logn)
+{
+    switch (logn) {
+        case 6: return P2<6>::S;
+        case 7: return P2<7>::S;
+        case 8: return P2<8>::S;
+        case 9: return P2<9>::S;
+        case 10: return P2<10>::S;
+        case 11: return P2<11>::S;
+        case 12: return P2<12>::S;
+        default: return 0;
+    }
+}
+
+int p2_lds(int logn)
+{
+    const int n = 1 << logn;
+    return p2_seqs_per_group(logn) * (n + n / 8);
+}
+
 hipError_t launch_fft_forward(const FftArgs& a, const FftClass* cls, int ncls, int ncompl, hipStream_t st)
 {
-    return launch_classes(Kind::Fwd, a, cls, ncls, ncompl, st);
+    return a.x32 ? launch_rings<true, float>(a, cls, ncls, ncompl, st) : launch_rings<true, double>(a, cls, ncls, ncompl, st);
 }
 
 hipError_t launch_fft_inverse(const FftArgs& a, const FftClass* cls, int ncls, int ncompl, hipStream_t st)
 {
-    return launch_classes(Kind::Inv, a, cls, ncls, ncompl, st);
+    return a.x32 ? launch_rings<false, float>(a, cls, ncls, ncompl, st) : launch_rings<false, double>(a, cls, ncls, ncompl, st);
 }
 
 hipError_t launch_residual(const FftArgs& a, const FftClass* cls, int ncls, int ncompl, hipStream_t st)
 {
-    return launch_classes(Kind::Res, a, cls, ncls, ncompl, st);
+    for (int i = 0; i < ncls; ++i) {
+        const int k = cls[i].kind;
+        if (k == FFT_FOUR) return hipErrorNotSupported;  // not covered by the residual kernel
+        const hipError_t e = k == FFT_GEN2 ? launch_res<2>(a, cls[i], ncompl, st)
+                             : k == FFT_GEN16 ? launch_res<16>(a, cls[i], ncompl, st) : launch_res<8>(a, cls[i], ncompl, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_bluestein_init(const FftLen* lens, const int* blue_lens, int nblue, const double2* tw,

@@ -175,35 +175,37 @@ __device__ __forceinline__ void inv_item_four(const FftArgs& a, const Item it, d
 }
 
 template <typename XT>
-__global__ __launch_bounds__(P2<12>::T, 2) void k_fft_fwd_four(FftArgs a, const FftItem* items, int nitems)
+__global__ __launch_bounds__(P2<12>::T, 2) void k_fft_fwd_four(FftArgs a, FftWork w, int cnt)
 {
     extern __shared__ double2 lds[];
-    const Item it = work_item(items, nitems, a.comp0);
-    if (2 * it.pair0 >= a.nmaps) return;  // only padding map sets: nothing reads them
+    Item it;
+    if (!work_item(w, cnt, blockIdx.x, a.comp0, it)) return;
     fwd_item_four<XT>(a, it, lds);
 }
 
 template <typename XT>
-__global__ __launch_bounds__(P2<12>::T, 2) void k_fft_inv_four(FftArgs a, const FftItem* items, int nitems)
+__global__ __launch_bounds__(P2<12>::T, 2) void k_fft_inv_four(FftArgs a, FftWork w, int cnt)
 {
     extern __shared__ double2 lds[];
-    const Item it = work_item(items, nitems, a.comp0);
-    if (2 * it.pair0 >= a.nmaps) return;
+    Item it;
+    if (!work_item(w, cnt, blockIdx.x, a.comp0, it)) return;
     inv_item_four<XT>(a, it, lds);
 }
 
 template <typename XT>
 hipError_t launch_four_x(bool fwd, const FftArgs& a, const FftClass& c, int ncompl, hipStream_t st)
 {
-    const dim3 grid(c.nitems * ncompl);
+    const FftWork w = work_of(a, c);
+    const int cnt = work_count(w, ncompl);
+    const dim3 grid(cnt);
     const size_t sh = (size_t)std::max(c.lds, P2<12>::SEQ) * sizeof(double2);
     const void* f = fwd ? (const void*)k_fft_fwd_four<XT> : (const void*)k_fft_inv_four<XT>;
     if (sh > 65536) {
         hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
         if (e != hipSuccess) return e;
     }
-    if (fwd) hipLaunchKernelGGL((k_fft_fwd_four<XT>), grid, dim3(P2<12>::T), sh, st, a, c.items, c.nitems);
-    else hipLaunchKernelGGL((k_fft_inv_four<XT>), grid, dim3(P2<12>::T), sh, st, a, c.items, c.nitems);
+    if (fwd) hipLaunchKernelGGL((k_fft_fwd_four<XT>), grid, dim3(P2<12>::T), sh, st, a, w, cnt);
+    else hipLaunchKernelGGL((k_fft_inv_four<XT>), grid, dim3(P2<12>::T), sh, st, a, w, cnt);
     return hipGetLastError();
 }
 
@@ -211,7 +213,6 @@ hipError_t launch_four_x(bool fwd, const FftArgs& a, const FftClass& c, int ncom
 
 hipError_t launch_fft_four(bool forward, const FftArgs& a, const FftClass& c, int ncompl, hipStream_t st)
 {
-    if (c.nitems <= 0) return hipSuccess;
     return a.x32 ? launch_four_x<float>(forward, a, c, ncompl, st) : launch_four_x<double>(forward, a, c, ncompl, st);
 }
 

@@ -96,16 +96,7 @@ struct sht_plan_s {
     double2* d_bhat = nullptr;
     SeedSet s0, s2;
 
-    // FFT work items for the current chunk size
-    // FFT work lists per chunk width (map pairs per chunk), kept so that changing
-    // the chunk between calls (serving batches of different sizes) reuploads nothing
-    struct ItemSet {
-        Dev dev;
-        std::vector<FftClass> classes;
-    };
-    std::map<int, ItemSet> item_sets;
-    std::vector<FftClass> classes;  // the current width's classes
-    int items_npairs = -1;
+    std::vector<FftClass> classes;  // ring classes of the FFT launches
     int64_t ldx_cur = 0;            // row pitch of the m-major arrays for the chunk being run
     int nm_cur = 0;                 // map sets of the chunk being run
 
@@ -294,7 +285,7 @@ int build_fft(sht_plan p)
                 pool.push_back(make_double2((double)cosl(ang), (double)(-sinl(ang))));
             }
             // convolution length: a power of two up to 2^12 (compile-time
-            // kernels of k_fft_p2.hip), else the smallest 7-smooth length
+            // kernels of fft_p2.h), else the smallest 7-smooth length
             int pm = 64, lg = 6;
             while (pm < 2 * r.n - 1) { pm *= 2; ++lg; }
             if (lg <= 12 && p2_seqs_per_group(lg) > 0) {
@@ -364,8 +355,9 @@ int build_fft(sht_plan p)
         L.nstage = (int)rad.size();
         for (size_t k = 0; k < rad.size(); ++k) L.radix[k] = rad[k];
         if (len > 16 * FFT_THREADS) return fail(SHT_ERR_UNSUPPORTED, "ring FFT length beyond the LDS plan");
-        // map pairs per workgroup: fill up to 1024 complex values when small, else 4096
-        int cap = (len <= 1024) ? 1024 : (len <= 4096 ? 4096 : 8192);
+        // map pairs per workgroup: up to 16, filling 4096 complex values (a row store then
+        // covers whole 64-byte pieces; 1024 values left one pair, 32 bytes, to a ring of 800)
+        const int cap = len <= 4096 ? 4096 : 8192;
         L.lgseq = 0;
         while (L.lgseq < 4 && (2 << L.lgseq) * len <= cap) ++L.lgseq;
         L.nseq = 1 << L.lgseq;
@@ -430,52 +422,38 @@ int build_fft(sht_plan p)
     return SHT_OK;
 }
 
-// FFT work items (ring, first pair) for npairs map pairs, grouped by LDS class.
-int build_items(sht_plan p, int npairs)
+// Ring classes of the FFT launches (see FftClass), short rings first: their few
+// workgroups are the longest chains (many m fold onto few bins).
+int build_classes(sht_plan p)
 {
-    if (p->items_npairs == npairs) return SHT_OK;
-    auto found = p->item_sets.find(npairs);
-    if (found != p->item_sets.end()) {
-        p->classes = found->second.classes;
-        p->items_npairs = npairs;
-        return SHT_OK;
-    }
-    // classes 0..2: runtime-length kernels by LDS size; 3 + (k - 6): length 2^k;
-    // 10 + (k - 6): Bluestein through length 2^k; 17: four-step (n = 4j)
-    constexpr int NCLS = 3 + 7 + 7 + 1;
-    std::vector<FftItem> cls_items[NCLS];
-    int lds[NCLS] = {};
+    std::map<std::pair<int, int>, std::vector<int>> by;  // (kind, map pairs per workgroup) -> rings
     for (int r = 0; r < p->nring; ++r) {
         const FftLen& L = p->lens[p->rings[r].len];
-        int c = (L.ldsc <= 2 * FFT_THREADS) ? 0 : (L.ldsc <= 8 * FFT_THREADS ? 1 : 2);
-        if (L.p2) c = 3 + (L.p2 - 6);
-        if (L.bp2) c = 10 + (L.bp2 - 6);
-        if (L.four) c = NCLS - 1;
-        lds[c] = std::max(lds[c], L.lds);
-        if (npairs % L.nseq) return fail(SHT_ERR_UNSUPPORTED, "map pairs per chunk not a multiple of the ring batch");
-        for (int q = 0; q < npairs; q += L.nseq) cls_items[c].push_back(FftItem{r, q});
+        const int kind = L.four ? FFT_FOUR : L.p2 ? FFT_P2 + L.p2 : L.bp2 ? FFT_BLUE + L.bp2
+                         : L.ldsc <= 2 * FFT_THREADS ? FFT_GEN2 : L.ldsc <= 8 * FFT_THREADS ? FFT_GEN8 : FFT_GEN16;
+        by[{kind, L.nseq}].push_back(r);
     }
-    std::vector<FftItem> all;
-    size_t off[NCLS];
-    for (int c = 0; c < NCLS; ++c) { off[c] = all.size(); all.insert(all.end(), cls_items[c].begin(), cls_items[c].end()); }
-    sht_plan_s::ItemSet set;
-    size_t bytes = std::max<size_t>(1, all.size()) * sizeof(FftItem);
-    HIPCHK(hipMalloc(&set.dev.p, bytes));
-    set.dev.n = bytes;
-    HIPCHK(hipMemcpy(set.dev.p, all.data(), all.size() * sizeof(FftItem), hipMemcpyHostToDevice));
-    p->table_bytes += bytes;
-    // the residual kernel runs every class with the runtime-length code: the
-    // power-of-two classes hold at most 4096 values per workgroup (8 per thread)
-    for (int c = 0; c < NCLS; ++c) {
-        const int elems = c == 0 ? 2 : (c == 2 ? 16 : 8);
-        const int lg = c >= 10 ? c - 10 + 6 : (c >= 3 ? c - 3 + 6 : 0);
-        const bool four = (c == NCLS - 1);
-        set.classes.push_back(FftClass{(const FftItem*)set.dev.p + off[c], (int)cls_items[c].size(), lds[c], elems,
-                                       four ? 0 : lg, (c >= 10 && !four) ? 1 : 0, four ? 1 : 0});
+    std::vector<int> all;
+    for (auto& kv : by) {
+        FftClass c{};
+        c.kind = kv.first.first;
+        c.nseq = kv.first.second;
+        c.nrings = (int)kv.second.size();
+        for (int r : kv.second) c.lds_rt = std::max(c.lds_rt, p->lens[p->rings[r].len].lds);
+        c.lds = c.kind >= FFT_P2 ? p2_lds(c.kind & 15) : c.lds_rt;
+        p->classes.push_back(c);
+        all.insert(all.end(), kv.second.begin(), kv.second.end());
     }
-    p->classes = set.classes;
-    p->item_sets.emplace(npairs, std::move(set));
-    p->items_npairs = npairs;
+    Dev d;
+    const int rc = upload(p, d, all);
+    if (rc) return rc;
+    const int* at = (const int*)d.p;
+    for (FftClass& c : p->classes) {
+        c.rings = at;
+        at += c.nrings;
+    }
+    std::stable_sort(p->classes.begin(), p->classes.end(),
+                     [](const FftClass& a, const FftClass& b) { return a.nrings < b.nrings; });
     return SHT_OK;
 }
 
@@ -818,17 +796,16 @@ int prep(sht_plan p)
     if (rc) return rc;
     p->ldx_cur = ldx_for(p->chunk);
     p->nm_cur = p->chunk;
-    return build_items(p, (int)(p->ldx_cur / 4));
+    return SHT_OK;
 }
 
 // Narrow the m-major row pitch to what a chunk of nm map sets needs (a last,
 // partial chunk then computes only its own columns); the component arrays keep
 // the full chunk's spacing, so any narrower pitch fits the workspace.
-int use_width(sht_plan p, int nm)
+void use_width(sht_plan p, int nm)
 {
     p->ldx_cur = ldx_for(nm);
     p->nm_cur = nm;
-    return build_items(p, (int)(p->ldx_cur / 4));
 }
 
 // Component selection (enum sht_comp bits) of the selective transforms.  The
@@ -1123,8 +1100,6 @@ void destroy_all(sht_plan p)
     drop_records(p);
     for (auto& d : p->owned)
         if (d.p) (void)hipFree(d.p);
-    for (auto& kv : p->item_sets)
-        if (kv.second.dev.p) (void)hipFree(kv.second.dev.p);
     if (p->ws && p->ws_owned) (void)hipFree(p->ws);
     if (p->F) (void)hipFree(p->F);
     if (p->norms) (void)hipFree(p->norms);
@@ -1184,6 +1159,7 @@ int create_plan(sht_plan* out, int nside, int lmax, int spin, int nmaps, int par
     build_rings(p);
     p->nrc = (p->rn + RCHUNK - 1) / RCHUNK;
     int rc = build_fft(p);
+    if (!rc) rc = build_classes(p);
     if (!rc && nparts > 1) rc = upload(p, p->d_own, p->own);
     if (!rc && nparts > 1) rc = upload(p, p->d_mlist, mlist);
     if (!rc && p->nown == 0) rc = fail(SHT_ERR_ARG, "this part owns no order m (more parts than m pairs)");
@@ -1194,16 +1170,8 @@ int create_plan(sht_plan* out, int nside, int lmax, int spin, int nmaps, int par
         p->chunk = default_chunk(p);
         rc = prep(p);
     }
-    // the static workspace of sht_alm2map_noalloc and the FFT work lists of every
-    // chunk width it may use, so that call allocates nothing
+    // the static workspace of sht_alm2map_noalloc
     if (!rc) rc = resolve_scratch(dev, &p->scratch);
-    if (!rc) {
-        std::vector<int64_t> widths;
-        for (int k = 1; k <= noalloc_chunk(p, SHT_FP32); ++k)
-            if (widths.empty() || widths.back() != ldx_for(k)) widths.push_back(ldx_for(k));
-        for (size_t i = 0; i < widths.size() && !rc; ++i) rc = build_items(p, (int)(widths[i] / 4));
-        if (!rc) rc = build_items(p, (int)(p->ldx_cur / 4));
-    }
     if (!rc) {
         hipError_t e = hipStreamSynchronize(p->stream);
         if (e != hipSuccess) rc = fail(SHT_ERR_DEVICE, std::string("plan set-up: ") + hipGetErrorString(e));
@@ -1318,7 +1286,7 @@ int sht_alm2map_sel(sht_plan p, int comps, const double* alm, double* map)
     const int64_t mstride = (int64_t)p->ncomp * p->npix;
     for (int k0 = 0; k0 < p->nmaps; k0 += p->chunk) {
         int nm = std::min(p->chunk, p->nmaps - k0);
-        if ((rc = use_width(p, nm))) return rc;
+        use_width(p, nm);
         if ((rc = run_a2m(p, alm + k0 * astride, nm, comps))) return rc;
         if ((rc = run_fft_inv(p, map + k0 * mstride, nm, comps))) return rc;
     }
@@ -1337,10 +1305,6 @@ int sht_alm2map_noalloc(sht_plan p, const double* alm, double* map)
         return fail(SHT_ERR_ARG, "the workspace of one map set (" + std::to_string(ws_need_at(p, 1, p->prec)) +
                                      " bytes) exceeds the static workspace of " + std::to_string(SCRATCH_BYTES) +
                                      " bytes");
-    for (int k0 = 0; k0 < p->nmaps; k0 += c) {  // every width's work list exists (plan creation)
-        const int npairs = (int)(ldx_for(std::min(c, p->nmaps - k0)) / 4);
-        if (!p->item_sets.count(npairs)) return fail(SHT_ERR_UNSUPPORTED, "no FFT work list for this chunk width");
-    }
     // run the plan's own stages on the static workspace, with chunks of c map sets,
     // no stage timing (events), then give the plan back its own workspace
     void* const ws = p->ws;
@@ -1357,8 +1321,8 @@ int sht_alm2map_noalloc(sht_plan p, const double* alm, double* map)
     const int64_t mstride = (int64_t)p->ncomp * p->npix;
     for (int k0 = 0; k0 < p->nmaps && !rc; k0 += c) {
         const int nm = std::min(c, p->nmaps - k0);
-        rc = use_width(p, nm);
-        if (!rc) rc = run_a2m(p, alm + k0 * astride, nm, SHT_COMP_ALL);
+        use_width(p, nm);
+        rc = run_a2m(p, alm + k0 * astride, nm, SHT_COMP_ALL);
         if (!rc) rc = run_fft_inv(p, map + k0 * mstride, nm, SHT_COMP_ALL);
     }
     p->ws = ws;
@@ -1368,8 +1332,7 @@ int sht_alm2map_noalloc(sht_plan p, const double* alm, double* map)
     p->chunk = chunk;
     p->ldx_cur = ldx;
     p->nm_cur = nm_cur;
-    const int rc2 = build_items(p, (int)(ldx / 4));  // cached: selects the plan's list again
-    return rc ? rc : rc2;
+    return rc;
 }
 
 int sht_alm2map(sht_plan p, const double* alm, double* map)
@@ -1390,7 +1353,7 @@ int sht_map2alm_sel(sht_plan p, int comps, const double* map, double* alm)
     const int64_t mstride = (int64_t)p->ncomp * p->npix;
     for (int k0 = 0; k0 < p->nmaps; k0 += p->chunk) {
         int nm = std::min(p->chunk, p->nmaps - k0);
-        if ((rc = use_width(p, nm))) return rc;
+        use_width(p, nm);
         FftArgs f = fft_args(p, nm);
         f.maps_in = map + k0 * mstride;
         int ncompl = p->ncomp;
@@ -1425,7 +1388,7 @@ int sht_eb_split(sht_plan p, const double* map, double* alm, double* map_e, doub
     const int64_t mstride = (int64_t)p->ncomp * p->npix;
     for (int k0 = 0; k0 < p->nmaps; k0 += p->chunk) {
         int nm = std::min(p->chunk, p->nmaps - k0);
-        if ((rc = use_width(p, nm))) return rc;
+        use_width(p, nm);
         FftArgs f = fft_args(p, nm);
         f.maps_in = map + k0 * mstride;
         {
@@ -1458,7 +1421,7 @@ int sht_map2alm_iter(sht_plan p, const double* map, double* alm, int niter, doub
     std::vector<double> sums(niter + 1, 0.0), hn;
     for (int k0 = 0; k0 < p->nmaps; k0 += p->chunk) {
         int nm = std::min(p->chunk, p->nmaps - k0);
-        if ((rc = use_width(p, nm))) return rc;
+        use_width(p, nm);
         double* a = alm + k0 * astride;
         FftArgs f = fft_args(p, nm);
         f.maps_in = map + k0 * mstride;
@@ -1526,7 +1489,7 @@ int sht_map2alm_immediate(sht_plan p, const double* map, double* alm, int niter,
     };
     for (int k0 = 0; k0 < p->nmaps; k0 += p->chunk) {
         int nm = std::min(p->chunk, p->nmaps - k0);
-        if ((rc = use_width(p, nm))) return rc;
+        use_width(p, nm);
         double* a = alm + k0 * astride;
         FftArgs f = fft_args(p, nm);
         f.maps_in = map + k0 * mstride;
