@@ -10,6 +10,7 @@
 // work of the boundary: dsigma and accumulation for map2alm (the paper's GEMM
 // alpha/beta, Sec. 3.1 item 7) and the B <-> iB change of variable of Sec. 2.3.
 #include <algorithm>
+#include <type_traits>
 
 #include "sht_internal.h"
 
@@ -17,9 +18,15 @@ namespace sht {
 namespace {
 
 constexpr int NT = 256;
-constexpr int TLB = 64;  // l per tile (= TL)
-constexpr int TK = 32;   // maps per tile
-constexpr int PER = 2 * TK * TLB / NT;  // tile elements per thread
+// Tiles of TLB l x TK maps: 64 x 32, or for a chunk of at most 16, 8 or 4 map sets only
+// the columns that hold them (the rows' pitch stays 64 columns) and as many more l: at
+// nside 512 one IQU set moved 64 columns for 2, 0.65 ms of a 3.8 ms round trip, 0.13 now.
+template <int TK>
+struct Tile {
+    static constexpr int L = TK == 32 ? 64 : (TK == 16 ? 64 : (TK == 8 ? 128 : 256));
+    static constexpr int PER = 2 * TK * L / NT;  // tile elements per thread
+    static constexpr bool LIST = L == 64;        // work list of 64-row tiles; else a fixed number per m
+};
 
 __device__ __forceinline__ int64_t calm(int L, int l, int m, int part)
 {
@@ -27,6 +34,10 @@ __device__ __forceinline__ int64_t calm(int L, int l, int m, int part)
     if (m == 0) return -1;
     return (int64_t)(L + 1 - m) * (L + 1) + (l - m);
 }
+
+// (m, l tile, block of maps) of a tile; false past the m's rows
+template <int TK>
+__device__ __forceinline__ bool tile_of(const AlmArgs& a, int& m, int& lt, int& kb);
 
 __device__ __forceinline__ void decode(const int* off, int lmax, const int* mlist, int nlist, int C, int g, int& m,
                                        int& lt, int& kb)
@@ -43,16 +54,46 @@ __device__ __forceinline__ void decode(const int* off, int lmax, const int* mlis
     lt = r - kb * nlt;
 }
 
+template <int TK>
+__device__ __forceinline__ bool tile_of(const AlmArgs& a, int& m, int& lt, int& kb)
+{
+    if constexpr (Tile<TK>::LIST) {
+        if ((int)blockIdx.x >= a.ntiles * (TK == 32 ? a.kblocks : 1)) return false;
+        decode(a.tileoff, a.lmax, a.mlist, a.nlist, TK == 32 ? a.kblocks : 1, blockIdx.x, m, lt, kb);
+        return true;
+    } else {
+        const int nt = (a.lmax + Tile<TK>::L) / Tile<TK>::L, i = (int)blockIdx.x / nt;
+        m = a.mlist ? a.mlist[i] : i;
+        lt = (int)blockIdx.x - i * nt;
+        kb = 0;
+        return a.rowoff[m + 1] > a.rowoff[m] && lbase(a.spin, m) + lt * Tile<TK>::L <= a.lmax;
+    }
+}
+template <int TK>
+int blocks_of(const AlmArgs& a)
+{
+    if (Tile<TK>::LIST) return a.ntiles * (TK == 32 ? a.kblocks : 1);
+    return (a.mlist ? a.nlist : a.lmax + 1) * ((a.lmax + Tile<TK>::L) / Tile<TK>::L);
+}
+
+// One launch lays out both spins: the first n0 values of blockIdx.y are components of
+// a0, the others of a1.
+#define SHT_ALM_OF_BLOCK                                       \
+    const bool first_args = (int)blockIdx.y < n0;              \
+    const AlmArgs a = first_args ? a0 : a1;                    \
+    const int comp = a.comp0 + (int)blockIdx.y - (first_args ? 0 : n0);
+
 // compact (FP64) -> m-major operand rows (T = double or float).
 // comp: component of the alm array; kind 0 = plain (T or E), 1 = B stored as B' = i a_B.
-template <typename T>
-__global__ __launch_bounds__(NT) void k_to_mmajor(AlmArgs a)
+template <typename T, int TK>
+__global__ __launch_bounds__(NT) void k_to_mmajor(AlmArgs a0, AlmArgs a1, int n0)
 {
+    SHT_ALM_OF_BLOCK
+    constexpr int TLB = Tile<TK>::L, PER = Tile<TK>::PER;
     __shared__ double tile[TLB][2 * TK + 1];
-    const int comp = a.comp0 + blockIdx.y;
     const int kind = (a.spin == 2 && comp == 2) ? 1 : 0;
     int m, lt, kb;
-    decode(a.tileoff, a.lmax, a.mlist, a.nlist, a.kblocks, blockIdx.x, m, lt, kb);
+    if (!tile_of<TK>(a, m, lt, kb)) return;
     const int L = a.lmax;
     const int lb = lbase(a.spin, m);
     const int l0 = lb + lt * TLB;
@@ -126,14 +167,15 @@ __global__ __launch_bounds__(NT) void k_to_mmajor(AlmArgs a)
 // have no l < 2 coefficients: the first tile of m < 2 clears them (store mode).
 // TO != void: also write scale * rows as the alm2map operand of the same update
 // (at Aop, in TO's format), from the tile already in LDS.
-template <typename T, typename TO = void>
-__global__ __launch_bounds__(NT) void k_from_mmajor(AlmArgs a)
+template <typename T, int TK, typename TO = void>
+__global__ __launch_bounds__(NT) void k_from_mmajor(AlmArgs a0, AlmArgs a1, int n0)
 {
+    SHT_ALM_OF_BLOCK
+    constexpr int TLB = Tile<TK>::L, PER = Tile<TK>::PER;
     __shared__ double tile[TLB][2 * TK + 1];
-    const int comp = a.comp0 + blockIdx.y;
     const int kind = (a.spin == 2 && comp == 2) ? 1 : 0;
     int m, lt, kb;
-    decode(a.tileoff, a.lmax, a.mlist, a.nlist, a.kblocks, blockIdx.x, m, lt, kb);
+    if (!tile_of<TK>(a, m, lt, kb)) return;
     const int L = a.lmax;
     const int lb = lbase(a.spin, m);
     const int l0 = lb + lt * TLB;
@@ -238,6 +280,7 @@ __global__ __launch_bounds__(NT) void k_level_rows(AlmArgs a)
     const int comp = a.comp0 + blockIdx.y;
     const int kind = (a.spin == 2 && comp == 2) ? 1 : 0;
     int m, lt, kb;
+    constexpr int TK = 32, TLB = 64;
     decode(a.tileoff, a.lmax, a.mlist, a.nlist, a.kblocks, blockIdx.x, m, lt, kb);
     const int L = a.lmax;
     const int lb = lbase(a.spin, m);
@@ -283,30 +326,48 @@ hipError_t launch_level_rows(const AlmArgs& a, int ncompl, int prec, hipStream_t
     return hipGetLastError();
 }
 
-hipError_t launch_level_commit(const AlmArgs& a, int ncompl, int prec, hipStream_t st)
+// grid and f(tile width) for the components of a (na of them) and b (nb)
+template <typename F>
+hipError_t with_tile(const AlmArgs& a, int na, const AlmArgs& b, int nb, F&& f)
 {
-    dim3 grid(a.ntiles * a.kblocks, ncompl);
-    if (prec == 0) hipLaunchKernelGGL((k_from_mmajor<double, double>), grid, dim3(NT), 0, st, a);
-    else if (prec == 2) hipLaunchKernelGGL((k_from_mmajor<float, uint64_t>), grid, dim3(NT), 0, st, a);
-    else hipLaunchKernelGGL((k_from_mmajor<float, float>), grid, dim3(NT), 0, st, a);
+    auto go = [&](auto w) {
+        constexpr int TK = decltype(w)::value;
+        f(w, dim3(std::max(na ? blocks_of<TK>(a) : 0, nb ? blocks_of<TK>(b) : 0), na + nb));
+    };
+    if (a.nmaps > 16) go(std::integral_constant<int, 32>{});
+    else if (a.nmaps > 8) go(std::integral_constant<int, 16>{});
+    else if (a.nmaps > 4) go(std::integral_constant<int, 8>{});
+    else go(std::integral_constant<int, 4>{});
     return hipGetLastError();
 }
 
-hipError_t launch_alm_to_mmajor(const AlmArgs& a, int ncompl, int prec, hipStream_t st)
+hipError_t launch_level_commit(const AlmArgs& a, int na, const AlmArgs& b, int nb, int prec, hipStream_t st)
 {
-    dim3 grid(a.ntiles * a.kblocks, ncompl);
-    if (prec == 0) hipLaunchKernelGGL(k_to_mmajor<double>, grid, dim3(NT), 0, st, a);
-    else if (prec == 2) hipLaunchKernelGGL(k_to_mmajor<uint64_t>, grid, dim3(NT), 0, st, a);  // split-BF16 words
-    else hipLaunchKernelGGL(k_to_mmajor<float>, grid, dim3(NT), 0, st, a);
-    return hipGetLastError();
+    return with_tile(a, na, b, nb, [&](auto w, dim3 grid) {
+        constexpr int TK = decltype(w)::value;
+        if (prec == 0) hipLaunchKernelGGL((k_from_mmajor<double, TK, double>), grid, dim3(NT), 0, st, a, b, na);
+        else if (prec == 2) hipLaunchKernelGGL((k_from_mmajor<float, TK, uint64_t>), grid, dim3(NT), 0, st, a, b, na);
+        else hipLaunchKernelGGL((k_from_mmajor<float, TK, float>), grid, dim3(NT), 0, st, a, b, na);
+    });
 }
 
-hipError_t launch_alm_from_mmajor(const AlmArgs& a, int ncompl, int prec, hipStream_t st)
+hipError_t launch_alm_to_mmajor(const AlmArgs& a, int na, const AlmArgs& b, int nb, int prec, hipStream_t st)
 {
-    dim3 grid(a.ntiles * a.kblocks, ncompl);
-    if (prec == 0) hipLaunchKernelGGL(k_from_mmajor<double>, grid, dim3(NT), 0, st, a);
-    else hipLaunchKernelGGL(k_from_mmajor<float>, grid, dim3(NT), 0, st, a);
-    return hipGetLastError();
+    return with_tile(a, na, b, nb, [&](auto w, dim3 grid) {
+        constexpr int TK = decltype(w)::value;
+        if (prec == 0) hipLaunchKernelGGL((k_to_mmajor<double, TK>), grid, dim3(NT), 0, st, a, b, na);
+        else if (prec == 2) hipLaunchKernelGGL((k_to_mmajor<uint64_t, TK>), grid, dim3(NT), 0, st, a, b, na);  // split-BF16 words
+        else hipLaunchKernelGGL((k_to_mmajor<float, TK>), grid, dim3(NT), 0, st, a, b, na);
+    });
+}
+
+hipError_t launch_alm_from_mmajor(const AlmArgs& a, int na, const AlmArgs& b, int nb, int prec, hipStream_t st)
+{
+    return with_tile(a, na, b, nb, [&](auto w, dim3 grid) {
+        constexpr int TK = decltype(w)::value;
+        if (prec == 0) hipLaunchKernelGGL((k_from_mmajor<double, TK>), grid, dim3(NT), 0, st, a, b, na);
+        else hipLaunchKernelGGL((k_from_mmajor<float, TK>), grid, dim3(NT), 0, st, a, b, na);
+    });
 }
 
 }  // namespace sht

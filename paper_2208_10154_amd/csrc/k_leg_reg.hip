@@ -100,9 +100,9 @@ constexpr int FEW_M = 128;
 __host__ __device__ inline int m_group(const LegArgs& a) { return nm_rows(a) < FEW_M ? 1 : 8; }
 
 // the same number of blocks per m (alm2map): m index and block of it
-__device__ __forceinline__ void unit_of(const LegArgs& a, int per, int& unit, int& slot)
+__device__ __forceinline__ void unit_of(const LegArgs& a, int b, int per, int& unit, int& slot)
 {
-    const int b = blockIdx.x, g = m_group(a), pos = g == 8 ? b >> 3 : b, q = pos / per;
+    const int g = m_group(a), pos = g == 8 ? b >> 3 : b, q = pos / per;
     unit = q * g + (g == 8 ? b & 7 : 0);
     slot = pos - q * per;
 }
@@ -124,16 +124,17 @@ int blocks_m2a(const LegArgs& a, int rtl, int ncg)
     return n * g * ncg;
 }
 // the (m, l tile, column group) of this block; false past the m's tiles
-__device__ __forceinline__ bool m2a_task(const LegArgs& a, int rtl, int ncg, int& m, int& lt, int& cg)
+__device__ __forceinline__ bool m2a_task(const LegArgs& a, int b, int rtl, int ncg, int& m, int& lt, int& cg)
 {
     int slot;
     if (a.mlist) {
-        const int per = tile_bound(a, rtl, 0) * ncg, u = (int)blockIdx.x / per;
+        const int per = tile_bound(a, rtl, 0) * ncg, u = b / per;
+        if (u >= a.nlist) return false;
         m = a.mlist[u];
-        slot = (int)blockIdx.x - u * per;
+        slot = b - u * per;
     } else {
         const int g = m_group(a);
-        int rem = g == 8 ? (int)blockIdx.x >> 3 : (int)blockIdx.x, q = 0, nt = tile_bound(a, rtl, 0);
+        int rem = g == 8 ? b >> 3 : b, q = 0, nt = tile_bound(a, rtl, 0);
         while (nt > 1) {  // deals q .. e - 1 have nt tiles per m
             const int e = (a.lmax + 1 - (nt - 1) * rtl + g - 1) / g, n = (e - q) * nt * ncg;
             if (rem < n) break;
@@ -143,7 +144,7 @@ __device__ __forceinline__ bool m2a_task(const LegArgs& a, int rtl, int ncg, int
         }
         const int d = rem / (nt * ncg);
         slot = rem - d * nt * ncg;
-        m = (q + d) * g + (g == 8 ? (int)blockIdx.x & 7 : 0);
+        m = (q + d) * g + (g == 8 ? b & 7 : 0);
         if (m > a.lmax) return false;
     }
     m = __builtin_amdgcn_readfirstlane(m);
@@ -250,7 +251,7 @@ __global__ __launch_bounds__(64, 2) void k_m2a_reg32(LegArgs a, int ncg)
     const int L = a.lmax;
 
     int m, lt, cg;
-    if (!m2a_task(a, RTL, ncg, m, lt, cg)) return;
+    if (!m2a_task(a, blockIdx.x, RTL, ncg, m, lt, cg)) return;
     const int lb = lbase(SPIN, m);
     const int l0 = lb + lt * RTL, lend = min(L, l0 + RTL - 1);
     const int ls = l0 + SEG * i, cnt = L - ls + 1;  // this lane's segment; rows in range
@@ -404,7 +405,7 @@ __global__ __launch_bounds__(64, 2) void k_m2a_reg32(LegArgs a, int ncg)
 //    two map sets.  Rows past lmax go on harmlessly and are not stored.
 // ============================================================================
 template <int SPIN, int NC, int C, int TS, bool SPLIT>
-__global__ __launch_bounds__(SPLIT ? 64 * RWAVES : 64, 2) void k_m2a_reg64(LegArgs a, int ncg)
+__device__ __forceinline__ void m2a_reg64(const LegArgs& a, int block, int ncg, double* lds)
 {
     using MF = Mf64<NC>;
     constexpr int MS = SPIN == 2 ? NC / 2 : NC;  // columns of one component per tile
@@ -415,7 +416,7 @@ __global__ __launch_bounds__(SPLIT ? 64 * RWAVES : 64, 2) void k_m2a_reg64(LegAr
     const int L = a.lmax;
 
     int m, lt, cg;
-    if (!m2a_task(a, RTL64, ncg, m, lt, cg)) return;
+    if (!m2a_task(a, block, RTL64, ncg, m, lt, cg)) return;
     const int lb = lbase(SPIN, m);
     const int l0 = lb + lt * RTL64, lend = min(L, l0 + RTL64 - 1);
     const int ls = l0 + TS * i;  // first row of this lane's run
@@ -641,12 +642,13 @@ __global__ __launch_bounds__(SPLIT ? 64 * RWAVES : 64, 2) void k_m2a_reg64(LegAr
             }
         }
     };
-    __shared__ typename MF::acc part[SPLIT ? RWAVES : 1][SPLIT ? TS : 1][SPLIT ? C : 1][SPLIT ? 64 : 1];
+    // partial sums [wave][row][tile][lane]
+    typename MF::acc* part = reinterpret_cast<typename MF::acc*>(lds) + lane;
     if constexpr (SPLIT) {
 #pragma unroll
         for (int t = 0; t < TS; ++t)
 #pragma unroll
-            for (int c = 0; c < C; ++c) part[wave][t][c][lane] = acc[t][c];
+            for (int c = 0; c < C; ++c) part[((wave * TS + t) * C + c) * 64] = acc[t][c];
         __syncthreads();
     }
     double n1 = 1.0, n0 = 1.0;
@@ -661,13 +663,34 @@ __global__ __launch_bounds__(SPLIT ? 64 * RWAVES : 64, 2) void k_m2a_reg64(LegAr
             typename MF::acc v[C];
 #pragma unroll
             for (int c = 0; c < C; ++c) {
-                v[c] = part[0][t][c][lane];
+                v[c] = part[(t * C + c) * 64];
 #pragma unroll
-                for (int w = 1; w < RWAVES; ++w) v[c] += part[w][t][c][lane];
+                for (int w = 1; w < RWAVES; ++w) v[c] += part[((w * TS + t) * C + c) * 64];
             }
             store(t, n, v);
         }
     }
+}
+
+// doubles of LDS of a split block
+template <int NC, int C, int TS>
+constexpr int split_lds() { return RWAVES * TS * C * 64 * Mf64<NC>::AR; }
+
+template <int SPIN, int NC, int C, int TS, bool SPLIT>
+__global__ __launch_bounds__(SPLIT ? 64 * RWAVES : 64, 2) void k_m2a_reg64(LegArgs a, int ncg)
+{
+    __shared__ alignas(32) double lds[SPLIT ? split_lds<NC, C, TS>() : 4];
+    m2a_reg64<SPIN, NC, C, TS, SPLIT>(a, blockIdx.x, ncg, lds);
+}
+
+// Both spins of a small call in one launch: blocks below n2 are spin 2, the others spin
+// 0.  Launched apart, each ends on a half-empty chip and pays its own start.
+template <int NC2, int NC0>
+__global__ __launch_bounds__(64 * RWAVES, 2) void k_m2a_pair(LegArgs a2, int ncg2, int n2, LegArgs a0, int ncg0)
+{
+    __shared__ alignas(32) double lds[split_lds<(NC2 > NC0 ? NC2 : NC0), 1, SEG>()];
+    if ((int)blockIdx.x < n2) m2a_reg64<2, NC2, 1, SEG, true>(a2, blockIdx.x, ncg2, lds);
+    else m2a_reg64<0, NC0, 1, SEG, true>(a0, (int)blockIdx.x - n2, ncg0, lds);
 }
 
 // ============================================================================
@@ -675,10 +698,11 @@ __global__ __launch_bounds__(SPLIT ? 64 * RWAVES : 64, 2) void k_m2a_reg64(LegAr
 // slot k takes the k-th quarter of the l range (whole 8-row segments), row i a ring.
 // Each step needs one row of coefficients and of A per quarter, read PD steps ahead.
 // ============================================================================
+constexpr int A2M_LDS = 2 * 4 * (SEG * 4 + 4);  // doubles: two blocks of coefficients of four quarters
 // EB = 1 (E only), 2 (B only): plain columns as in spin 0 (tiles of 8 map sets), even
 // and odd rows of P and M apart; the other component is neither read nor multiplied.
 template <int SPIN, int EB, int NC, int R, int C>
-__global__ __launch_bounds__(64, 2) void k_a2m_reg(LegArgs a, int per, int nrt)
+__device__ __forceinline__ void a2m_reg(const LegArgs& a, int block, int per, int nrt, double* lds)
 {
     constexpr bool PACK = SPIN == 2 && EB == 0;  // S and D columns in one tile
     using MF = Mf64<NC>;
@@ -688,13 +712,13 @@ __global__ __launch_bounds__(64, 2) void k_a2m_reg(LegArgs a, int per, int nrt)
     constexpr int PD = PACK && C == 4 ? 2 : 4;  // rows of A read ahead
     static_assert(SEG % PD == 0, "the operand buffers cycle within a segment");
     constexpr int CQ = SEG * CS + 4;  // doubles per quarter of a coefficient block (padded)
-    __shared__ alignas(16) double ctab[2][4 * CQ];
+    static_assert(8 * CQ <= A2M_LDS);
     const int lane = threadIdx.x;
     const int i = lane & 15, k = lane >> 4;
     const int L = a.lmax;
 
     int unit, slot;
-    unit_of(a, per, unit, slot);
+    unit_of(a, block, per, unit, slot);
     if (unit >= nm_rows(a)) return;
     const int m = a.mlist ? __builtin_amdgcn_readfirstlane(a.mlist[unit]) : unit;
     const int cg = slot / nrt, rt = slot - cg * nrt;
@@ -762,8 +786,8 @@ __global__ __launch_bounds__(64, 2) void k_a2m_reg(LegArgs a, int per, int nrt)
         unsigned ahead = 0;  // plain blocks: offset of the next row to read
         // coefficients of the 8 rows a block of steps produces, per quarter: one
         // 16-byte load per lane and block, handed round through the wave's own LDS
-        double2* cw = reinterpret_cast<double2*>(ctab[0]) + k * (CQ / 2) + (CS == 4 ? i : (i & 7));
-        const double* cr = ctab[0] + k * CQ;
+        double2* cw = reinterpret_cast<double2*>(lds) + k * (CQ / 2) + (CS == 4 ? i : (i & 7));
+        const double* cr = lds + k * CQ;
         const double2* cg2 = reinterpret_cast<const double2*>(a.coef + row0 * CS);
         auto load_coef = [&](int t) {
             const int row = min(t + 2 + (CS == 4 ? (i >> 1) : (i & 7)), nrow);
@@ -909,6 +933,22 @@ __global__ __launch_bounds__(64, 2) void k_a2m_reg(LegArgs a, int per, int nrt)
             }
 }
 
+template <int SPIN, int EB, int NC, int R, int C>
+__global__ __launch_bounds__(64, 2) void k_a2m_reg(LegArgs a, int per, int nrt)
+{
+    __shared__ alignas(16) double lds[A2M_LDS];
+    a2m_reg<SPIN, EB, NC, R, C>(a, blockIdx.x, per, nrt, lds);
+}
+
+// both spins of a small call in one launch, as k_m2a_pair
+template <int NC, int R>
+__global__ __launch_bounds__(64, 2) void k_a2m_pair(LegArgs a2, int per2, int n2, LegArgs a0, int per0, int nrt)
+{
+    __shared__ alignas(16) double lds[A2M_LDS];
+    if ((int)blockIdx.x < n2) a2m_reg<2, 0, NC, R, 1>(a2, blockIdx.x, per2, nrt, lds);
+    else a2m_reg<0, 0, NC, R, 1>(a0, (int)blockIdx.x - n2, per0, nrt, lds);
+}
+
 // ----------------------------------------------------------------------------
 // Choice of kernel and tile
 // ----------------------------------------------------------------------------
@@ -925,7 +965,7 @@ double l_tiles(const LegArgs& a, int tl)
 }
 
 // alm2map: R x 16 rings and C tiles of NC columns per wave.  Beside its MFMAs a wave
-// spends 0.38 (R = 1) or 0.3 (R = 2) of a tile on recursion and operands; the last waves
+// spends about 0.5 (R = 1) or 0.3 (R = 2) of a tile on recursion and operands; the last waves
 // of a launch run alone for about one more wave (chains of the first m are twice the
 // mean).  One or two 4-column tiles (spin 2: 1 or 2 map sets, spin 0: up to 4) take the
 // 4-column form: us per launch at nside 512, spin 2, 1 set 1228 -> 654, 2 sets 1233 ->
@@ -953,7 +993,7 @@ A2mPick pick_a2m(const LegArgs& a)
     for (int r = 1; r <= 2; ++r)
         for (int c = 1; c <= (a.eb && r == 2 ? 2 : 4); c *= 2) {
             const int ncg = (t + c - 1) / c;
-            const double cost = r * (c + (r == 1 ? 0.38 : 0.3)) * (waves(r, ncg) / 1024.0 + 1.0);
+            const double cost = r * (c + (r == 1 ? 0.38 + 0.05 * c : 0.3)) * (waves(r, ncg) / 1024.0 + 1.0);
             if (cost < least) {
                 least = cost;
                 best = {16, r, c};
@@ -1052,6 +1092,23 @@ hipError_t m2a_tile(const LegArgs& a, const M2aPick& k, int prec, hipStream_t st
     return k.c == 1 ? go_m2a64<SPIN, 16, 1, 8, false>(a, st) : go_m2a64<SPIN, 16, 2, 8, false>(a, st);
 }
 
+template <int NC2, int NC0>
+void go_m2a_pair(const LegArgs& a0, const LegArgs& a2, hipStream_t st)
+{
+    const int ncg2 = tiles_of(a2, NC2 / 2), ncg0 = tiles_of(a0, NC0);
+    const int n2 = (blocks_m2a(a2, 16 * SEG, ncg2) + 7) / 8 * 8, n0 = blocks_m2a(a0, 16 * SEG, ncg0);
+    hipLaunchKernelGGL((k_m2a_pair<NC2, NC0>), dim3(n2 + n0), dim3(64 * RWAVES), 0, st, a2, ncg2, n2, a0, ncg0);
+}
+
+template <int NC, int R>
+void go_a2m_pair(const LegArgs& a0, const LegArgs& a2, hipStream_t st)
+{
+    const int nrt = (a2.rn + 16 * R - 1) / (16 * R);
+    const int per2 = nrt * tiles_of(a2, NC / 2), per0 = nrt * tiles_of(a0, NC);
+    const int n2 = (blocks_for(a2, per2) + 7) / 8 * 8, n0 = blocks_for(a0, per0);
+    hipLaunchKernelGGL((k_a2m_pair<NC, R>), dim3(n2 + n0), dim3(64), 0, st, a2, per2, n2, a0, per0, nrt);
+}
+
 }  // namespace
 
 bool leg_m2a_reg(const LegArgs& a, int prec) { return pick_m2a(a, prec).c != 0; }
@@ -1060,6 +1117,34 @@ hipError_t launch_leg_m2a_reg(const LegArgs& a, int prec, hipStream_t st)
 {
     const M2aPick k = pick_m2a(a, prec);
     return a.spin == 0 ? m2a_tile<0>(a, k, prec, st) : m2a_tile<2>(a, k, prec, st);
+}
+
+// Pairing pays while one spin alone leaves the chip part empty: map2alm where both spins
+// split their rings, alm2map up to 8192 waves (nside 64, 16 IQU sets).
+bool launch_leg_m2a_pair(const LegArgs& a0, const LegArgs& a2, int prec, hipStream_t st)
+{
+    if (prec != 0) return false;
+    const M2aPick k0 = pick_m2a(a0, prec), k2 = pick_m2a(a2, prec);
+    if (!k0.split || !k2.split) return false;
+    if (k2.nc == 4) go_m2a_pair<4, 4>(a0, a2, st);
+    else if (k0.nc == 4) go_m2a_pair<16, 4>(a0, a2, st);
+    else go_m2a_pair<16, 16>(a0, a2, st);
+    return true;
+}
+
+bool launch_leg_a2m_pair(const LegArgs& a0, const LegArgs& a2, int prec, hipStream_t st)
+{
+    if (prec != 0 || a2.eb) return false;
+    const double waves = (double)nm_rows(a2) * ((a2.rn + 15) / 16);
+    if (a2.ncols == 2) {
+        if (waves > 8192.0) return false;
+        if (waves > 4096.0) go_a2m_pair<4, 2>(a0, a2, st);
+        else go_a2m_pair<4, 1>(a0, a2, st);
+        return true;
+    }
+    if (waves * tiles_of(a2, 8) > 8192.0) return false;
+    go_a2m_pair<16, 1>(a0, a2, st);
+    return true;
 }
 
 hipError_t launch_leg_a2m_reg(const LegArgs& a, hipStream_t st)

@@ -150,6 +150,13 @@ struct StageTimer {
         if (hipEventCreate(&a) != hipSuccess || hipEventCreate(&b) != hipSuccess) { a = b = nullptr; return; }
         (void)hipEventRecord(a, p->stream);
     }
+    // nothing was launched: no record
+    void drop()
+    {
+        if (a) (void)hipEventDestroy(a);
+        if (b) (void)hipEventDestroy(b);
+        a = b = nullptr;
+    }
     ~StageTimer()
     {
         if (!a) return;
@@ -830,18 +837,12 @@ int valid_sel(sht_plan p, int sel)
 int run_to_mmajor(sht_plan p, const double* alm, int nm, int sel)
 {
     StageTimer t(p, SHT_STAGE_ALM_LAYOUT);
-    if (sel_t(sel)) {
-        AlmArgs t0 = alm_args(p, p->s0, nm);
-        t0.alm_in = alm;
-        HIPCHK(launch_alm_to_mmajor(t0, 1, p->prec, p->stream));
-    }
-    if (sel_pol(p, sel)) {
-        AlmArgs t2 = alm_args(p, p->s2, nm);
-        t2.alm_in = alm;
-        const int eb = sel_eb(sel);
-        if (eb == 2) t2.comp0 = 2;
-        HIPCHK(launch_alm_to_mmajor(t2, eb ? 1 : 2, p->prec, p->stream));
-    }
+    const bool pol = sel_pol(p, sel);
+    const int eb = sel_eb(sel);
+    AlmArgs t0 = alm_args(p, p->s0, nm), t2 = pol ? alm_args(p, p->s2, nm) : t0;
+    t0.alm_in = t2.alm_in = alm;
+    if (pol && eb == 2) t2.comp0 = 2;
+    HIPCHK(launch_alm_to_mmajor(t0, sel_t(sel) ? 1 : 0, t2, !pol ? 0 : eb ? 1 : 2, p->prec, p->stream));
     return SHT_OK;
 }
 
@@ -857,6 +858,18 @@ void own_list(sht_plan p, LegArgs& a)
 // m-major rows -> ring Fourier coefficients of the selected components
 int run_leg_a2m(sht_plan p, int sel)
 {
+    if (sel_t(sel) && sel_pol(p, sel) && !sel_eb(sel)) {  // small calls: one launch, timed as spin 2
+        StageTimer t(p, SHT_STAGE_A2M_SPIN2);
+        LegArgs a0 = leg_args(p, p->s0), a2 = leg_args(p, p->s2);
+        a0.A = a2.A = ws_Aop(p);
+        own_list(p, a0);
+        own_list(p, a2);
+        if (launch_leg_a2m_pair(a0, a2, p->prec, p->stream)) {
+            HIPCHK(hipGetLastError());
+            return SHT_OK;
+        }
+        t.drop();
+    }
     if (sel_t(sel)) {
         StageTimer t(p, SHT_STAGE_A2M_SPIN0);
         LegArgs a = leg_args(p, p->s0);
@@ -905,11 +918,18 @@ int run_m2a(sht_plan p, double* alm, int nm, int accumulate, int sel = SHT_COMP_
 {
     const double dsig = 4.0 * M_PI / (double)p->npix;
     const bool t = sel_t(sel), pol = sel_pol(p, sel);
-    if (t) {
+    bool both = false;
+    if (t && pol && !sel_eb(sel)) {  // small calls: one launch, timed as spin 2
+        StageTimer tm(p, SHT_STAGE_M2A_SPIN2);
+        both = launch_leg_m2a_pair(leg_args(p, p->s0), leg_args(p, p->s2), p->prec, p->stream);
+        HIPCHK(hipGetLastError());
+        if (!both) tm.drop();
+    }
+    if (t && !both) {
         StageTimer tm(p, SHT_STAGE_M2A_SPIN0);
         HIPCHK(launch_leg_m2a(leg_args(p, p->s0), p->prec, p->stream));
     }
-    if (pol) {
+    if (pol && !both) {
         StageTimer tm(p, SHT_STAGE_M2A_SPIN2);
         LegArgs a = leg_args(p, p->s2);
         a.eb = sel_eb(sel);
@@ -918,25 +938,14 @@ int run_m2a(sht_plan p, double* alm, int nm, int accumulate, int sel = SHT_COMP_
     StageTimer tm(p, SHT_STAGE_ALM_LAYOUT);
     const int64_t csz = (int64_t)(p->lmax + 1) * (p->lmax + 1);
     const int64_t astride = (int64_t)p->ncomp * csz;
-    if (t) {
-        AlmArgs t0 = alm_args(p, p->s0, nm);
-        t0.alm_out = alm;
-        t0.scale = dsig;
-        t0.accumulate = accumulate;
-        HIPCHK(launch_alm_from_mmajor(t0, 1, p->prec, p->stream));
-    } else if (!accumulate) {
-        HIPCHK(launch_zero_strided(alm, nm, astride, csz, p->stream));
-    }
-    if (pol) {
-        // with E or B alone the kernel leaves the other block's rows zero
-        AlmArgs t2 = alm_args(p, p->s2, nm);
-        t2.alm_out = alm;
-        t2.scale = dsig;
-        t2.accumulate = accumulate;
-        HIPCHK(launch_alm_from_mmajor(t2, 2, p->prec, p->stream));
-    } else if (p->spin == 2 && !accumulate) {
-        HIPCHK(launch_zero_strided(alm + csz, nm, astride, 2 * csz, p->stream));
-    }
+    AlmArgs t0 = alm_args(p, p->s0, nm), t2 = pol ? alm_args(p, p->s2, nm) : t0;
+    t0.alm_out = t2.alm_out = alm;
+    t0.scale = t2.scale = dsig;
+    t0.accumulate = t2.accumulate = accumulate;
+    // with E or B alone the kernel leaves the other block's rows zero
+    HIPCHK(launch_alm_from_mmajor(t0, t ? 1 : 0, t2, pol ? 2 : 0, p->prec, p->stream));
+    if (!t && !accumulate) HIPCHK(launch_zero_strided(alm, nm, astride, csz, p->stream));
+    if (!pol && p->spin == 2 && !accumulate) HIPCHK(launch_zero_strided(alm + csz, nm, astride, 2 * csz, p->stream));
     return SHT_OK;
 }
 
@@ -1018,51 +1027,65 @@ int run_level(sht_plan p, double* alm, int nm, int d)
     // kernels of k_leg_reg.hip split within a workgroup and write each row once.
     const int ct = (int)std::max<int64_t>(1, p->ldx_cur / 128);
     auto parts = [](int64_t wgs) { return (int)std::min<int64_t>(8, std::max<int64_t>(1, 1024 / std::max<int64_t>(1, wgs))); };
-    for (int spin : {0, 2}) {
-        if (spin == 2 && p->spin != 2) break;
-        SeedSet& S = spin == 0 ? p->s0 : p->s2;
-        const int* pref = (const int*)(spin == 0 ? V.pref0.p : V.pref2.p) + V.start[d] + d;
-        const int nt = spin == 0 ? V.ntiles0[d] : V.ntiles2[d];
-        const int ncompl = spin == 0 ? 1 : 2;
-        LegArgs a = leg_args(p, S);
-        a.mlist = ml;
-        a.nlist = nl;
-        a.tiles = pref;
-        a.ntiles = nt;
-        AlmArgs b = alm_args(p, S, nm);
-        b.mlist = ml;
-        b.nlist = nl;
-        b.tileoff = pref;
-        b.ntiles = nt;
-        b.alm_out = alm;
-        b.accumulate = 1;
-        {
-            StageTimer t(p, spin == 0 ? SHT_STAGE_M2A_SPIN0 : SHT_STAGE_M2A_SPIN2);
-            a.ksplit = leg_m2a_reg(a, p->prec) ? 1 : parts((int64_t)nt * ct);
-            if (a.ksplit > 1) {
-                b.scale = 0.0;  // clear the rows the split map2alm adds into
-                HIPCHK(launch_level_rows(b, ncompl, p->prec, p->stream));
-            }
-            HIPCHK(launch_leg_m2a(a, p->prec, p->stream));
-        }
-        {
-            StageTimer t(p, SHT_STAGE_ALM_LAYOUT);
-            b.scale = dsig;
-            HIPCHK(launch_level_commit(b, ncompl, p->prec, p->stream));
-        }
-        {
-            StageTimer t(p, spin == 0 ? SHT_STAGE_A2M_SPIN0 : SHT_STAGE_A2M_SPIN2);
-            const int tr = spin == 0 ? 64 : 32;  // rings per alm2map tile
-            a.ksplit = p->prec == SHT_FP64 ? 1 : parts((int64_t)nl * ct * ((p->rn + tr - 1) / tr));
-            if (a.ksplit > 1) {  // clear this spin's rows the split alm2map adds into
-                FftArgs z = f;
-                z.comp0 = spin == 0 ? 0 : 1;
-                HIPCHK(launch_level_zero(z, ml, nl, ncompl, p->stream));
-            }
-            a.A = ws_Aop(p);  // the rows the commit wrote as the synthesis operand
-            HIPCHK(launch_leg_a2m(a, p->prec, p->stream));
-        }
+    const int nspin = p->spin == 2 ? 2 : 1;
+    LegArgs a[2];
+    AlmArgs c[2];
+    for (int i = 0; i < nspin; ++i) {
+        SeedSet& S = i == 0 ? p->s0 : p->s2;
+        const int* pref = (const int*)(i == 0 ? V.pref0.p : V.pref2.p) + V.start[d] + d;
+        const int nt = i == 0 ? V.ntiles0[d] : V.ntiles2[d];
+        a[i] = leg_args(p, S);
+        a[i].mlist = ml;
+        a[i].nlist = nl;
+        a[i].tiles = pref;
+        a[i].ntiles = nt;
+        c[i] = alm_args(p, S, nm);
+        c[i].mlist = ml;
+        c[i].nlist = nl;
+        c[i].tileoff = pref;
+        c[i].ntiles = nt;
+        c[i].alm_out = alm;
+        c[i].accumulate = 1;
+        c[i].scale = dsig;
     }
+    auto pair = [&](int stage, bool (*launch)(const LegArgs&, const LegArgs&, int, hipStream_t)) {
+        if (nspin != 2) return false;
+        StageTimer t(p, stage);
+        if (launch(a[0], a[1], p->prec, p->stream)) return true;
+        t.drop();
+        return false;
+    };
+    const bool m2a_both = pair(SHT_STAGE_M2A_SPIN2, launch_leg_m2a_pair);
+    for (int i = 0; i < nspin && !m2a_both; ++i) {
+        const int nt = a[i].ntiles;
+        StageTimer t(p, i == 0 ? SHT_STAGE_M2A_SPIN0 : SHT_STAGE_M2A_SPIN2);
+        a[i].ksplit = leg_m2a_reg(a[i], p->prec) ? 1 : parts((int64_t)nt * ct);
+        if (a[i].ksplit > 1) {
+            c[i].scale = 0.0;  // clear the rows the split map2alm adds into
+            HIPCHK(launch_level_rows(c[i], i == 0 ? 1 : 2, p->prec, p->stream));
+        }
+        HIPCHK(launch_leg_m2a(a[i], p->prec, p->stream));
+        c[i].scale = dsig;
+    }
+    HIPCHK(hipGetLastError());
+    {
+        StageTimer t(p, SHT_STAGE_ALM_LAYOUT);
+        HIPCHK(launch_level_commit(c[0], 1, c[nspin - 1], nspin == 2 ? 2 : 0, p->prec, p->stream));
+    }
+    for (int i = 0; i < nspin; ++i) a[i].A = ws_Aop(p);  // the rows the commit wrote as the synthesis operand
+    const bool a2m_both = pair(SHT_STAGE_A2M_SPIN2, launch_leg_a2m_pair);
+    for (int i = 0; i < nspin && !a2m_both; ++i) {
+        StageTimer t(p, i == 0 ? SHT_STAGE_A2M_SPIN0 : SHT_STAGE_A2M_SPIN2);
+        const int tr = i == 0 ? 64 : 32;  // rings per alm2map tile
+        a[i].ksplit = p->prec == SHT_FP64 ? 1 : parts((int64_t)nl * ct * ((p->rn + tr - 1) / tr));
+        if (a[i].ksplit > 1) {  // clear this spin's rows the split alm2map adds into
+            FftArgs z = f;
+            z.comp0 = i == 0 ? 0 : 1;
+            HIPCHK(launch_level_zero(z, ml, nl, i == 0 ? 1 : 2, p->stream));
+        }
+        HIPCHK(launch_leg_a2m(a[i], p->prec, p->stream));
+    }
+    HIPCHK(hipGetLastError());
     StageTimer t(p, SHT_STAGE_RESIDUAL);
     HIPCHK(launch_level_fold(f, ml, nl, (const int*)V.cmin.p, p->ncomp, p->stream));
     return SHT_OK;

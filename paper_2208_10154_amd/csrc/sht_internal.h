@@ -129,8 +129,9 @@ struct AlmArgs {
     const int* mlist;       // optional m list (tileoff then over the list entries, ntiles its total)
     int nlist;
 };
-hipError_t launch_alm_to_mmajor(const AlmArgs& a, int ncompl, int prec, hipStream_t st);
-hipError_t launch_alm_from_mmajor(const AlmArgs& a, int ncompl, int prec, hipStream_t st);
+// one launch for the na components of a and the nb components of b (either may be 0)
+hipError_t launch_alm_to_mmajor(const AlmArgs& a, int na, const AlmArgs& b, int nb, int prec, hipStream_t st);
+hipError_t launch_alm_from_mmajor(const AlmArgs& a, int na, const AlmArgs& b, int nb, int prec, hipStream_t st);
 // base[i*stride + j] = 0 for i < rows, j < len
 hipError_t launch_zero_strided(double* base, int rows, int64_t stride, int64_t len, hipStream_t st);
 // immediate iteration: A rows of the listed m (m2a output) -> scale * rows, in
@@ -140,7 +141,7 @@ hipError_t launch_level_rows(const AlmArgs& a, int ncompl, int prec, hipStream_t
 // immediate iteration: alm += scale * rows (as launch_alm_from_mmajor with
 // accumulate) and scale * rows written as the alm2map operand (Aop, m = 0 parts
 // without a compact slot zeroed), in one pass
-hipError_t launch_level_commit(const AlmArgs& a, int ncompl, int prec, hipStream_t st);
+hipError_t launch_level_commit(const AlmArgs& a, int na, const AlmArgs& b, int nb, int prec, hipStream_t st);
 
 
 // Folded m order 0, lmax, 1, lmax-1, ...: work per m falls linearly with m, so any
@@ -188,5 +189,8 @@ hipError_t launch_leg_a2m_bf16(const LegArgs& a, hipStream_t st);
 bool leg_m2a_reg(const LegArgs& a, int prec);
 hipError_t launch_leg_m2a_reg(const LegArgs& a, int prec, hipStream_t st);
 hipError_t launch_leg_a2m_reg(const LegArgs& a, hipStream_t st);
+// both spins of one call (a0: spin 0, a2: spin 2) in one launch; false: not launched
+bool launch_leg_m2a_pair(const LegArgs& a0, const LegArgs& a2, int prec, hipStream_t st);
+bool launch_leg_a2m_pair(const LegArgs& a0, const LegArgs& a2, int prec, hipStream_t st);
 
 }  // namespace sht
