@@ -53,7 +53,7 @@ static_assert(M_TR == RCHUNK, "ring chunks and skip-table entries coincide");
 // the m-major coefficient workspace.  Tile: 64 l x 64*NU columns; rings in
 // chunks of 32; wave w owns NU column tiles of 16 and all 64 rows.
 // ============================================================================
-template <typename T, int NU, bool NW = false>
+template <typename T, int NU, int NW = 0>
 __global__ __launch_bounds__(NT, 2) void k_m2a_spin0(LegArgs a)
 {
     constexpr int RS = HALF + 1;        // [ring][row/2]
@@ -67,10 +67,10 @@ __global__ __launch_bounds__(NT, 2) void k_m2a_spin0(LegArgs a)
     const int L = a.lmax, lb = m;
     const int l0 = lb + lt * TL, lend = min(L, l0 + TL - 1);
     const int lane = threadIdx.x & 63, wave = wave_index();
-    const int col = NW ? (lane & 15) : ct * (64 * NU) + 16 * NU * wave + (lane & 15);
-    // narrow tile (NW: at most 8 map sets, the first 16 columns): the four waves
-    // split the tile's output blocks instead of its columns
-    auto mine = [&](int p, int t) { return !NW || (p == (wave >> 1) && t == (wave & 1)); };
+    const int col = NW ? 16 * (NW == 2 ? wave & 1 : 0) + (lane & 15) : ct * (64 * NU) + 16 * NU * wave + (lane & 15);
+    // narrow tile (NW = 1: at most 8 map sets, the first 16 columns; 2: at most 16, two
+    // waves per 16 columns): the waves split the tile's output blocks as well
+    auto mine = [&](int p, int t) { return NW == 0 || (p == (wave >> 1) && (NW == 2 || t == (wave & 1))); };
     // fill items: 32 rings x SPT segments, one per lane (segment uniform per half-wave)
     static_assert(M_TR * SPT == NT, "one fill item per thread");
     constexpr bool filler = true;
@@ -215,7 +215,7 @@ __global__ __launch_bounds__(NT, 2) void k_m2a_spin0(LegArgs a)
 // rings in chunks of 32; wave w owns NU column tiles of 16.  EB = 1 (E only) or
 // 2 (B only) computes one block row of the transform; the other stays zero.
 // ============================================================================
-template <typename T, int NU, int EB, bool NW = false>
+template <typename T, int NU, int EB, int NW = 0>
 __global__ __launch_bounds__(NT, 2) void k_m2a_spin2(LegArgs a)
 {
     constexpr int RS = HALF + 1;
@@ -230,10 +230,10 @@ __global__ __launch_bounds__(NT, 2) void k_m2a_spin2(LegArgs a)
     const int l0 = lb + lt * TL, lend = min(L, l0 + TL - 1);
     const int po = (lb - m) & 1;
     const int lane = threadIdx.x & 63, wave = wave_index();
-    const int col = NW ? (lane & 15) : ct * (64 * NU) + 16 * NU * wave + (lane & 15);
-    // narrow tile (NW: at most 8 map sets, the first 16 columns): the four waves
-    // split the tile's output blocks instead of its columns
-    auto mine = [&](int p, int t) { return !NW || (p == (wave >> 1) && t == (wave & 1)); };
+    const int col = NW ? 16 * (NW == 2 ? wave & 1 : 0) + (lane & 15) : ct * (64 * NU) + 16 * NU * wave + (lane & 15);
+    // narrow tile (NW = 1: at most 8 map sets, the first 16 columns; 2: at most 16, two
+    // waves per 16 columns): the waves split the tile's output blocks as well
+    auto mine = [&](int p, int t) { return NW == 0 || (p == (wave >> 1) && (NW == 2 || t == (wave & 1))); };
     const int pcol = col ^ 1;                           // Y = iU swaps re/im: partner column
     const unsigned ysg = (col & 1) ? 0u : 0x80000000u;  // Y_re = -U_im, Y_im = U_re
     // fill items: 32 rings x SPT segments, one per lane (segment uniform per half-wave)
@@ -393,7 +393,7 @@ __global__ __launch_bounds__(NT, 2) void k_m2a_spin2(LegArgs a)
 // ============================================================================
 constexpr int A0_TR = 64;
 
-template <typename T, int NU, bool NW = false>
+template <typename T, int NU, int NW = 0>
 __global__ __launch_bounds__(NT, 2) void k_a2m_spin0(LegArgs a)
 {
     constexpr int RS = A0_TR + 1;       // [row/2][ring]
@@ -411,10 +411,10 @@ __global__ __launch_bounds__(NT, 2) void k_a2m_spin0(LegArgs a)
     const int L = a.lmax, lb = m;
     const int r0 = rt * A0_TR;
     const int lane = threadIdx.x & 63, wave = wave_index();
-    const int col = NW ? (lane & 15) : ct * (64 * NU) + 16 * NU * wave + (lane & 15);
-    // narrow tile (NW: at most 8 map sets, the first 16 columns): the four waves
-    // split the tile's output blocks instead of its columns
-    auto mine = [&](int t) { return !NW || t == wave; };
+    const int col = NW ? 16 * (NW == 2 ? wave & 1 : 0) + (lane & 15) : ct * (64 * NU) + 16 * NU * wave + (lane & 15);
+    // narrow tile (NW = 1: at most 8 map sets, the first 16 columns; 2: at most 16, two
+    // waves per 16 columns): the waves split the tile's output blocks as well
+    auto mine = [&](int t) { return NW == 0 || (NW == 1 ? t == wave : (t >> 1) == (wave >> 1)); };
     // fill items: 64 rings x SPT segments, two per lane: ring = lane, segments
     // wave and wave + 4 (wave-uniform)
     static_assert(A0_TR * SPT == 2 * NT && SPT == 8, "two fill items per thread");
@@ -560,7 +560,7 @@ constexpr int A2_TR = 32;
 
 // EB = 1 (E only) or 2 (B only) drops the other block's loads and products:
 // the half-block transforms of pixel-domain E/B separation (Sec. 2.3).
-template <typename T, int NU, int EB, bool NW = false>
+template <typename T, int NU, int EB, int NW = 0>
 __global__ __launch_bounds__(NT, 2) void k_a2m_spin2(LegArgs a)
 {
     constexpr int RS = A2_TR + 1;
@@ -579,12 +579,12 @@ __global__ __launch_bounds__(NT, 2) void k_a2m_spin2(LegArgs a)
     const int po = (lb - m) & 1;
     const int r0 = rt * A2_TR;
     const int lane = threadIdx.x & 63, wave = wave_index();
-    const int col = NW ? (lane & 15) : ct * (64 * NU) + 16 * NU * wave + (lane & 15);
-    // narrow tile (NW: at most 8 map sets, the first 16 columns): the four waves
-    // split the tile's output blocks instead of its columns
+    const int col = NW ? 16 * (NW == 2 ? wave & 1 : 0) + (lane & 15) : ct * (64 * NU) + 16 * NU * wave + (lane & 15);
+    // narrow tile (NW = 1: at most 8 map sets, the first 16 columns; 2: at most 16, two
+    // waves per 16 columns): the waves split the tile's output blocks as well
     // (waves 0 and 1: the Q sums of ring tiles 0 and 1; waves 2 and 3: the iU sums)
-    auto mineq = [&](int t) { return !NW || (t == (wave & 1) && wave < 2); };
-    auto mineu = [&](int t) { return !NW || (t == (wave & 1) && wave >= 2); };
+    auto mineq = [&](int t) { return NW == 0 || (NW == 1 ? t == (wave & 1) && wave < 2 : t == (wave >> 1)); };
+    auto mineu = [&](int t) { return NW == 0 || (NW == 1 ? t == (wave & 1) && wave >= 2 : t == (wave >> 1)); };
     static_assert(A2_TR * SPT == NT, "one fill item per thread");
     constexpr bool filler = true;
     const int frl = lane & 31;
@@ -745,6 +745,9 @@ __global__ __launch_bounds__(NT, 2) void k_a2m_spin2(LegArgs a)
         }
 }
 
+// column tiles of w columns that hold map sets
+int col_tiles(const LegArgs& a, int w) { return (a.ncols + w - 1) / w; }
+
 // widest column tiling (64 NU columns per workgroup, NU <= NUMAX) that divides ldx
 int pick_nu(int numax, int64_t ldx)
 {
@@ -763,11 +766,12 @@ hipError_t launch_m2a_t(const LegArgs& a, hipStream_t st)
     const dim3 blk(NT);
     if (a.spin == 0) {
         const int nu = pick_nu(4, a.ldx);
-        b.ctiles = (int)(a.ldx / (64 * nu));
+        b.ctiles = col_tiles(a, 64 * nu);
         const dim3 grid(b.ntiles * b.ctiles * kparts(a));
         if constexpr (sizeof(T) == 4) {
             if (narrow(a)) {
-                hipLaunchKernelGGL((k_m2a_spin0<T, 1, true>), grid, blk, 0, st, b);
+                if (narrow(a) == 1) hipLaunchKernelGGL((k_m2a_spin0<T, 1, 1>), grid, blk, 0, st, b);
+                else hipLaunchKernelGGL((k_m2a_spin0<T, 1, 2>), grid, blk, 0, st, b);
                 return hipGetLastError();
             }
         }
@@ -776,16 +780,20 @@ hipError_t launch_m2a_t(const LegArgs& a, hipStream_t st)
         else hipLaunchKernelGGL((k_m2a_spin0<T, 1>), grid, blk, 0, st, b);
     } else {
         const int nu = pick_nu(2, a.ldx);
-        b.ctiles = (int)(a.ldx / (64 * nu));
+        b.ctiles = col_tiles(a, 64 * nu);
         const dim3 grid(b.ntiles * b.ctiles * kparts(a));
         if (nu == 2) {
             if (a.eb == 1) hipLaunchKernelGGL((k_m2a_spin2<T, 2, 1>), grid, blk, 0, st, b);
             else if (a.eb == 2) hipLaunchKernelGGL((k_m2a_spin2<T, 2, 2>), grid, blk, 0, st, b);
             else hipLaunchKernelGGL((k_m2a_spin2<T, 2, 0>), grid, blk, 0, st, b);
-        } else if (narrow(a)) {
-            if (a.eb == 1) hipLaunchKernelGGL((k_m2a_spin2<T, 1, 1, true>), grid, blk, 0, st, b);
-            else if (a.eb == 2) hipLaunchKernelGGL((k_m2a_spin2<T, 1, 2, true>), grid, blk, 0, st, b);
-            else hipLaunchKernelGGL((k_m2a_spin2<T, 1, 0, true>), grid, blk, 0, st, b);
+        } else if (narrow(a) == 1) {
+            if (a.eb == 1) hipLaunchKernelGGL((k_m2a_spin2<T, 1, 1, 1>), grid, blk, 0, st, b);
+            else if (a.eb == 2) hipLaunchKernelGGL((k_m2a_spin2<T, 1, 2, 1>), grid, blk, 0, st, b);
+            else hipLaunchKernelGGL((k_m2a_spin2<T, 1, 0, 1>), grid, blk, 0, st, b);
+        } else if (narrow(a) == 2) {
+            if (a.eb == 1) hipLaunchKernelGGL((k_m2a_spin2<T, 1, 1, 2>), grid, blk, 0, st, b);
+            else if (a.eb == 2) hipLaunchKernelGGL((k_m2a_spin2<T, 1, 2, 2>), grid, blk, 0, st, b);
+            else hipLaunchKernelGGL((k_m2a_spin2<T, 1, 0, 2>), grid, blk, 0, st, b);
         } else {
             if (a.eb == 1) hipLaunchKernelGGL((k_m2a_spin2<T, 1, 1>), grid, blk, 0, st, b);
             else if (a.eb == 2) hipLaunchKernelGGL((k_m2a_spin2<T, 1, 2>), grid, blk, 0, st, b);
@@ -801,24 +809,29 @@ hipError_t launch_a2m_f32(const LegArgs& a, hipStream_t st)
     const dim3 blk(NT);
     if (a.spin == 0) {
         const int nu = pick_nu(4, a.ldx);
-        b.ctiles = (int)(a.ldx / (64 * nu));
+        b.ctiles = col_tiles(a, 64 * nu);
         const dim3 grid(nm_rows(a) * b.ctiles * ((a.rn + A0_TR - 1) / A0_TR) * kparts(a));
         if (nu == 4) hipLaunchKernelGGL((k_a2m_spin0<float, 4>), grid, blk, 0, st, b);
-        else if (narrow(a)) hipLaunchKernelGGL((k_a2m_spin0<float, 1, true>), grid, blk, 0, st, b);
+        else if (narrow(a) == 1) hipLaunchKernelGGL((k_a2m_spin0<float, 1, 1>), grid, blk, 0, st, b);
+        else if (narrow(a) == 2) hipLaunchKernelGGL((k_a2m_spin0<float, 1, 2>), grid, blk, 0, st, b);
         else if (nu == 1) hipLaunchKernelGGL((k_a2m_spin0<float, 1>), grid, blk, 0, st, b);
         else hipLaunchKernelGGL((k_a2m_spin0<float, 2>), grid, blk, 0, st, b);
     } else {
         const int nu = pick_nu(2, a.ldx);
-        b.ctiles = (int)(a.ldx / (64 * nu));
+        b.ctiles = col_tiles(a, 64 * nu);
         const dim3 grid(nm_rows(a) * b.ctiles * ((a.rn + A2_TR - 1) / A2_TR) * kparts(a));
         if (nu == 2) {
             if (a.eb == 1) hipLaunchKernelGGL((k_a2m_spin2<float, 2, 1>), grid, blk, 0, st, b);
             else if (a.eb == 2) hipLaunchKernelGGL((k_a2m_spin2<float, 2, 2>), grid, blk, 0, st, b);
             else hipLaunchKernelGGL((k_a2m_spin2<float, 2, 0>), grid, blk, 0, st, b);
-        } else if (narrow(a)) {
-            if (a.eb == 1) hipLaunchKernelGGL((k_a2m_spin2<float, 1, 1, true>), grid, blk, 0, st, b);
-            else if (a.eb == 2) hipLaunchKernelGGL((k_a2m_spin2<float, 1, 2, true>), grid, blk, 0, st, b);
-            else hipLaunchKernelGGL((k_a2m_spin2<float, 1, 0, true>), grid, blk, 0, st, b);
+        } else if (narrow(a) == 1) {
+            if (a.eb == 1) hipLaunchKernelGGL((k_a2m_spin2<float, 1, 1, 1>), grid, blk, 0, st, b);
+            else if (a.eb == 2) hipLaunchKernelGGL((k_a2m_spin2<float, 1, 2, 1>), grid, blk, 0, st, b);
+            else hipLaunchKernelGGL((k_a2m_spin2<float, 1, 0, 1>), grid, blk, 0, st, b);
+        } else if (narrow(a) == 2) {
+            if (a.eb == 1) hipLaunchKernelGGL((k_a2m_spin2<float, 1, 1, 2>), grid, blk, 0, st, b);
+            else if (a.eb == 2) hipLaunchKernelGGL((k_a2m_spin2<float, 1, 2, 2>), grid, blk, 0, st, b);
+            else hipLaunchKernelGGL((k_a2m_spin2<float, 1, 0, 2>), grid, blk, 0, st, b);
         } else {
             if (a.eb == 1) hipLaunchKernelGGL((k_a2m_spin2<float, 1, 1>), grid, blk, 0, st, b);
             else if (a.eb == 2) hipLaunchKernelGGL((k_a2m_spin2<float, 1, 2>), grid, blk, 0, st, b);

@@ -233,7 +233,7 @@ __device__ __forceinline__ const float* fptr(const void* base, int64_t comp, int
 // map2alm, spin 0.  Tile 64 l x 64*NU columns, rings in chunks of 32.
 // LDS: [buffer][hi, lo][parity class][class row][ring (K)].
 // ============================================================================
-template <int NU, bool NW = false>
+template <int NU, int NW = 0>
 __global__ __launch_bounds__(NT, 2) void k_m2a_spin0_bf(LegArgs a)
 {
     constexpr int CLS = HALF * KP, PL = 2 * CLS, BUF = 3 * PL;
@@ -246,10 +246,10 @@ __global__ __launch_bounds__(NT, 2) void k_m2a_spin0_bf(LegArgs a)
     const int L = a.lmax, lb = m;
     const int l0 = lb + lt * TL, lend = min(L, l0 + TL - 1);
     const int lane = threadIdx.x & 63, wave = wave_index();
-    const int col = NW ? (lane & 15) : ct * (64 * NU) + 16 * NU * wave + (lane & 15);
-    // narrow tile (NW: at most 8 map sets, the first 16 columns): the four waves
-    // split the tile's output blocks instead of its columns
-    auto mine = [&](int p, int t) { return !NW || (p == (wave >> 1) && t == (wave & 1)); };
+    const int col = NW ? 16 * (NW == 2 ? wave & 1 : 0) + (lane & 15) : ct * (64 * NU) + 16 * NU * wave + (lane & 15);
+    // narrow tile (NW = 1: at most 8 map sets, the first 16 columns; 2: at most 16, two
+    // waves per 16 columns): the waves split the tile's output blocks as well
+    auto mine = [&](int p, int t) { return NW == 0 || (p == (wave >> 1) && (NW == 2 || t == (wave & 1))); };
     const int k0 = 8 * (lane >> 4);
     // fill items: 32 rings x SPT segments, one per lane (segment uniform per half-wave)
     static_assert(32 * SPT == NT, "one fill item per thread");
@@ -395,7 +395,7 @@ __global__ __launch_bounds__(NT, 2) void k_m2a_spin0_bf(LegArgs a)
 // map2alm, spin 2 (see k_m2a_spin2 in k_leg.hip for the block form and EB).
 // LDS: [buffer][hi, lo][F+, F-][parity class][class row][ring (K)].
 // ============================================================================
-template <int NU, int EB, bool NW = false>
+template <int NU, int EB, int NW = 0>
 __global__ __launch_bounds__(NT, 2) void k_m2a_spin2_bf(LegArgs a)
 {
     constexpr int CLS = HALF * KP, FOFF = 2 * CLS, PL = 2 * FOFF, BUF = 3 * PL;
@@ -409,10 +409,10 @@ __global__ __launch_bounds__(NT, 2) void k_m2a_spin2_bf(LegArgs a)
     const int l0 = lb + lt * TL, lend = min(L, l0 + TL - 1);
     const int po = (lb - m) & 1;
     const int lane = threadIdx.x & 63, wave = wave_index();
-    const int col = NW ? (lane & 15) : ct * (64 * NU) + 16 * NU * wave + (lane & 15);
-    // narrow tile (NW: at most 8 map sets, the first 16 columns): the four waves
-    // split the tile's output blocks instead of its columns
-    auto mine = [&](int p, int t) { return !NW || (p == (wave >> 1) && t == (wave & 1)); };
+    const int col = NW ? 16 * (NW == 2 ? wave & 1 : 0) + (lane & 15) : ct * (64 * NU) + 16 * NU * wave + (lane & 15);
+    // narrow tile (NW = 1: at most 8 map sets, the first 16 columns; 2: at most 16, two
+    // waves per 16 columns): the waves split the tile's output blocks as well
+    auto mine = [&](int p, int t) { return NW == 0 || (p == (wave >> 1) && (NW == 2 || t == (wave & 1))); };
     const int pcol = col ^ 1;
     const unsigned ysg = (col & 1) ? 0u : 0x80000000u;
     const int k0 = 8 * (lane >> 4);
@@ -587,7 +587,7 @@ __global__ __launch_bounds__(NT, 2) void k_m2a_spin2_bf(LegArgs a)
 // ============================================================================
 constexpr int A0_TR = 64;
 
-template <int NU, bool NW = false>
+template <int NU, int NW = 0>
 __global__ __launch_bounds__(NT, 2) void k_a2m_spin0_bf(LegArgs a)
 {
     constexpr int CLS = A0_TR * KP, PL = 2 * CLS, BUF = 3 * PL;
@@ -604,10 +604,10 @@ __global__ __launch_bounds__(NT, 2) void k_a2m_spin0_bf(LegArgs a)
     const int L = a.lmax, lb = m;
     const int r0 = rt * A0_TR;
     const int lane = threadIdx.x & 63, wave = wave_index();
-    const int col = NW ? (lane & 15) : ct * (64 * NU) + 16 * NU * wave + (lane & 15);
-    // narrow tile (NW: at most 8 map sets, the first 16 columns): the four waves
-    // split the tile's output blocks instead of its columns
-    auto mine = [&](int t) { return !NW || t == wave; };
+    const int col = NW ? 16 * (NW == 2 ? wave & 1 : 0) + (lane & 15) : ct * (64 * NU) + 16 * NU * wave + (lane & 15);
+    // narrow tile (NW = 1: at most 8 map sets, the first 16 columns; 2: at most 16, two
+    // waves per 16 columns): the waves split the tile's output blocks as well
+    auto mine = [&](int t) { return NW == 0 || (NW == 1 ? t == wave : (t >> 1) == (wave >> 1)); };
     const int k0 = 8 * (lane >> 4);
     // fill items: 64 rings x SPT segments, two per lane: ring = lane, segments
     // wave and wave + 4 (wave-uniform)
@@ -768,7 +768,7 @@ __global__ __launch_bounds__(NT, 2) void k_a2m_spin0_bf(LegArgs a)
 constexpr int A2_TR = 32;
 
 // EB = 1 (E only) or 2 (B only): the half-block transforms, as in k_leg.hip
-template <int NU, int EB, bool NW = false>
+template <int NU, int EB, int NW = 0>
 __global__ __launch_bounds__(NT, 2) void k_a2m_spin2_bf(LegArgs a)
 {
     constexpr int CLS = A2_TR * KP, FOFF = 2 * CLS, PL = 2 * FOFF, BUF = 3 * PL;
@@ -786,12 +786,12 @@ __global__ __launch_bounds__(NT, 2) void k_a2m_spin2_bf(LegArgs a)
     const int po = (lb - m) & 1;
     const int r0 = rt * A2_TR;
     const int lane = threadIdx.x & 63, wave = wave_index();
-    const int col = NW ? (lane & 15) : ct * (64 * NU) + 16 * NU * wave + (lane & 15);
-    // narrow tile (NW: at most 8 map sets, the first 16 columns): the four waves
-    // split the tile's output blocks instead of its columns
+    const int col = NW ? 16 * (NW == 2 ? wave & 1 : 0) + (lane & 15) : ct * (64 * NU) + 16 * NU * wave + (lane & 15);
+    // narrow tile (NW = 1: at most 8 map sets, the first 16 columns; 2: at most 16, two
+    // waves per 16 columns): the waves split the tile's output blocks as well
     // (waves 0 and 1: the Q sums of ring tiles 0 and 1; waves 2 and 3: the iU sums)
-    auto mineq = [&](int t) { return !NW || (t == (wave & 1) && wave < 2); };
-    auto mineu = [&](int t) { return !NW || (t == (wave & 1) && wave >= 2); };
+    auto mineq = [&](int t) { return NW == 0 || (NW == 1 ? t == (wave & 1) && wave < 2 : t == (wave >> 1)); };
+    auto mineu = [&](int t) { return NW == 0 || (NW == 1 ? t == (wave & 1) && wave >= 2 : t == (wave >> 1)); };
     const int k0 = 8 * (lane >> 4);
     // fill items: 32 rings x SPT segments, one per lane (segment uniform per half-wave)
     static_assert(32 * SPT == NT, "one fill item per thread");
@@ -996,24 +996,30 @@ hipError_t launch_leg_m2a_bf16(const LegArgs& a, hipStream_t st)
     if (a.spin == 0) {
         if (narrow(a)) {
             b.ctiles = 1;
-            hipLaunchKernelGGL((k_m2a_spin0_bf<1, true>), dim3(b.ntiles * kparts(a)), blk, 0, st, b);
+            const dim3 grid(b.ntiles * kparts(a));
+            if (narrow(a) == 1) hipLaunchKernelGGL((k_m2a_spin0_bf<1, 1>), grid, blk, 0, st, b);
+            else hipLaunchKernelGGL((k_m2a_spin0_bf<1, 2>), grid, blk, 0, st, b);
         } else if (a.ldx % 128 == 0) {
-            b.ctiles = (int)(a.ldx / 128);
+            b.ctiles = (a.ncols + 127) / 128;
             hipLaunchKernelGGL((k_m2a_spin0_bf<2>), dim3(b.ntiles * b.ctiles * kparts(a)), blk, 0, st, b);
         } else {
-            b.ctiles = (int)(a.ldx / 64);
+            b.ctiles = (a.ncols + 63) / 64;
             hipLaunchKernelGGL((k_m2a_spin0_bf<1>), dim3(b.ntiles * b.ctiles * kparts(a)), blk, 0, st, b);
         }
     } else {
         // one column tile per workgroup: with three pieces per operand, the
         // split operands of two tiles need more than the 256 registers a wave
         // may hold at two waves per SIMD
-        b.ctiles = (int)(a.ldx / 64);
+        b.ctiles = (a.ncols + 63) / 64;
         const dim3 grid(b.ntiles * b.ctiles * kparts(a));
-        if (narrow(a)) {
-            if (a.eb == 1) hipLaunchKernelGGL((k_m2a_spin2_bf<1, 1, true>), grid, blk, 0, st, b);
-            else if (a.eb == 2) hipLaunchKernelGGL((k_m2a_spin2_bf<1, 2, true>), grid, blk, 0, st, b);
-            else hipLaunchKernelGGL((k_m2a_spin2_bf<1, 0, true>), grid, blk, 0, st, b);
+        if (narrow(a) == 1) {
+            if (a.eb == 1) hipLaunchKernelGGL((k_m2a_spin2_bf<1, 1, 1>), grid, blk, 0, st, b);
+            else if (a.eb == 2) hipLaunchKernelGGL((k_m2a_spin2_bf<1, 2, 1>), grid, blk, 0, st, b);
+            else hipLaunchKernelGGL((k_m2a_spin2_bf<1, 0, 1>), grid, blk, 0, st, b);
+        } else if (narrow(a) == 2) {
+            if (a.eb == 1) hipLaunchKernelGGL((k_m2a_spin2_bf<1, 1, 2>), grid, blk, 0, st, b);
+            else if (a.eb == 2) hipLaunchKernelGGL((k_m2a_spin2_bf<1, 2, 2>), grid, blk, 0, st, b);
+            else hipLaunchKernelGGL((k_m2a_spin2_bf<1, 0, 2>), grid, blk, 0, st, b);
         } else if (a.eb == 1) hipLaunchKernelGGL((k_m2a_spin2_bf<1, 1>), grid, blk, 0, st, b);
         else if (a.eb == 2) hipLaunchKernelGGL((k_m2a_spin2_bf<1, 2>), grid, blk, 0, st, b);
         else hipLaunchKernelGGL((k_m2a_spin2_bf<1, 0>), grid, blk, 0, st, b);
@@ -1027,18 +1033,23 @@ hipError_t launch_leg_a2m_bf16(const LegArgs& a, hipStream_t st)
     const dim3 blk(NT);
     if (a.spin == 0) {
         const int nu = a.ldx % 128 == 0 ? 2 : 1;
-        b.ctiles = (int)(a.ldx / (64 * nu));
+        b.ctiles = (a.ncols + 64 * nu - 1) / (64 * nu);
         const dim3 grid(nm_rows(a) * b.ctiles * ((a.rn + A0_TR - 1) / A0_TR) * kparts(a));
-        if (narrow(a)) hipLaunchKernelGGL((k_a2m_spin0_bf<1, true>), grid, blk, 0, st, b);
+        if (narrow(a) == 1) hipLaunchKernelGGL((k_a2m_spin0_bf<1, 1>), grid, blk, 0, st, b);
+        else if (narrow(a) == 2) hipLaunchKernelGGL((k_a2m_spin0_bf<1, 2>), grid, blk, 0, st, b);
         else if (nu == 2) hipLaunchKernelGGL((k_a2m_spin0_bf<2>), grid, blk, 0, st, b);
         else hipLaunchKernelGGL((k_a2m_spin0_bf<1>), grid, blk, 0, st, b);
     } else {
-        b.ctiles = (int)(a.ldx / 64);
+        b.ctiles = (a.ncols + 63) / 64;
         const dim3 grid(nm_rows(a) * b.ctiles * ((a.rn + A2_TR - 1) / A2_TR) * kparts(a));
-        if (narrow(a)) {
-            if (a.eb == 1) hipLaunchKernelGGL((k_a2m_spin2_bf<1, 1, true>), grid, blk, 0, st, b);
-            else if (a.eb == 2) hipLaunchKernelGGL((k_a2m_spin2_bf<1, 2, true>), grid, blk, 0, st, b);
-            else hipLaunchKernelGGL((k_a2m_spin2_bf<1, 0, true>), grid, blk, 0, st, b);
+        if (narrow(a) == 1) {
+            if (a.eb == 1) hipLaunchKernelGGL((k_a2m_spin2_bf<1, 1, 1>), grid, blk, 0, st, b);
+            else if (a.eb == 2) hipLaunchKernelGGL((k_a2m_spin2_bf<1, 2, 1>), grid, blk, 0, st, b);
+            else hipLaunchKernelGGL((k_a2m_spin2_bf<1, 0, 1>), grid, blk, 0, st, b);
+        } else if (narrow(a) == 2) {
+            if (a.eb == 1) hipLaunchKernelGGL((k_a2m_spin2_bf<1, 1, 2>), grid, blk, 0, st, b);
+            else if (a.eb == 2) hipLaunchKernelGGL((k_a2m_spin2_bf<1, 2, 2>), grid, blk, 0, st, b);
+            else hipLaunchKernelGGL((k_a2m_spin2_bf<1, 0, 2>), grid, blk, 0, st, b);
         } else if (a.eb == 1) hipLaunchKernelGGL((k_a2m_spin2_bf<1, 1>), grid, blk, 0, st, b);
         else if (a.eb == 2) hipLaunchKernelGGL((k_a2m_spin2_bf<1, 2>), grid, blk, 0, st, b);
         else hipLaunchKernelGGL((k_a2m_spin2_bf<1, 0>), grid, blk, 0, st, b);

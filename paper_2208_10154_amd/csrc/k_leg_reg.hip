@@ -1026,7 +1026,10 @@ M2aPick pick_m2a(const LegArgs& a, int prec)
     // set-up costs about eight of its groups of 8 rings
     const double rec = f64 ? 0.35 : (a.spin == 2 ? 1.35 : 1.5), setup = 1.0 + 64.0 / a.rn;
     const double lds = f64 ? 1.53 : (a.spin == 2 ? 1.58 : 1.7);  // per tile of the LDS kernels
-    double least = lds * (a.ldx / (a.spin == 2 ? 8 : 16)) * l_tiles(a, 64) * 0.5;
+    // columns the LDS kernels compute; their narrow forms take 0.45 (16 columns) and 0.7
+    // (32) of a full tile's time
+    const double wide = narrow(a) == 1 ? 29.0 : narrow(a) == 2 ? 45.0 : a.ldx == 64 ? 64.0 : (a.ncols + 127) / 128 * 128.0;
+    double least = lds * (wide / (a.spin == 2 ? 8 : 16)) * l_tiles(a, 64) * 0.5;
     M2aPick best{16, 0, 8, false};
     for (int c = 1; c <= (f64 ? 2 : 4); c *= 2) {
         const double cost = (t + c - 1) / c * (c + rec) * lt * setup;

@@ -102,11 +102,14 @@ struct LegArgs {
     int ncols;              // columns holding map sets in this chunk (2 per map set); the rest pad
 };
 
-// Narrow tiles: a chunk of at most 8 map sets (16 columns, inside one 64-column
-// tile) runs Legendre kernels whose four waves split the tile's output blocks
-// instead of its columns, so a small batch is not charged for the 24 padding map
-// sets of the tile.
-__host__ __device__ inline bool narrow(const LegArgs& a) { return a.ldx == 64 && a.ncols > 0 && a.ncols <= 16; }
+// Narrow tiles of the LDS kernels: a chunk of at most 8 (1) or 16 (2) map sets, the
+// first 16 or 32 columns of a 64-column tile.  The four waves then split the tile's
+// output blocks instead of, or besides, its columns, so a small batch is not charged for
+// the padding map sets of the tile.
+__host__ __device__ inline int narrow(const LegArgs& a)
+{
+    return a.ldx != 64 || a.ncols <= 0 ? 0 : a.ncols <= 16 ? 1 : a.ncols <= 32 ? 2 : 0;
+}
 
 // Layout change compact alm <-> m-major rows (one spin's components per launch).
 struct AlmArgs {

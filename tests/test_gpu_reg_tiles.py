@@ -55,10 +55,11 @@ def test_tile_edges_against_the_oracle(sht, spin, nside, lmax, nmaps):
 
 @pytest.mark.parametrize("spin,nside,lmax,nmaps,part,precision", [
     (0, 64, 191, 192, 8, "fp64"), (2, 256, 700, 3, 1, "fp64"), (0, 200, 599, 9, 2, "fp64"), (2, 48, 143, 70, 5, "fp64"), (2, 128, 383, 21, 7, "fp32"),
-    (0, 128, 383, 96, 8, "fp32")])
+    (0, 128, 383, 96, 8, "fp32"), (2, 24, 71, 13, 6, "fp32"), (2, 24, 71, 70, 16, "bf16x3"), (2, 40, 100, 17, 9, "bf16x3"),
+    (0, 24, 71, 67, 16, "bf16x3")])
 def test_wide_and_small_batches_agree(sht, spin, nside, lmax, nmaps, part, precision):
     """A map's result does not depend on the kernel its batch's width picks: 1e-12, far
-    above FP64 rounding; FP32 rows are summed in one order on either route."""
+    above FP64 rounding; FP32 and BF16x3 rows are summed in one order on any route."""
     import torch
     note(f"routes spin={spin} nside={nside} lmax={lmax} nmaps={nmaps} {precision}")
     g = torch.Generator(device="cuda")
