@@ -46,6 +46,9 @@ constexpr int KS = 8;          // MFMA K-steps per tile (4 rings, or 4 l per cla
 constexpr int RPK = SEG / KS;  // recursion rows emitted per K-step
 static_assert(RPK * KS == SEG, "the fill of one segment is spread over the K-steps of a tile");
 constexpr int M_TR = 32;       // map2alm: rings per chunk (= RCHUNK, the skip granularity)
+// values of the recursion tile in LDS (both buffers) per kernel
+constexpr int LDS_M2A0 = 2 * 2 * M_TR * (HALF + 1), LDS_M2A2 = 2 * LDS_M2A0;
+constexpr int LDS_A2M0 = 2 * 2 * HALF * (64 + 1), LDS_A2M2 = 2 * 4 * HALF * (32 + 1);
 static_assert(M_TR == RCHUNK, "ring chunks and skip-table entries coincide");
 
 // ============================================================================
@@ -53,15 +56,15 @@ static_assert(M_TR == RCHUNK, "ring chunks and skip-table entries coincide");
 // the m-major coefficient workspace.  Tile: 64 l x 64*NU columns; rings in
 // chunks of 32; wave w owns NU column tiles of 16 and all 64 rows.
 // ============================================================================
-template <typename T, int NU, int NW = 0>
-__global__ __launch_bounds__(NT, 2) void k_m2a_spin0(LegArgs a)
+template <typename T, int NU, int NW>
+__device__ __forceinline__ void m2a_spin0(const LegArgs& a, int block, int nblocks, T* lam, double* ctile)
 {
     constexpr int RS = HALF + 1;        // [ring][row/2]
     constexpr int CLS = M_TR * RS, BUF = 2 * CLS;
-    __shared__ T lam[2 * BUF];          // [buffer][parity class][ring][row/2]
+    static_assert(2 * BUF == LDS_M2A0);  // lam: [buffer][parity class][ring][row/2]
 
     int m, lt, ct;
-    int g = xcd_remap(blockIdx.x, gridDim.x);
+    int g = xcd_remap(block, nblocks);
     const int sk = split_part(a, g);
     decode_tiles(a, g, m, lt, ct);
     const int L = a.lmax, lb = m;
@@ -79,7 +82,6 @@ __global__ __launch_bounds__(NT, 2) void k_m2a_spin0(LegArgs a)
     const int ls = l0 + SEG * fs;
     const int cnt = min(SEG, L - ls + 1);
     const int64_t row0 = a.rowoff[m];
-    __shared__ double ctile[CoefTile<2>::N];
     CoefTile<2>::put(ctile, CoefTile<2>::fetch(a, row0 + (l0 - lb)));
     __syncthreads();
     const double* cp = ctile + SEG * fs * 2;
@@ -207,6 +209,14 @@ __global__ __launch_bounds__(NT, 2) void k_m2a_spin0(LegArgs a)
             }
 }
 
+template <typename T, int NU, int NW = 0>
+__global__ __launch_bounds__(NT, 2) void k_m2a_spin0(LegArgs a)
+{
+    __shared__ T lam[LDS_M2A0];
+    __shared__ double ctile[CoefTile<2>::N];
+    m2a_spin0<T, NU, NW>(a, blockIdx.x, gridDim.x, lam, ctile);
+}
+
 // ============================================================================
 // map2alm, spin 2 (E and iB from Q and iU):
 //   even l-m: A_E = F+ SX + F- DY,  iA_B = F+ SY + F- DX
@@ -215,15 +225,15 @@ __global__ __launch_bounds__(NT, 2) void k_m2a_spin0(LegArgs a)
 // rings in chunks of 32; wave w owns NU column tiles of 16.  EB = 1 (E only) or
 // 2 (B only) computes one block row of the transform; the other stays zero.
 // ============================================================================
-template <typename T, int NU, int EB, int NW = 0>
-__global__ __launch_bounds__(NT, 2) void k_m2a_spin2(LegArgs a)
+template <typename T, int NU, int EB, int NW>
+__device__ __forceinline__ void m2a_spin2(const LegArgs& a, int block, int nblocks, T* fpm, double* ctile)
 {
     constexpr int RS = HALF + 1;
     constexpr int CLS = M_TR * RS, FOFF = 2 * CLS, BUF = 4 * CLS;
-    __shared__ T fpm[2 * BUF];  // [buffer][F+ / F-][parity class][ring][row/2]
+    static_assert(2 * BUF == LDS_M2A2);  // fpm: [buffer][F+ / F-][parity class][ring][row/2]
 
     int m, lt, ct;
-    int g = xcd_remap(blockIdx.x, gridDim.x);
+    int g = xcd_remap(block, nblocks);
     const int sk = split_part(a, g);
     decode_tiles(a, g, m, lt, ct);
     const int L = a.lmax, lb = lbase(2, m);
@@ -244,7 +254,6 @@ __global__ __launch_bounds__(NT, 2) void k_m2a_spin2(LegArgs a)
     const int ls = l0 + SEG * fs;
     const int cnt = min(SEG, L - ls + 1);
     const int64_t row0 = a.rowoff[m];
-    __shared__ double ctile[CoefTile<4>::N];
     CoefTile<4>::put(ctile, CoefTile<4>::fetch(a, row0 + (l0 - lb)));
     __syncthreads();
     const double* cp = ctile + SEG * fs * 4;
@@ -386,6 +395,14 @@ __global__ __launch_bounds__(NT, 2) void k_m2a_spin2(LegArgs a)
             }
 }
 
+template <typename T, int NU, int EB, int NW = 0>
+__global__ __launch_bounds__(NT, 2) void k_m2a_spin2(LegArgs a)
+{
+    __shared__ T fpm[LDS_M2A2];
+    __shared__ double ctile[CoefTile<4>::N];
+    m2a_spin2<T, NU, EB, NW>(a, blockIdx.x, gridDim.x, fpm, ctile);
+}
+
 // ============================================================================
 // alm2map, spin 0: E = sum_{even l-m} lambda A, O = sum_{odd} lambda A,
 // T_N = E + O, T_S = E - O.  Tile: 64 rings x 64*NU columns, l in chunks of 64;
@@ -393,16 +410,15 @@ __global__ __launch_bounds__(NT, 2) void k_m2a_spin2(LegArgs a)
 // ============================================================================
 constexpr int A0_TR = 64;
 
-template <typename T, int NU, int NW = 0>
-__global__ __launch_bounds__(NT, 2) void k_a2m_spin0(LegArgs a)
+template <typename T, int NU, int NW>
+__device__ __forceinline__ void a2m_spin0(const LegArgs& a, int block, int nblocks, T* lam, double (*ctile)[CoefTile<2>::N])
 {
     constexpr int RS = A0_TR + 1;       // [row/2][ring]
     constexpr int CLS = HALF * RS, BUF = 2 * CLS;
-    __shared__ T lam[2 * BUF];          // [buffer][parity class][row/2][ring]
-    __shared__ double ctile[2][CoefTile<2>::N];
+    static_assert(2 * BUF == LDS_A2M0);  // lam: [buffer][parity class][row/2][ring]
 
     const int nrt = (a.rn + A0_TR - 1) / A0_TR;
-    int g = xcd_remap(blockIdx.x, gridDim.x);
+    int g = xcd_remap(block, nblocks);
     const int sk = split_part(a, g);
     const int mi = g / (a.ctiles * nrt);
     const int m = a.mlist ? a.mlist[mi] : mfold(mi, a.lmax);
@@ -549,6 +565,14 @@ __global__ __launch_bounds__(NT, 2) void k_a2m_spin0(LegArgs a)
         }
 }
 
+template <typename T, int NU, int NW = 0>
+__global__ __launch_bounds__(NT, 2) void k_a2m_spin0(LegArgs a)
+{
+    __shared__ T lam[LDS_A2M0];
+    __shared__ double ctile[2][CoefTile<2>::N];
+    a2m_spin0<T, NU, NW>(a, blockIdx.x, gridDim.x, lam, ctile);
+}
+
 // ============================================================================
 // alm2map, spin 2, with B' = i a_B:
 //   U1 = sum_even F+ E + sum_odd F- B',  U2 = sum_odd F+ E + sum_even F- B'
@@ -560,16 +584,15 @@ constexpr int A2_TR = 32;
 
 // EB = 1 (E only) or 2 (B only) drops the other block's loads and products:
 // the half-block transforms of pixel-domain E/B separation (Sec. 2.3).
-template <typename T, int NU, int EB, int NW = 0>
-__global__ __launch_bounds__(NT, 2) void k_a2m_spin2(LegArgs a)
+template <typename T, int NU, int EB, int NW>
+__device__ __forceinline__ void a2m_spin2(const LegArgs& a, int block, int nblocks, T* fpm, double (*ctile)[CoefTile<4>::N])
 {
     constexpr int RS = A2_TR + 1;
     constexpr int CLS = HALF * RS, FOFF = 2 * CLS, BUF = 4 * CLS;
-    __shared__ T fpm[2 * BUF];  // [buffer][F+ / F-][parity class][row/2][ring]
-    __shared__ double ctile[2][CoefTile<4>::N];
+    static_assert(2 * BUF == LDS_A2M2);  // fpm: [buffer][F+ / F-][parity class][row/2][ring]
 
     const int nrt = (a.rn + A2_TR - 1) / A2_TR;
-    int g = xcd_remap(blockIdx.x, gridDim.x);
+    int g = xcd_remap(block, nblocks);
     const int sk = split_part(a, g);
     const int mi = g / (a.ctiles * nrt);
     const int m = a.mlist ? a.mlist[mi] : mfold(mi, a.lmax);
@@ -745,6 +768,38 @@ __global__ __launch_bounds__(NT, 2) void k_a2m_spin2(LegArgs a)
         }
 }
 
+template <typename T, int NU, int EB, int NW = 0>
+__global__ __launch_bounds__(NT, 2) void k_a2m_spin2(LegArgs a)
+{
+    __shared__ T fpm[LDS_A2M2];
+    __shared__ double ctile[2][CoefTile<4>::N];
+    a2m_spin2<T, NU, EB, NW>(a, blockIdx.x, gridDim.x, fpm, ctile);
+}
+
+// Both spins of a small call in one launch (a chunk of at most 32 map sets): blocks
+// below c2 are spin 2, those from n2 on spin 0.  Launched apart, each ends on a
+// half-empty chip and pays its own start: nside 64, 16 IQU sets, FP32 map2alm 49 -> 32
+// us, BF16x3 40 -> 31 us.
+template <int NW>
+__global__ __launch_bounds__(NT, 2) void k_m2a_pair32(LegArgs a2, int c2, int n2, LegArgs a0, int c0)
+{
+    __shared__ float lam[LDS_M2A2];
+    __shared__ double ctile[CoefTile<4>::N];
+    const int b = blockIdx.x;
+    if (b < c2) m2a_spin2<float, 1, 0, NW>(a2, b, c2, lam, ctile);
+    else if (b >= n2) m2a_spin0<float, 1, NW>(a0, b - n2, c0, lam, ctile);
+}
+
+template <int NW>
+__global__ __launch_bounds__(NT, 2) void k_a2m_pair32(LegArgs a2, int c2, int n2, LegArgs a0, int c0)
+{
+    __shared__ float lam[LDS_A2M2 > LDS_A2M0 ? LDS_A2M2 : LDS_A2M0];
+    __shared__ double ctile[2][CoefTile<4>::N];
+    const int b = blockIdx.x;
+    if (b < c2) a2m_spin2<float, 1, 0, NW>(a2, b, c2, lam, ctile);
+    else if (b >= n2) a2m_spin0<float, 1, NW>(a0, b - n2, c0, lam, reinterpret_cast<double (*)[CoefTile<2>::N]>(ctile));
+}
+
 // column tiles of w columns that hold map sets
 int col_tiles(const LegArgs& a, int w) { return (a.ncols + w - 1) / w; }
 
@@ -842,6 +897,37 @@ hipError_t launch_a2m_f32(const LegArgs& a, hipStream_t st)
 }
 
 }  // namespace
+
+// One launch for both spins (a0: spin 0, a2: spin 2, all of E and B) where their blocks
+// fill the chip's 512 slots at most twelve times (nside 128, 30 sets: map2alm 203 -> 183
+// us, alm2map 230 -> 199); false: not launched.
+bool launch_leg_m2a_pair_f32(const LegArgs& a0, const LegArgs& a2, hipStream_t st)
+{
+    const int c2 = a2.ntiles, c0 = a0.ntiles;
+    if (a2.eb || a2.ldx != 64 || a0.ksplit > 1 || a2.ksplit > 1 || c0 + c2 > 6144 || c0 < 1 || c2 < 1) return false;
+    LegArgs b2 = a2, b0 = a0;
+    b2.ctiles = b0.ctiles = 1;
+    const int n2 = (c2 + 7) / 8 * 8;
+    const dim3 grid(n2 + c0), blk(NT);
+    if (narrow(a2) == 1) hipLaunchKernelGGL((k_m2a_pair32<1>), grid, blk, 0, st, b2, c2, n2, b0, c0);
+    else if (narrow(a2) == 2) hipLaunchKernelGGL((k_m2a_pair32<2>), grid, blk, 0, st, b2, c2, n2, b0, c0);
+    else hipLaunchKernelGGL((k_m2a_pair32<0>), grid, blk, 0, st, b2, c2, n2, b0, c0);
+    return true;
+}
+
+bool launch_leg_a2m_pair_f32(const LegArgs& a0, const LegArgs& a2, hipStream_t st)
+{
+    const int c2 = nm_rows(a2) * ((a2.rn + A2_TR - 1) / A2_TR), c0 = nm_rows(a0) * ((a0.rn + A0_TR - 1) / A0_TR);
+    if (a2.eb || a2.ldx != 64 || a0.ksplit > 1 || a2.ksplit > 1 || c0 + c2 > 6144) return false;
+    LegArgs b2 = a2, b0 = a0;
+    b2.ctiles = b0.ctiles = 1;
+    const int n2 = (c2 + 7) / 8 * 8;
+    const dim3 grid(n2 + c0), blk(NT);
+    if (narrow(a2) == 1) hipLaunchKernelGGL((k_a2m_pair32<1>), grid, blk, 0, st, b2, c2, n2, b0, c0);
+    else if (narrow(a2) == 2) hipLaunchKernelGGL((k_a2m_pair32<2>), grid, blk, 0, st, b2, c2, n2, b0, c0);
+    else hipLaunchKernelGGL((k_a2m_pair32<0>), grid, blk, 0, st, b2, c2, n2, b0, c0);
+    return true;
+}
 
 hipError_t launch_leg_m2a(const LegArgs& a, int prec, hipStream_t st)
 {

@@ -50,6 +50,9 @@ constexpr int NPH = 8;         // phases per tile
 constexpr int RPP = SEG / NPH; // recursion rows per phase
 static_assert(RPP * NPH == SEG, "the fill of one segment is spread over the phases of a tile");
 constexpr int M_TR = 32;
+// values of the recursion tile in LDS (both buffers, three planes) per kernel
+constexpr int LDS_M2A0 = 2 * 3 * 2 * HALF * KP, LDS_M2A2 = 2 * LDS_M2A0;
+constexpr int LDS_A2M0 = 2 * 3 * 2 * 64 * KP, LDS_A2M2 = 2 * 3 * 4 * 32 * KP;
 
 // an operand split into three bf16 pieces
 struct S3 {
@@ -233,14 +236,13 @@ __device__ __forceinline__ const float* fptr(const void* base, int64_t comp, int
 // map2alm, spin 0.  Tile 64 l x 64*NU columns, rings in chunks of 32.
 // LDS: [buffer][hi, lo][parity class][class row][ring (K)].
 // ============================================================================
-template <int NU, int NW = 0>
-__global__ __launch_bounds__(NT, 2) void k_m2a_spin0_bf(LegArgs a)
+template <int NU, int NW>
+__device__ __forceinline__ void m2a_spin0_bf(const LegArgs& a, int block, int nblocks, __bf16* lam, double* ctile)
 {
     constexpr int CLS = HALF * KP, PL = 2 * CLS, BUF = 3 * PL;
-    __shared__ __attribute__((aligned(16))) __bf16 lam[2 * BUF];
-
+    static_assert(2 * BUF == LDS_M2A0);
     int m, lt, ct;
-    int g = xcd_remap(blockIdx.x, gridDim.x);
+    int g = xcd_remap(block, nblocks);
     const int sk = split_part(a, g);
     decode_tiles(a, g, m, lt, ct);
     const int L = a.lmax, lb = m;
@@ -259,7 +261,6 @@ __global__ __launch_bounds__(NT, 2) void k_m2a_spin0_bf(LegArgs a)
     const int ls = l0 + SEG * fs;
     const int cnt = min(SEG, L - ls + 1);
     const int64_t row0 = a.rowoff[m];
-    __shared__ double ctile[CoefTile<2>::N];
     CoefTile<2>::put(ctile, CoefTile<2>::fetch(a, row0 + (l0 - lb)));
     __syncthreads();
     const double* cp = ctile + SEG * fs * 2;
@@ -391,18 +392,25 @@ __global__ __launch_bounds__(NT, 2) void k_m2a_spin0_bf(LegArgs a)
             }
 }
 
+template <int NU, int NW = 0>
+__global__ __launch_bounds__(NT, 2) void k_m2a_spin0_bf(LegArgs a)
+{
+    __shared__ __attribute__((aligned(16))) __bf16 lam[LDS_M2A0];
+    __shared__ double ctile[CoefTile<2>::N];
+    m2a_spin0_bf<NU, NW>(a, blockIdx.x, gridDim.x, lam, ctile);
+}
+
 // ============================================================================
 // map2alm, spin 2 (see k_m2a_spin2 in k_leg.hip for the block form and EB).
 // LDS: [buffer][hi, lo][F+, F-][parity class][class row][ring (K)].
 // ============================================================================
-template <int NU, int EB, int NW = 0>
-__global__ __launch_bounds__(NT, 2) void k_m2a_spin2_bf(LegArgs a)
+template <int NU, int EB, int NW>
+__device__ __forceinline__ void m2a_spin2_bf(const LegArgs& a, int block, int nblocks, __bf16* fpm, double* ctile)
 {
     constexpr int CLS = HALF * KP, FOFF = 2 * CLS, PL = 2 * FOFF, BUF = 3 * PL;
-    __shared__ __attribute__((aligned(16))) __bf16 fpm[2 * BUF];
-
+    static_assert(2 * BUF == LDS_M2A2);
     int m, lt, ct;
-    int g = xcd_remap(blockIdx.x, gridDim.x);
+    int g = xcd_remap(block, nblocks);
     const int sk = split_part(a, g);
     decode_tiles(a, g, m, lt, ct);
     const int L = a.lmax, lb = lbase(2, m);
@@ -424,7 +432,6 @@ __global__ __launch_bounds__(NT, 2) void k_m2a_spin2_bf(LegArgs a)
     const int ls = l0 + SEG * fs;
     const int cnt = min(SEG, L - ls + 1);
     const int64_t row0 = a.rowoff[m];
-    __shared__ double ctile[CoefTile<4>::N];
     CoefTile<4>::put(ctile, CoefTile<4>::fetch(a, row0 + (l0 - lb)));
     __syncthreads();
     const double* cp = ctile + SEG * fs * 4;
@@ -581,21 +588,28 @@ __global__ __launch_bounds__(NT, 2) void k_m2a_spin2_bf(LegArgs a)
             }
 }
 
+template <int NU, int EB, int NW = 0>
+__global__ __launch_bounds__(NT, 2) void k_m2a_spin2_bf(LegArgs a)
+{
+    __shared__ __attribute__((aligned(16))) __bf16 fpm[LDS_M2A2];
+    __shared__ double ctile[CoefTile<4>::N];
+    m2a_spin2_bf<NU, EB, NW>(a, blockIdx.x, gridDim.x, fpm, ctile);
+}
+
 // ============================================================================
 // alm2map, spin 0.  Tile 64 rings x 64*NU columns, l in chunks of 64.
 // LDS: [buffer][hi, lo][parity class][ring][class row (K)].
 // ============================================================================
 constexpr int A0_TR = 64;
 
-template <int NU, int NW = 0>
-__global__ __launch_bounds__(NT, 2) void k_a2m_spin0_bf(LegArgs a)
+template <int NU, int NW>
+__device__ __forceinline__ void a2m_spin0_bf(const LegArgs& a, int block, int nblocks, __bf16* lam, double (*ctile)[CoefTile<2>::N])
 {
     constexpr int CLS = A0_TR * KP, PL = 2 * CLS, BUF = 3 * PL;
-    __shared__ __attribute__((aligned(16))) __bf16 lam[2 * BUF];
-    __shared__ double ctile[2][CoefTile<2>::N];
+    static_assert(2 * BUF == LDS_A2M0);
 
     const int nrt = (a.rn + A0_TR - 1) / A0_TR;
-    int g = xcd_remap(blockIdx.x, gridDim.x);
+    int g = xcd_remap(block, nblocks);
     const int sk = split_part(a, g);
     const int mi = g / (a.ctiles * nrt);
     const int m = a.mlist ? a.mlist[mi] : mfold(mi, a.lmax);
@@ -761,6 +775,14 @@ __global__ __launch_bounds__(NT, 2) void k_a2m_spin0_bf(LegArgs a)
         }
 }
 
+template <int NU, int NW = 0>
+__global__ __launch_bounds__(NT, 2) void k_a2m_spin0_bf(LegArgs a)
+{
+    __shared__ __attribute__((aligned(16))) __bf16 lam[LDS_A2M0];
+    __shared__ double ctile[2][CoefTile<2>::N];
+    a2m_spin0_bf<NU, NW>(a, blockIdx.x, gridDim.x, lam, ctile);
+}
+
 // ============================================================================
 // alm2map, spin 2 (see k_a2m_spin2 in k_leg.hip for the block form).
 // LDS: [buffer][hi, lo][F+, F-][parity class][ring][class row (K)].
@@ -768,15 +790,14 @@ __global__ __launch_bounds__(NT, 2) void k_a2m_spin0_bf(LegArgs a)
 constexpr int A2_TR = 32;
 
 // EB = 1 (E only) or 2 (B only): the half-block transforms, as in k_leg.hip
-template <int NU, int EB, int NW = 0>
-__global__ __launch_bounds__(NT, 2) void k_a2m_spin2_bf(LegArgs a)
+template <int NU, int EB, int NW>
+__device__ __forceinline__ void a2m_spin2_bf(const LegArgs& a, int block, int nblocks, __bf16* fpm, double (*ctile)[CoefTile<4>::N])
 {
     constexpr int CLS = A2_TR * KP, FOFF = 2 * CLS, PL = 2 * FOFF, BUF = 3 * PL;
-    __shared__ __attribute__((aligned(16))) __bf16 fpm[2 * BUF];
-    __shared__ double ctile[2][CoefTile<4>::N];
+    static_assert(2 * BUF == LDS_A2M2);
 
     const int nrt = (a.rn + A2_TR - 1) / A2_TR;
-    int g = xcd_remap(blockIdx.x, gridDim.x);
+    int g = xcd_remap(block, nblocks);
     const int sk = split_part(a, g);
     const int mi = g / (a.ctiles * nrt);
     const int m = a.mlist ? a.mlist[mi] : mfold(mi, a.lmax);
@@ -987,6 +1008,38 @@ __global__ __launch_bounds__(NT, 2) void k_a2m_spin2_bf(LegArgs a)
         }
 }
 
+template <int NU, int EB, int NW = 0>
+__global__ __launch_bounds__(NT, 2) void k_a2m_spin2_bf(LegArgs a)
+{
+    __shared__ __attribute__((aligned(16))) __bf16 fpm[LDS_A2M2];
+    __shared__ double ctile[2][CoefTile<4>::N];
+    a2m_spin2_bf<NU, EB, NW>(a, blockIdx.x, gridDim.x, fpm, ctile);
+}
+
+// Both spins of a small call in one launch (a chunk of at most 32 map sets): blocks
+// below c2 are spin 2, those from n2 on spin 0.  Launched apart, each ends on a
+// half-empty chip and pays its own start: nside 64, 16 IQU sets, FP32 map2alm 49 -> 32
+// us, BF16x3 40 -> 31 us.
+template <int NW>
+__global__ __launch_bounds__(NT, 2) void k_m2a_pair_bf(LegArgs a2, int c2, int n2, LegArgs a0, int c0)
+{
+    __shared__ __attribute__((aligned(16))) __bf16 lam[LDS_M2A2];
+    __shared__ double ctile[CoefTile<4>::N];
+    const int b = blockIdx.x;
+    if (b < c2) m2a_spin2_bf<1, 0, NW>(a2, b, c2, lam, ctile);
+    else if (b >= n2) m2a_spin0_bf<1, NW>(a0, b - n2, c0, lam, ctile);
+}
+
+template <int NW>
+__global__ __launch_bounds__(NT, 2) void k_a2m_pair_bf(LegArgs a2, int c2, int n2, LegArgs a0, int c0)
+{
+    __shared__ __attribute__((aligned(16))) __bf16 lam[LDS_A2M2 > LDS_A2M0 ? LDS_A2M2 : LDS_A2M0];
+    __shared__ double ctile[2][CoefTile<4>::N];
+    const int b = blockIdx.x;
+    if (b < c2) a2m_spin2_bf<1, 0, NW>(a2, b, c2, lam, ctile);
+    else if (b >= n2) a2m_spin0_bf<1, NW>(a0, b - n2, c0, lam, reinterpret_cast<double (*)[CoefTile<2>::N]>(ctile));
+}
+
 }  // namespace
 
 hipError_t launch_leg_m2a_bf16(const LegArgs& a, hipStream_t st)
@@ -1055,6 +1108,37 @@ hipError_t launch_leg_a2m_bf16(const LegArgs& a, hipStream_t st)
         else hipLaunchKernelGGL((k_a2m_spin2_bf<1, 0>), grid, blk, 0, st, b);
     }
     return hipGetLastError();
+}
+
+// One launch for both spins (a0: spin 0, a2: spin 2, all of E and B) where their blocks
+// fill the chip's 512 slots at most four times (alm2map twelve: nside 128, 30 sets 226 ->
+// 206 us, where map2alm gains nothing); false: not launched.
+bool launch_leg_m2a_pair_bf16(const LegArgs& a0, const LegArgs& a2, hipStream_t st)
+{
+    const int c2 = a2.ntiles, c0 = a0.ntiles;
+    if (a2.eb || a2.ldx != 64 || a0.ksplit > 1 || a2.ksplit > 1 || c0 + c2 > 2048 || c0 < 1 || c2 < 1) return false;
+    LegArgs b2 = a2, b0 = a0;
+    b2.ctiles = b0.ctiles = 1;
+    const int n2 = (c2 + 7) / 8 * 8;
+    const dim3 grid(n2 + c0), blk(NT);
+    if (narrow(a2) == 1) hipLaunchKernelGGL((k_m2a_pair_bf<1>), grid, blk, 0, st, b2, c2, n2, b0, c0);
+    else if (narrow(a2) == 2) hipLaunchKernelGGL((k_m2a_pair_bf<2>), grid, blk, 0, st, b2, c2, n2, b0, c0);
+    else hipLaunchKernelGGL((k_m2a_pair_bf<0>), grid, blk, 0, st, b2, c2, n2, b0, c0);
+    return true;
+}
+
+bool launch_leg_a2m_pair_bf16(const LegArgs& a0, const LegArgs& a2, hipStream_t st)
+{
+    const int c2 = nm_rows(a2) * ((a2.rn + A2_TR - 1) / A2_TR), c0 = nm_rows(a0) * ((a0.rn + A0_TR - 1) / A0_TR);
+    if (a2.eb || a2.ldx != 64 || a0.ksplit > 1 || a2.ksplit > 1 || c0 + c2 > 6144) return false;
+    LegArgs b2 = a2, b0 = a0;
+    b2.ctiles = b0.ctiles = 1;
+    const int n2 = (c2 + 7) / 8 * 8;
+    const dim3 grid(n2 + c0), blk(NT);
+    if (narrow(a2) == 1) hipLaunchKernelGGL((k_a2m_pair_bf<1>), grid, blk, 0, st, b2, c2, n2, b0, c0);
+    else if (narrow(a2) == 2) hipLaunchKernelGGL((k_a2m_pair_bf<2>), grid, blk, 0, st, b2, c2, n2, b0, c0);
+    else hipLaunchKernelGGL((k_a2m_pair_bf<0>), grid, blk, 0, st, b2, c2, n2, b0, c0);
+    return true;
 }
 
 }  // namespace sht

@@ -1126,7 +1126,8 @@ hipError_t launch_leg_m2a_reg(const LegArgs& a, int prec, hipStream_t st)
 // split their rings, alm2map up to 8192 waves (nside 64, 16 IQU sets).
 bool launch_leg_m2a_pair(const LegArgs& a0, const LegArgs& a2, int prec, hipStream_t st)
 {
-    if (prec != 0) return false;
+    if (prec == 2) return launch_leg_m2a_pair_bf16(a0, a2, st);
+    if (prec == 1) return !leg_m2a_reg(a0, prec) && !leg_m2a_reg(a2, prec) && launch_leg_m2a_pair_f32(a0, a2, st);
     const M2aPick k0 = pick_m2a(a0, prec), k2 = pick_m2a(a2, prec);
     if (!k0.split || !k2.split) return false;
     if (k2.nc == 4) go_m2a_pair<4, 4>(a0, a2, st);
@@ -1137,7 +1138,9 @@ bool launch_leg_m2a_pair(const LegArgs& a0, const LegArgs& a2, int prec, hipStre
 
 bool launch_leg_a2m_pair(const LegArgs& a0, const LegArgs& a2, int prec, hipStream_t st)
 {
-    if (prec != 0 || a2.eb) return false;
+    if (prec == 2) return launch_leg_a2m_pair_bf16(a0, a2, st);
+    if (prec == 1) return launch_leg_a2m_pair_f32(a0, a2, st);
+    if (a2.eb) return false;
     const double waves = (double)nm_rows(a2) * ((a2.rn + 15) / 16);
     if (a2.ncols == 2) {
         if (waves > 8192.0) return false;

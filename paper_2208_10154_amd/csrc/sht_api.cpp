@@ -1049,7 +1049,7 @@ int run_level(sht_plan p, double* alm, int nm, int d)
         c[i].scale = dsig;
     }
     auto pair = [&](int stage, bool (*launch)(const LegArgs&, const LegArgs&, int, hipStream_t)) {
-        if (nspin != 2) return false;
+        if (nspin != 2 || p->prec != SHT_FP64) return false;  // the other precisions split reductions below
         StageTimer t(p, stage);
         if (launch(a[0], a[1], p->prec, p->stream)) return true;
         t.drop();

@@ -195,5 +195,9 @@ hipError_t launch_leg_a2m_reg(const LegArgs& a, hipStream_t st);
 // both spins of one call (a0: spin 0, a2: spin 2) in one launch; false: not launched
 bool launch_leg_m2a_pair(const LegArgs& a0, const LegArgs& a2, int prec, hipStream_t st);
 bool launch_leg_a2m_pair(const LegArgs& a0, const LegArgs& a2, int prec, hipStream_t st);
+bool launch_leg_m2a_pair_f32(const LegArgs& a0, const LegArgs& a2, hipStream_t st);
+bool launch_leg_a2m_pair_f32(const LegArgs& a0, const LegArgs& a2, hipStream_t st);
+bool launch_leg_m2a_pair_bf16(const LegArgs& a0, const LegArgs& a2, hipStream_t st);
+bool launch_leg_a2m_pair_bf16(const LegArgs& a0, const LegArgs& a2, hipStream_t st);
 
 }  // namespace sht
