@@ -93,7 +93,7 @@ struct FftWork {
     const int* rings;
     int nrings;
     int groups;        // pair groups with map sets
-    int nseq;
+    int rpw, lgp;      // rings per workgroup, log2 of the sequences (map pairs) per ring
 };
 // power-of-two ring lengths 2^6 .. 2^12: map pairs per workgroup (0: not handled)
 int p2_seqs_per_group(int logn);

@@ -180,7 +180,7 @@ __device__ __forceinline__ void run_passes(double2 (&v)[8], double2 (&w)[8], dou
 }
 
 // Work item of workgroup pos of the cnt workgroups of a class (cnt = components x
-// rings x pair groups): workgroups are dealt to the 8 XCDs round-robin, so pos is
+// ring groups x pair groups): workgroups are dealt to the 8 XCDs round-robin, so pos is
 // remapped to give each XCD one contiguous range (neighbouring pair groups of a
 // ring, which write adjacent columns of the same m-major rows, then share an L2).
 // Only groups holding map sets of the chunk are launched: the ring coefficient
@@ -189,23 +189,54 @@ __device__ __forceinline__ void run_passes(double2 (&v)[8], double2 (&w)[8], dou
 // only with each other).
 struct Item {
     int ring, pair0, comp;
+    // workgroups of several rings: the group's rings (left of them) and log2 of the
+    // sequences per ring
+    const int* rings;
+    int left, lgp;
 };
 __device__ __forceinline__ bool work_item(const FftWork& w, int cnt, int pos, int comp0, Item& it)
 {
     const int q = cnt >> 3, r = cnt & 7, x = pos & 7, y = pos >> 3;
     if (y >= q + (x < r ? 1 : 0)) return false;  // a class starts on a multiple of 8
     const int idx = x * q + min(x, r) + y;
-    const int per = w.nrings * w.groups;
+    const int ngr = (w.nrings + w.rpw - 1) / w.rpw, per = ngr * w.groups;
     const int comp = idx / per, rem = idx - comp * per;
-    const int ri = rem / w.groups;
-    it = Item{w.rings[ri], (rem - ri * w.groups) * w.nseq, comp0 + comp};
+    const int gi = rem / w.groups, ri = gi * w.rpw;
+    it = Item{w.rings[ri], (rem - gi * w.groups) << w.lgp, comp0 + comp, w.rings + ri, w.nrings - ri, w.lgp};
     return true;
 }
-__host__ __device__ inline int work_count(const FftWork& w, int ncompl) { return w.nrings * w.groups * ncompl; }
-inline FftWork work_of(const FftArgs& a, const FftClass& c)
+__host__ __device__ inline int work_count(const FftWork& w, int ncompl)
+{
+    return (w.nrings + w.rpw - 1) / w.rpw * w.groups * ncompl;
+}
+// minlg: least log2 of the sequences per ring of the compile-time kinds (ONE_RING:
+// every workgroup serves one ring)
+constexpr int ONE_RING = 31;
+inline FftWork work_of(const FftArgs& a, const FftClass& c, int minlg = ONE_RING)
 {
     const int used = (a.nmaps + 1) / 2;
-    return FftWork{c.rings, c.nrings, (used + c.nseq - 1) / c.nseq, c.nseq};
+    int lgs = 0, lgp = c.kind < FFT_P2 ? ONE_RING : minlg;
+    while ((1 << lgs) < c.nseq) ++lgs;
+    while (lgp < lgs && (1 << lgp) < used) ++lgp;
+    lgp = std::min(lgp, lgs);
+    const int per = 1 << lgp;
+    return FftWork{c.rings, c.nrings, (used + per - 1) / per, c.nseq >> lgp, lgp};
+}
+// Sequence seq of a workgroup: its ring and map pair.  dead: past the class's rings
+// (the last ring stands in for the loads, nothing is stored).
+struct Seq {
+    int ring, pair;
+    bool dead;
+};
+template <bool MULTI>
+__device__ __forceinline__ Seq seq_of(const Item& it, int seq)
+{
+    if constexpr (MULTI) {
+        const int slot = seq >> it.lgp;
+        return Seq{it.rings[min(slot, it.left - 1)], it.pair0 + (seq & ((1 << it.lgp) - 1)), slot >= it.left};
+    } else {
+        return Seq{it.ring, it.pair0 + seq, false};
+    }
 }
 
 // m values per thread and batch in the unfolding (loads of a batch issued first)
@@ -305,17 +336,17 @@ __device__ __forceinline__ void blue_core(double2 (&u)[8], double2* sb, int tl, 
 // (natural order, n values at lds + seq * SEQ, all threads past a barrier): the
 // data spectra F of the iterative map2alm (halfcomplex, when kept) and the unfold
 // T_m = e^{-i m phi0} F_{m mod n} into the X rows, lanes over (m, pair, part).
-template <int LOGM, typename XT>
-__device__ __forceinline__ void blue_spectrum_out(const FftArgs& a, const Item it, const double2* lds,
-                                                  const RingDev& rg, const double2* twn)
+template <int LOGM, typename XT, bool MULTI = false>
+__device__ __forceinline__ void blue_spectrum_out(const FftArgs& a, const Item it, const double2* lds)
 {
     using C = P2<LOGM>;
     constexpr int T = C::T, S = C::S;
-    const int n = rg.n;
-    const int seq = (int)threadIdx.x / T, tl = (int)threadIdx.x % T;
-    const double2* sb = lds + seq * C::SEQ;
-    const int k = 2 * (it.pair0 + seq);
     if (a.F) {  // data spectra of both maps (iterative map2alm), halfcomplex
+        const int seq = (int)threadIdx.x / T, tl = (int)threadIdx.x % T;
+        const double2* sb = lds + seq * C::SEQ;
+        const Seq sr = seq_of<MULTI>(it, seq);
+        const RingDev rg = a.rings[sr.ring];
+        const int n = rg.n, k = sr.dead ? a.nmaps : 2 * sr.pair;
         for (int pos = tl; pos < n; pos += T) {
             const int j = (pos == 0) ? 0 : (pos == n - 1 ? n / 2 : (pos + 1) / 2);
             const int jn = j ? n - j : 0;
@@ -335,10 +366,14 @@ __device__ __forceinline__ void blue_spectrum_out(const FftArgs& a, const Item i
     const int sq = ((int)threadIdx.x >> LP) & (S - 1);
     const int mi = (int)threadIdx.x >> (LP + C::LOGS);
     const double2* zs = lds + sq * C::SEQ;
-    XT* X = static_cast<XT*>(a.X) + (int64_t)it.comp * a.xcomp + (int64_t)it.ring * a.ldx + 4 * (it.pair0 + sq) + 2 * part;
+    const Seq sr = seq_of<MULTI>(it, sq);
+    const RingDev rg = a.rings[sr.ring];
+    const double2* twn = a.tw + a.lens[rg.len].tw;  // e^{-i pi t/n}, t < 2n
+    XT* X = static_cast<XT*>(a.X) + (int64_t)it.comp * a.xcomp + (int64_t)sr.ring * a.ldx + 4 * sr.pair + 2 * part;
     const int64_t mrow = (int64_t)a.nring * a.ldx;
+    const int n = rg.n;
     MStep ws(mi, MSTEP, n, rg.s);
-    const int mtop = min(a.lmax, rg.mcut);
+    const int mtop = sr.dead ? -1 : min(a.lmax, rg.mcut);
     for (int m0 = mi; m0 <= mtop; m0 += MB * MSTEP) {
         double2 ph[MB];
         int jj[MB];
@@ -371,13 +406,11 @@ __device__ __forceinline__ void blue_spectrum_out(const FftArgs& a, const Item i
 // m mod n and its mirror, several terms per bin, so added atomically; lanes over
 // (m, pair, part), the map-b lane handing its term to the map-a lane.  Ends with
 // a barrier.
-template <int LOGM, typename XT>
-__device__ __forceinline__ void blue_fold(const FftArgs& a, const Item it, double2* lds, const RingDev& rg,
-                                          const double2* twn, int nclear)
+template <int LOGM, typename XT, bool MULTI = false>
+__device__ __forceinline__ void blue_fold(const FftArgs& a, const Item it, double2* lds, int nclear)
 {
     using C = P2<LOGM>;
     constexpr int S = C::S;
-    const int n = rg.n, lmax = min(a.lmax, rg.mcut);  // rows past the ring's cutoff are zero
     for (int e = (int)threadIdx.x; e < nclear; e += C::NTH) lds[e] = make_double2(0.0, 0.0);
     __syncthreads();
     const int part = (int)threadIdx.x & 1;
@@ -385,8 +418,12 @@ __device__ __forceinline__ void blue_fold(const FftArgs& a, const Item it, doubl
     const int mi = (int)threadIdx.x >> (1 + C::LOGS);
     constexpr int MSTEP = C::NTH >> (1 + C::LOGS);
     double2* zs = lds + sq * C::SEQ;
-    const XT* X = static_cast<const XT*>(a.X) + (int64_t)it.comp * a.xcomp + (int64_t)it.ring * a.ldx +
-                  4 * (it.pair0 + sq) + 2 * part;
+    const Seq sr = seq_of<MULTI>(it, sq);
+    const RingDev rg = a.rings[sr.ring];
+    const double2* twn = a.tw + a.lens[rg.len].tw;  // e^{-i pi t/n}, t < 2n
+    const int n = rg.n, lmax = min(a.lmax, rg.mcut);  // rows past the ring's cutoff are zero
+    const XT* X = static_cast<const XT*>(a.X) + (int64_t)it.comp * a.xcomp + (int64_t)sr.ring * a.ldx +
+                  4 * sr.pair + 2 * part;
     const int64_t mrow = (int64_t)a.nring * a.ldx;
     MStep ws(mi, MSTEP, n, rg.s);
     for (int m0 = mi; m0 <= lmax; m0 += MB * MSTEP) {
@@ -426,23 +463,24 @@ __device__ __forceinline__ void blue_fold(const FftArgs& a, const Item it, doubl
     __syncthreads();
 }
 
-template <int LOGN, typename XT>
+template <int LOGN, typename XT, bool MULTI>
 __device__ __forceinline__ void fwd_item(const FftArgs& a, const Item it, double2* lds)
 {
     using C = P2<LOGN>;
     constexpr int N = C::N, T = C::T, S = C::S;
-    const RingDev rg = a.rings[it.ring];
-    const double2* tw = a.tw + a.lens[rg.len].tw;  // e^{-i pi t/N}, t < 2N
+    const double2* tw = a.tw + a.lens[a.rings[it.ring].len].tw;  // e^{-i pi t/N}, t < 2N
     const int seq = (int)threadIdx.x / T, tl = (int)threadIdx.x % T;
     double2* sb = lds + seq * C::SEQ;
-    const int k = 2 * (it.pair0 + seq);
+    const Seq sr = seq_of<MULTI>(it, seq);
+    const int64_t first = a.rings[sr.ring].first;
+    const int k = sr.dead ? a.nmaps : 2 * sr.pair;
 
     // pass-0 inputs x[tl + r T] of map pair (k, k+1), straight from global memory
     double2 v[8], w[8];
     {
         const int64_t ms = (int64_t)a.ncomp * a.npix;
-        const double* pa = a.maps_in + (int64_t)it.comp * a.npix + rg.first + min(k, a.nmaps - 1) * ms;
-        const double* pb = a.maps_in + (int64_t)it.comp * a.npix + rg.first + min(k + 1, a.nmaps - 1) * ms;
+        const double* pa = a.maps_in + (int64_t)it.comp * a.npix + first + min(k, a.nmaps - 1) * ms;
+        const double* pb = a.maps_in + (int64_t)it.comp * a.npix + first + min(k + 1, a.nmaps - 1) * ms;
 #pragma unroll
         for (int r = 0; r < 8; ++r) v[r] = make_double2(pa[tl + r * T], pb[tl + r * T]);
 #pragma unroll
@@ -469,9 +507,9 @@ __device__ __forceinline__ void fwd_item(const FftArgs& a, const Item it, double
             const double2 Fa = make_double2(0.5 * (z.x + y.x), 0.5 * (z.y - y.y));
             const double2 Fb = make_double2(0.5 * (z.y + y.y), 0.5 * (y.x - z.x));
             const bool im = (pos != 0) && (pos != N - 1) && ((pos & 1) == 0);
-            if (k < a.nmaps) a.F[((int64_t)k * a.ncomp + it.comp) * a.npix + rg.first + pos] = im ? Fa.y : Fa.x;
+            if (k < a.nmaps) a.F[((int64_t)k * a.ncomp + it.comp) * a.npix + first + pos] = im ? Fa.y : Fa.x;
             if (k + 1 < a.nmaps)
-                a.F[((int64_t)(k + 1) * a.ncomp + it.comp) * a.npix + rg.first + pos] = im ? Fb.y : Fb.x;
+                a.F[((int64_t)(k + 1) * a.ncomp + it.comp) * a.npix + first + pos] = im ? Fb.y : Fb.x;
         }
     }
 
@@ -484,9 +522,11 @@ __device__ __forceinline__ void fwd_item(const FftArgs& a, const Item it, double
     const int sq = ((int)threadIdx.x >> LP) & (S - 1);
     const int mi = (int)threadIdx.x >> (LP + C::LOGS);
     const double2* zs = lds + sq * C::SEQ;
-    XT* X = static_cast<XT*>(a.X) + (int64_t)it.comp * a.xcomp + (int64_t)it.ring * a.ldx + 4 * (it.pair0 + sq) + 2 * part;
+    const Seq so = seq_of<MULTI>(it, sq);
+    const RingDev rg = a.rings[so.ring];
+    XT* X = static_cast<XT*>(a.X) + (int64_t)it.comp * a.xcomp + (int64_t)so.ring * a.ldx + 4 * so.pair + 2 * part;
     const int64_t mrow = (int64_t)a.nring * a.ldx;
-    const int s = rg.s, mtop = min(a.lmax, rg.mcut);
+    const int s = rg.s, mtop = so.dead ? -1 : min(a.lmax, rg.mcut);
     for (int m0 = mi; m0 <= mtop; m0 += MB * MSTEP) {
         double2 ph[MB];
 #pragma unroll
@@ -509,15 +549,13 @@ __device__ __forceinline__ void fwd_item(const FftArgs& a, const Item it, double
     }
 }
 
-template <int LOGN, typename XT>
+template <int LOGN, typename XT, bool MULTI>
 __device__ __forceinline__ void inv_item(const FftArgs& a, const Item it, double2* lds)
 {
     using C = P2<LOGN>;
     constexpr int N = C::N, T = C::T, S = C::S;
     constexpr int MSTEP = C::NTH >> C::LOGS;  // = T
-    const RingDev rg = a.rings[it.ring];
-    const double2* tw = a.tw + a.lens[rg.len].tw;
-    const int s = rg.s, lmax = min(a.lmax, rg.mcut);  // rows past the ring's cutoff are zero
+    const double2* tw = a.tw + a.lens[a.rings[it.ring].len].tw;
 
     // Fold: C_j = sum_{m = j} c_m + sum_{m >= 1, -m = j} conj(c_m) of both maps,
     // Z = C^a + i C^b, into LDS in natural order.  Lanes run over (m, pair) so a
@@ -527,10 +565,12 @@ __device__ __forceinline__ void inv_item(const FftArgs& a, const Item it, double
         const int sq = (int)threadIdx.x & (S - 1);
         const int mi = (int)threadIdx.x >> C::LOGS;
         double2* zs = lds + sq * C::SEQ;
-        const XT* X = static_cast<const XT*>(a.X) + (int64_t)it.comp * a.xcomp + (int64_t)it.ring * a.ldx +
-                      4 * (it.pair0 + sq);
+        const Seq sr = seq_of<MULTI>(it, sq);
+        const RingDev rg = a.rings[sr.ring];
+        const int s = rg.s, lmax = min(a.lmax, rg.mcut);  // rows past the ring's cutoff are zero
+        const XT* X = static_cast<const XT*>(a.X) + (int64_t)it.comp * a.xcomp + (int64_t)sr.ring * a.ldx + 4 * sr.pair;
         const int64_t mrow = (int64_t)a.nring * a.ldx;
-        if (lmax < N) {
+        if ((MULTI ? a.lmax : lmax) < N) {  // the same for every ring of the workgroup
             // every bin has at most one direct and one mirror term: bins j = m
             // take d_m (zero beyond lmax), then bins N - m add e_m
             double2 e[8];
@@ -602,9 +642,10 @@ __device__ __forceinline__ void inv_item(const FftArgs& a, const Item it, double
 
     // natural-order outputs: map k = Re, map k+1 = -Im (conjugate of the DFT)
     using QL = Pass<LOGN, C::NP - 1>;
-    const int k = 2 * (it.pair0 + seq);
+    const Seq so = seq_of<MULTI>(it, seq);
+    const int k = so.dead ? a.nmaps : 2 * so.pair;
     const int64_t ms = (int64_t)a.ncomp * a.npix;
-    double* oa = a.maps_out + (int64_t)it.comp * a.npix + rg.first + (int64_t)k * ms;
+    double* oa = a.maps_out + (int64_t)it.comp * a.npix + a.rings[so.ring].first + (int64_t)k * ms;
     if (k < a.nmaps) {
 #pragma unroll
         for (int b = 0; b < QL::B; ++b) {
@@ -621,21 +662,21 @@ __device__ __forceinline__ void inv_item(const FftArgs& a, const Item it, double
     }
 }
 
-template <int LOGM, typename XT>
+template <int LOGM, typename XT, bool MULTI>
 __device__ __forceinline__ void fwd_item_blue(const FftArgs& a, const Item it, double2* lds)
 {
     using C = P2<LOGM>;
-    constexpr int T = C::T, S = C::S;
-    const RingDev rg = a.rings[it.ring];
+    constexpr int T = C::T;
+    const int seq = (int)threadIdx.x / T, tl = (int)threadIdx.x % T;
+    const Seq sr = seq_of<MULTI>(it, seq);
+    const RingDev rg = a.rings[sr.ring];
     const FftLen* L = a.lens + rg.len;
     const int n = rg.n;
-    const double2* twn = a.tw + L->tw;      // e^{-i pi t/n}, t < 2n
     const double2* twM = a.tw + L->twm;     // e^{-i pi t/M}, t < 2M
     const double2* chirp = a.tw + L->chirp;
     const double2* bhat = a.bhat + L->bhat;
-    const int seq = (int)threadIdx.x / T, tl = (int)threadIdx.x % T;
     double2* sb = lds + seq * C::SEQ;
-    const int k = 2 * (it.pair0 + seq);
+    const int k = sr.dead ? a.nmaps : 2 * sr.pair;
 
     double2 u[8];
     {
@@ -667,26 +708,26 @@ __device__ __forceinline__ void fwd_item_blue(const FftArgs& a, const Item it, d
     }
     __syncthreads();
 
-    blue_spectrum_out<LOGM, XT>(a, it, lds, rg, twn);
+    blue_spectrum_out<LOGM, XT, MULTI>(a, it, lds);
 }
 
-template <int LOGM, typename XT>
+template <int LOGM, typename XT, bool MULTI>
 __device__ __forceinline__ void inv_item_blue(const FftArgs& a, const Item it, double2* lds)
 {
     using C = P2<LOGM>;
     constexpr int T = C::T, S = C::S;
-    const RingDev rg = a.rings[it.ring];
+    blue_fold<LOGM, XT, MULTI>(a, it, lds, S * C::SEQ);
+
+    const int seq = (int)threadIdx.x / T, tl = (int)threadIdx.x % T;
+    const Seq sr = seq_of<MULTI>(it, seq);
+    const RingDev rg = a.rings[sr.ring];
     const FftLen* L = a.lens + rg.len;
     const int n = rg.n;
-    const double2* twn = a.tw + L->tw;
     const double2* twM = a.tw + L->twm;
     const double2* chirp = a.tw + L->chirp;
     const double2* bhat = a.bhat + L->bhat;
 
-    blue_fold<LOGM, XT>(a, it, lds, rg, twn, S * C::SEQ);
-
     // Bluestein on conj(Z): pass-0 values conj(Z_i) w_i
-    const int seq = (int)threadIdx.x / T, tl = (int)threadIdx.x % T;
     double2* sb = lds + seq * C::SEQ;
     double2 u[8];
     {
@@ -703,7 +744,7 @@ __device__ __forceinline__ void inv_item_blue(const FftArgs& a, const Item it, d
     blue_core<LOGM>(u, sb, tl, twM, bhat);
 
     // pixels: y_j = w_j u[k] = DFT(conj Z)_j; map k = Re(conj y), map k+1 = Im(conj y)
-    const int k = 2 * (it.pair0 + seq);
+    const int k = sr.dead ? a.nmaps : 2 * sr.pair;
     const int64_t ms = (int64_t)a.ncomp * a.npix;
     double* oa = a.maps_out + (int64_t)it.comp * a.npix + rg.first + (int64_t)k * ms;
     double2 c[8];

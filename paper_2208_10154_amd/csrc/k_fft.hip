@@ -701,21 +701,21 @@ struct FftTable {
     FftWork work[MAX_CLASSES];
 };
 
-template <bool FWD, int LOGN, bool BLUE, typename XT>
+template <bool FWD, int LOGN, bool BLUE, typename XT, bool MULTI>
 __device__ __forceinline__ void run_p2(const FftArgs& a, const Item& it, double2* lds)
 {
     // whole waves past the kind's threads end here (the barriers count the others)
     if (__builtin_amdgcn_readfirstlane((int)threadIdx.x) >= P2<LOGN>::NTH) return;
     if constexpr (FWD) {
-        if constexpr (BLUE) fwd_item_blue<LOGN, XT>(a, it, lds);
-        else fwd_item<LOGN, XT>(a, it, lds);
+        if constexpr (BLUE) fwd_item_blue<LOGN, XT, MULTI>(a, it, lds);
+        else fwd_item<LOGN, XT, MULTI>(a, it, lds);
     } else {
-        if constexpr (BLUE) inv_item_blue<LOGN, XT>(a, it, lds);
-        else inv_item<LOGN, XT>(a, it, lds);
+        if constexpr (BLUE) inv_item_blue<LOGN, XT, MULTI>(a, it, lds);
+        else inv_item<LOGN, XT, MULTI>(a, it, lds);
     }
 }
 
-template <bool FWD, typename XT>
+template <bool FWD, typename XT, bool MULTI>
 __global__ __launch_bounds__(NT, 4) void k_fft_rings(FftArgs a, FftTable t, int ncompl)
 {
     extern __shared__ double2 lds[];
@@ -729,8 +729,8 @@ __global__ __launch_bounds__(NT, 4) void k_fft_rings(FftArgs a, FftTable t, int 
         case FFT_GEN2: FWD ? gen_fwd<2>(a, it, lds) : gen_inv<2>(a, it, lds); break;
         case FFT_GEN8: FWD ? gen_fwd<8>(a, it, lds) : gen_inv<8>(a, it, lds); break;
 #define SHT_FFT_KIND(LG)                                                    \
-    case FFT_P2 + LG: run_p2<FWD, LG, false, XT>(a, it, lds); break;        \
-    case FFT_BLUE + LG: run_p2<FWD, LG, true, XT>(a, it, lds); break;
+    case FFT_P2 + LG: run_p2<FWD, LG, false, XT, MULTI>(a, it, lds); break;        \
+    case FFT_BLUE + LG: run_p2<FWD, LG, true, XT, MULTI>(a, it, lds); break;
         SHT_FFT_KIND(6)
         SHT_FFT_KIND(7)
         SHT_FFT_KIND(8)
@@ -743,6 +743,19 @@ __global__ __launch_bounds__(NT, 4) void k_fft_rings(FftArgs a, FftTable t, int 
     }
 }
 
+// Least log2 of the map pairs per ring when workgroups take several rings.  The forward
+// transform of one or two map sets keeps a second (padding) pair where the coefficient
+// rows' lines (128 bytes per m and ring) outgrow the 256 MB cache: the 64-byte rows then
+// leave whole sectors, while 32-byte ones are read back before they are written (nside
+// 512, one map set: 234 us against 293 us; nside 256, 240 MB of lines: 92 us with two
+// pairs, 64 us with one).
+constexpr int64_t LINES_MAX = (int64_t)320 << 20;
+int least_lg(bool fwd, const FftArgs& a, int ncompl)
+{
+    const int64_t lines = (int64_t)ncompl * (a.lmax + 1) * a.nring * 128;
+    return fwd && lines > LINES_MAX ? 1 : 0;
+}
+
 hipError_t allow_lds(const void* f, size_t bytes)
 {
     return bytes > 65536 ? hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) : hipSuccess;
@@ -751,6 +764,20 @@ hipError_t allow_lds(const void* f, size_t bytes)
 template <bool FWD, typename XT>
 hipError_t launch_rings(const FftArgs& a, const FftClass* cls, int ncls, int ncompl, hipStream_t st)
 {
+    // A workgroup holds 4096 values, so a small chunk has fewer map pairs than sequences
+    // per workgroup and would transform padding: such workgroups take several rings of
+    // the class instead, where that leaves at least a tenth of the workgroups out (below
+    // that the per-sequence ring data cost more than they save: nside 512, 8 map sets,
+    // 547 us with one ring, 563 us with several).  us forward + inverse, one ring ->
+    // several: nside 64 x 16 31 + 39 -> 29 + 34, 128 x 1 51 + 64 -> 29 + 36, 256 x 1
+    // 104 + 130 -> 67 + 100, 256 x 4 120 + 133 -> 96 + 114, 512 x 1 unchanged + 299 -> 284.
+    const int pack = least_lg(FWD, a, ncompl);
+    int64_t packed = 0, single = 0;
+    for (int i = 0; i < ncls; ++i) {
+        packed += work_count(work_of(a, cls[i], pack), ncompl);
+        single += work_count(work_of(a, cls[i]), ncompl);
+    }
+    const bool multi = 10 * packed <= 9 * single;
     FftTable t;
     int n = 0, blocks = 0, lds = 0;
     for (int i = 0; i < ncls; ++i) {
@@ -760,7 +787,7 @@ hipError_t launch_rings(const FftArgs& a, const FftClass* cls, int ncls, int nco
             if (e != hipSuccess) return e;
             continue;
         }
-        const FftWork w = work_of(a, c);
+        const FftWork w = work_of(a, c, multi ? pack : ONE_RING);
         const int cnt = work_count(w, ncompl);
         if (c.kind == FFT_GEN16) {
             const size_t sh = (size_t)c.lds * sizeof(double2);
@@ -785,9 +812,10 @@ hipError_t launch_rings(const FftArgs& a, const FftClass* cls, int ncls, int nco
         t.work[i] = FftWork{};
     }
     const size_t sh = (size_t)lds * sizeof(double2);
-    const hipError_t e = allow_lds((const void*)k_fft_rings<FWD, XT>, sh);
+    const auto fn = multi ? k_fft_rings<FWD, XT, true> : k_fft_rings<FWD, XT, false>;
+    const hipError_t e = allow_lds((const void*)fn, sh);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_fft_rings<FWD, XT>), dim3(blocks), dim3(NT), sh, st, a, t, ncompl);
+    hipLaunchKernelGGL(fn, dim3(blocks), dim3(NT), sh, st, a, t, ncompl);
     return hipGetLastError();
 }
 

@@ -102,7 +102,7 @@ __device__ __forceinline__ void fwd_item_four(const FftArgs& a, const Item it, d
         }
     }
     __syncthreads();
-    blue_spectrum_out<12, XT>(a, it, lds, rg, twn);
+    blue_spectrum_out<12, XT>(a, it, lds);
 }
 
 template <typename XT>
@@ -121,7 +121,7 @@ __device__ __forceinline__ void inv_item_four(const FftArgs& a, const Item it, d
 
     // conj(Z) in LDS, then the four decimated sequences into registers (the
     // inverse DFT is conj(DFT(conj Z)))
-    blue_fold<12, XT>(a, it, lds, rg, twn, n);
+    blue_fold<12, XT>(a, it, lds, n);
     double2 x[FOUR_Q][4];
 #pragma unroll
     for (int q = 0; q < FOUR_Q; ++q) {

@@ -54,7 +54,7 @@ def test_tile_edges_against_the_oracle(sht, spin, nside, lmax, nmaps):
 
 
 @pytest.mark.parametrize("spin,nside,lmax,nmaps,part,precision", [
-    (0, 64, 191, 192, 8, "fp64"), (2, 256, 700, 3, 1, "fp64"), (0, 200, 599, 9, 2, "fp64"), (2, 48, 143, 70, 5, "fp64"), (2, 128, 383, 21, 7, "fp32"),
+    (0, 64, 255, 33, 3, "fp64"), (2, 64, 150, 40, 5, "fp32"), (0, 64, 191, 192, 8, "fp64"), (2, 256, 700, 3, 1, "fp64"), (0, 200, 599, 9, 2, "fp64"), (2, 48, 143, 70, 5, "fp64"), (2, 128, 383, 21, 7, "fp32"),
     (0, 128, 383, 96, 8, "fp32"), (2, 24, 71, 13, 6, "fp32"), (2, 24, 71, 70, 16, "bf16x3"), (2, 40, 100, 17, 9, "bf16x3"),
     (0, 24, 71, 67, 16, "bf16x3")])
 def test_wide_and_small_batches_agree(sht, spin, nside, lmax, nmaps, part, precision):
