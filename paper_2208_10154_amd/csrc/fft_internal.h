@@ -85,6 +85,7 @@ struct FftClass {
     const int* rings;  // device: rings of the class
     int nrings;
     int nseq;          // map pairs per workgroup
+    int direct;        // 1: on every ring of the class, no m of the ring's cut reaches its length
     int lds;           // complex LDS elements per workgroup (compile-time kinds: their own)
     int lds_rt;        // the same of the runtime-length code on these rings (k_residual)
 };
@@ -94,6 +95,7 @@ struct FftWork {
     int nrings;
     int groups;        // pair groups with map sets
     int rpw, lgp;      // rings per workgroup, log2 of the sequences (map pairs) per ring
+    int direct;        // FftClass::direct
 };
 // power-of-two ring lengths 2^6 .. 2^12: map pairs per workgroup (0: not handled)
 int p2_seqs_per_group(int logn);

@@ -70,6 +70,25 @@ __device__ __forceinline__ void dft8(double2* v)
         v[2 * q + 1] = b[q];
     }
 }
+// the same with v[4..7] = 0 (zero padding of the chirp transform)
+__device__ __forceinline__ void dft8_low(double2* v)
+{
+    constexpr double H = 0.70710678118654752440;
+    double2 a[4], b[4];
+#pragma unroll
+    for (int n = 0; n < 4; ++n) a[n] = v[n];
+    b[0] = v[0];
+    b[1] = make_double2(H * (v[1].x + v[1].y), H * (v[1].y - v[1].x));    // * (1 - i)/sqrt(2)
+    b[2] = make_double2(v[2].y, -v[2].x);                                  // * -i
+    b[3] = make_double2(H * (v[3].y - v[3].x), -H * (v[3].x + v[3].y));   // * (-1 - i)/sqrt(2)
+    dft4(a);
+    dft4(b);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        v[2 * q] = a[q];
+        v[2 * q + 1] = b[q];
+    }
+}
 template <int R>
 __device__ __forceinline__ void dftr(double2* v)
 {
@@ -142,8 +161,8 @@ __device__ __forceinline__ void load_twiddles(double2 (&w)[8], int tl, const dou
 
 // Runs passes PASS..NP-1 on the values in v (inputs of pass PASS, twiddles w
 // already loaded).  On return v holds the last pass's outputs: value b*R + r is
-// element tl + T*b + r*N/R of the transform.
-template <int LOGN, int PASS>
+// element tl + T*b + r*N/R of the transform.  LOW: the inputs v[4..7] are zero.
+template <int LOGN, int PASS, bool LOW = false>
 __device__ __forceinline__ void run_passes(double2 (&v)[8], double2 (&w)[8], double2* sb, int tl, const double2* tw)
 {
     using C = P2<LOGN>;
@@ -156,7 +175,10 @@ __device__ __forceinline__ void run_passes(double2 (&v)[8], double2 (&w)[8], dou
         }
     }
 #pragma unroll
-    for (int b = 0; b < Q::B; ++b) dftr<Q::R>(v + b * Q::R);
+    for (int b = 0; b < Q::B; ++b) {
+        if constexpr (LOW) dft8_low(v);
+        else dftr<Q::R>(v + b * Q::R);
+    }
     if constexpr (!Q::LAST) {
         using Q2 = Pass<LOGN, PASS + 1>;
         load_twiddles<LOGN, PASS + 1>(w, tl, tw);  // in flight across the exchange
@@ -193,6 +215,7 @@ struct Item {
     // sequences per ring
     const int* rings;
     int left, lgp;
+    int direct;  // every ring of the class: cut below its length
 };
 __device__ __forceinline__ bool work_item(const FftWork& w, int cnt, int pos, int comp0, Item& it)
 {
@@ -202,7 +225,7 @@ __device__ __forceinline__ bool work_item(const FftWork& w, int cnt, int pos, in
     const int ngr = (w.nrings + w.rpw - 1) / w.rpw, per = ngr * w.groups;
     const int comp = idx / per, rem = idx - comp * per;
     const int gi = rem / w.groups, ri = gi * w.rpw;
-    it = Item{w.rings[ri], (rem - gi * w.groups) << w.lgp, comp0 + comp, w.rings + ri, w.nrings - ri, w.lgp};
+    it = Item{w.rings[ri], (rem - gi * w.groups) << w.lgp, comp0 + comp, w.rings + ri, w.nrings - ri, w.lgp, w.direct};
     return true;
 }
 __host__ __device__ inline int work_count(const FftWork& w, int ncompl)
@@ -220,7 +243,7 @@ inline FftWork work_of(const FftArgs& a, const FftClass& c, int minlg = ONE_RING
     while (lgp < lgs && (1 << lgp) < used) ++lgp;
     lgp = std::min(lgp, lgs);
     const int per = 1 << lgp;
-    return FftWork{c.rings, c.nrings, (used + per - 1) / per, c.nseq >> lgp, lgp};
+    return FftWork{c.rings, c.nrings, (used + per - 1) / per, c.nseq >> lgp, lgp, c.direct};
 }
 // Sequence seq of a workgroup: its ring and map pair.  dead: past the class's rings
 // (the last ring stands in for the loads, nothing is stored).
@@ -276,17 +299,25 @@ __device__ __forceinline__ void load4(const XT* p, double2& ta, double2& tb)
 // transform: the two transforms are chained in registers.
 // ----------------------------------------------------------------------------
 
-// m = m0, m0 + dm, ...: keeps j = m mod n and ph = (m s) mod 2n
+// m = m0, m0 + dm, ...: keeps j = m mod n and ph = (m s) mod 2n (s is 0 or 1; m0, dm < 2^16)
 struct MStep {
     int j, ph, dj, dph, n, two_n;
+    // m mod n and m mod 2n through the quotient in single precision, off by one at most
+    __device__ __forceinline__ void mod(int m, int& r, int& r2) const
+    {
+        int q = (int)((float)m * __builtin_amdgcn_rcpf((float)n));
+        r = m - q * n;
+        if (r < 0) { r += n; --q; }
+        if (r >= n) { r -= n; ++q; }
+        r2 = r + ((q & 1) ? n : 0);
+    }
     __device__ __forceinline__ MStep(int m0, int dm, int n_, int s)
     {
         n = n_;
         two_n = 2 * n_;
-        j = m0 % n;
-        ph = (int)(((int64_t)m0 * s) % two_n);
-        dj = dm % n;
-        dph = (int)(((int64_t)dm * s) % two_n);
+        mod(m0, j, ph);
+        mod(dm, dj, dph);
+        if (!s) ph = dph = 0;
     }
     __device__ __forceinline__ void next()
     {
@@ -296,6 +327,63 @@ struct MStep {
         if (ph >= two_n) ph -= two_n;
     }
 };
+
+// Fold of one map pair's rows m <= lmax < n onto the bins of a ring: with
+// c_m = e^{+i m phi0} T_m of both maps, d_m = c^a_m + i c^b_m and e_m = conj(c^a_m) +
+// i conj(c^b_m), bin j takes d_j and, for j >= 1, e_{n-j}.  The rows j and n - j give the
+// bins j and n - j, so a thread that holds both writes each bin once, with no clearing,
+// no atomics and no barrier between terms (bin 0 goes with bin n/2).  The phase of row
+// n - j is (-1)^s times the conjugate of that of row j: one table load for both.  FP32
+// rows load both, as the table's rounding of the second decides the last bit of the maps,
+// and these maps are rounded to FP32 again by the next map2alm.
+// Against cleared bins and four FP64 LDS atomics per row and pair, inverse transforms of
+// FP64 IQU, us: nside 128 x 16 93 -> 70, 256 x 16 307 -> 247, 512 x 16 1143 -> 952,
+// 512 x 125 9240 -> 7470.
+// conj(p) t, with the rounding of each part stated: it must not depend on the code around
+__device__ __forceinline__ double2 cmul_conj(double2 p, double2 t)
+{
+    return make_double2(fma(p.x, t.x, p.y * t.y), fma(p.x, t.y, -(p.y * t.x)));
+}
+constexpr int FB = 2;  // bin pairs whose rows are loaded together
+template <typename XT, typename Put>
+__device__ __forceinline__ void fold_direct(const FftArgs& a, const XT* X, int64_t mrow, const double2* twn, int n, int s,
+                                            int lmax, int j0, int dj, const Put& put)
+{
+    const int nh = n >> 1;
+    const double2 zero = make_double2(0.0, 0.0);
+    const double fl = s ? -1.0 : 1.0;
+    for (int jb = j0; jb < nh; jb += FB * dj) {
+        double2 ta[FB], tb[FB], ua[FB], ub[FB], p[FB], pm[FB];
+#pragma unroll
+        for (int u = 0; u < FB; ++u) {
+            const int j = min(jb + u * dj, nh - 1), m = j ? n - j : nh;
+            load4<XT>(X + min(j, lmax) * mrow, ta[u], tb[u]);
+            p[u] = twn[s * j];
+            if constexpr (sizeof(XT) == 4) pm[u] = twn[s * m];
+            ua[u] = ub[u] = zero;
+            if (m <= lmax) load4<XT>(X + m * mrow, ua[u], ub[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < FB; ++u) {
+            const int j = jb + u * dj, m = j ? n - j : nh;
+            if (j >= nh) break;
+            bool l1 = j <= lmax, l2 = m <= lmax;
+            if (a.mown) {
+                l1 = l1 && a.mown[min(j, lmax)];
+                l2 = l2 && a.mown[min(m, lmax)];
+            }
+            const double2 p2 = sizeof(XT) == 4 ? pm[u]
+                               : j             ? make_double2(fl * p[u].x, -fl * p[u].y)
+                                               : make_double2(s ? 0.0 : 1.0, s ? -1.0 : 0.0);
+            const double2 ca = l1 ? cmul_conj(p[u], ta[u]) : zero, cb = l1 ? cmul_conj(p[u], tb[u]) : zero;
+            const double2 ga = l2 ? cmul_conj(p2, ua[u]) : zero, gb = l2 ? cmul_conj(p2, ub[u]) : zero;
+            const double2 e1 = make_double2(ca.x + cb.y, cb.x - ca.y), e2 = make_double2(ga.x + gb.y, gb.x - ga.y);
+            const double2 d1 = make_double2(ca.x - cb.y, ca.y + cb.x), d2 = make_double2(ga.x - gb.y, ga.y + gb.x);
+            put(j, j ? cadd(d1, e2) : d1);
+            put(m, cadd(d2, j ? e1 : e2));
+        }
+    }
+}
 
 // the registers after a transform, reordered to the pass-0 layout
 template <int LOGM>
@@ -309,108 +397,176 @@ __device__ __forceinline__ void to_pass0(const double2 (&v)[8], double2 (&u)[8])
     }
 }
 
-// Convolution step of Bluestein on the pass-0 values u (x_i w_i at i = tl + k T,
-// zero for i >= n): on return y_j = w_j u[k] for j = tl + k T < n.
-template <int LOGM>
-__device__ __forceinline__ void blue_core(double2 (&u)[8], double2* sb, int tl, const double2* twM, const double2* bhat)
+// Convolution step of Bluestein on the pass-0 values u (x_i w_i at i = tl + k T, k < 4,
+// zero for i >= n; n <= M/2 = 4 T): on return y_j = w_j u[k] for j = tl + k T < n, k < 4.
+// CUT: the first transform skips the zero half of its inputs, the second the outputs past
+// 4 T.  The compiler then fuses other products of the butterflies, which moves the last
+// bit of the results: chunks with FP32 rows, whose rounding to FP32 would turn such a bit
+// into 6e-8 of a coefficient now and then, keep the whole transforms.
+template <typename XT>
+constexpr bool CUT = sizeof(XT) == 8;
+template <typename XT>
+constexpr int NU = CUT<XT> ? 4 : 8;
+// scale of the pixels taken into a forward transform: the halves of Z +- conj Z' go in
+// with them for FP64 rows
+template <typename XT>
+constexpr double PIXS = CUT<XT> ? 0.5 : 1.0;
+template <int LOGM, bool CUT>
+__device__ __forceinline__ void blue_core(double2 (&u)[CUT ? 4 : 8], double2* sb, int tl, const double2* twM, const double2* bhat)
 {
     constexpr int T = P2<LOGM>::T;
-    double2 v[8], w[8];
+    double2 v[8], z[8], w[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = u[k];
-    run_passes<LOGM, 0>(v, w, sb, tl, twM);
-    to_pass0<LOGM>(v, u);
+    for (int k = 0; k < (CUT ? 4 : 8); ++k) v[k] = u[k];
+    run_passes<LOGM, 0, CUT>(v, w, sb, tl, twM);
+    to_pass0<LOGM>(v, z);
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-        const double2 z = cmul(u[k], bhat[tl + k * T]);
-        u[k] = make_double2(z.x, -z.y);
+        const double2 y = cmul(z[k], bhat[tl + k * T]);
+        z[k] = make_double2(y.x, -y.y);
     }
     __syncthreads();  // the first transform's last readers of sb are done
-    run_passes<LOGM, 0>(u, w, sb, tl, twM);
-    to_pass0<LOGM>(u, v);
+    run_passes<LOGM, 0>(z, w, sb, tl, twM);
+    to_pass0<LOGM>(z, v);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) u[k] = make_double2(v[k].x, -v[k].y);
+    for (int k = 0; k < (CUT ? 4 : 8); ++k) u[k] = make_double2(v[k].x, -v[k].y);
 }
 
-// Output of one ring's forward transform, the spectrum Z of each map pair in LDS
-// (natural order, n values at lds + seq * SEQ, all threads past a barrier): the
-// data spectra F of the iterative map2alm (halfcomplex, when kept) and the unfold
-// T_m = e^{-i m phi0} F_{m mod n} into the X rows, lanes over (m, pair, part).
-template <int LOGM, typename XT, bool MULTI = false>
-__device__ __forceinline__ void blue_spectrum_out(const FftArgs& a, const Item it, const double2* lds)
-{
+// Output of one ring's forward transform, the spectrum Z of each map pair times PIXS in
+// LDS (natural order, n values at lds + seq * SEQ): the unfold T_m = e^{-i m phi0} F_{m mod n}
+// into the X rows.  Lanes run over (m, pair, part): FP64 rows take two 16-byte parts per
+// pair (map k, map k+1), FP32 rows one, so the lanes of a wave store contiguous row
+// segments of all S pairs.  The FP64 lane of map k forms Z + conj Z', that of map k+1
+// -i (Z - conj Z'), with the -i in its phase.  Constructed before the barrier that
+// completes Z, so that the first phases load across it; a batch's phases load behind the
+// stores of the one before.  Forward transforms of FP64 IQU, us, with the changes to the
+// zero half of the chirp transforms: nside 256 x 16 257 -> 247, 512 x 16 1048 -> 1002,
+// 512 x 125 9000 -> 8140 (25 GB moved; 5.0 ms at the rate of a copy).
+template <int LOGM, typename XT, bool MULTI, bool POW2>
+struct Unfold {
     using C = P2<LOGM>;
-    constexpr int T = C::T, S = C::S;
-    if (a.F) {  // data spectra of both maps (iterative map2alm), halfcomplex
-        const int seq = (int)threadIdx.x / T, tl = (int)threadIdx.x % T;
-        const double2* sb = lds + seq * C::SEQ;
-        const Seq sr = seq_of<MULTI>(it, seq);
-        const RingDev rg = a.rings[sr.ring];
-        const int n = rg.n, k = sr.dead ? a.nmaps : 2 * sr.pair;
-        for (int pos = tl; pos < n; pos += T) {
-            const int j = (pos == 0) ? 0 : (pos == n - 1 ? n / 2 : (pos + 1) / 2);
-            const int jn = j ? n - j : 0;
-            const double2 z = sb[j], y = sb[jn];
-            const double2 Fa = make_double2(0.5 * (z.x + y.x), 0.5 * (z.y - y.y));
-            const double2 Fb = make_double2(0.5 * (z.y + y.y), 0.5 * (y.x - z.x));
-            const bool im = (pos != 0) && (pos != n - 1) && ((pos & 1) == 0);
-            if (k < a.nmaps) a.F[((int64_t)k * a.ncomp + it.comp) * a.npix + rg.first + pos] = im ? Fa.y : Fa.x;
-            if (k + 1 < a.nmaps)
-                a.F[((int64_t)(k + 1) * a.ncomp + it.comp) * a.npix + rg.first + pos] = im ? Fb.y : Fb.x;
-        }
-    }
+    static constexpr int LP = sizeof(XT) == 8 ? 1 : 0;  // log2 parts per pair
+    static constexpr int MSTEP = C::NTH >> (LP + C::LOGS);
+    const double2 *zs, *tw;
+    XT* X;
+    int64_t mrow;
+    int part, m0, mtop, n, s;
+    MStep ws;
+    double2 ph[MB];
+    int jj[MB];
 
-    constexpr int LP = sizeof(XT) == 8 ? 1 : 0;
-    constexpr int MSTEP = C::NTH >> (LP + C::LOGS);
-    const int part = (int)threadIdx.x & ((1 << LP) - 1);
-    const int sq = ((int)threadIdx.x >> LP) & (S - 1);
-    const int mi = (int)threadIdx.x >> (LP + C::LOGS);
-    const double2* zs = lds + sq * C::SEQ;
-    const Seq sr = seq_of<MULTI>(it, sq);
-    const RingDev rg = a.rings[sr.ring];
-    const double2* twn = a.tw + a.lens[rg.len].tw;  // e^{-i pi t/n}, t < 2n
-    XT* X = static_cast<XT*>(a.X) + (int64_t)it.comp * a.xcomp + (int64_t)sr.ring * a.ldx + 4 * sr.pair + 2 * part;
-    const int64_t mrow = (int64_t)a.nring * a.ldx;
-    const int n = rg.n;
-    MStep ws(mi, MSTEP, n, rg.s);
-    const int mtop = sr.dead ? -1 : min(a.lmax, rg.mcut);
-    for (int m0 = mi; m0 <= mtop; m0 += MB * MSTEP) {
-        double2 ph[MB];
-        int jj[MB];
+    __device__ __forceinline__ Unfold(const FftArgs& a, const Item& it, const double2* lds)
+        : Unfold(a, it, lds, ((int)threadIdx.x >> LP) & (C::S - 1))
+    {
+    }
+    __device__ __forceinline__ Unfold(const FftArgs& a, const Item& it, const double2* lds, int sq)
+        : Unfold(a, it, lds, sq, seq_of<MULTI>(it, sq))
+    {
+    }
+    __device__ __forceinline__ Unfold(const FftArgs& a, const Item& it, const double2* lds, int sq, Seq sr)
+        : Unfold(a, it, lds, sq, sr, a.rings[sr.ring])
+    {
+    }
+    __device__ __forceinline__ Unfold(const FftArgs& a, const Item& it, const double2* lds, int sq, Seq sr, const RingDev& rg)
+        : zs(lds + sq * C::SEQ), tw(a.tw + a.lens[rg.len].tw), mrow((int64_t)a.nring * a.ldx),
+          part((int)threadIdx.x & ((1 << LP) - 1)), m0((int)threadIdx.x >> (LP + C::LOGS)),
+          mtop(sr.dead ? -1 : min(a.lmax, rg.mcut)), n(rg.n), s(rg.s), ws(m0, MSTEP, rg.n, rg.s)
+    {
+        X = static_cast<XT*>(a.X) + (int64_t)it.comp * a.xcomp + (int64_t)sr.ring * a.ldx + 4 * sr.pair + 2 * part;
+        fetch();
+    }
+    __device__ __forceinline__ void fetch()
+    {
 #pragma unroll
-        for (int q = 0; q < MB; ++q) {
-            ph[q] = twn[ws.ph];
-            jj[q] = ws.j;
-            ws.next();
-        }
-#pragma unroll
-        for (int q = 0; q < MB; ++q) {
-            const int m = m0 + q * MSTEP;
-            if (m <= mtop) {
-                const int j = jj[q], jn = j ? n - j : 0;
-                const double2 z = zs[j], y = zs[jn];
-                const double2 Fa = make_double2(0.5 * (z.x + y.x), 0.5 * (z.y - y.y));
-                const double2 Fb = make_double2(0.5 * (z.y + y.y), 0.5 * (y.x - z.x));
-                if constexpr (sizeof(XT) == 8) {
-                    *reinterpret_cast<double2*>(X + m * mrow) = cmul(ph[q], part ? Fb : Fa);
-                } else {
-                    store4<XT>(X + m * mrow, cmul(ph[q], Fa), cmul(ph[q], Fb));
-                }
+        for (int u = 0; u < MB; ++u) {
+            if constexpr (POW2) {
+                const int m = m0 + u * MSTEP;
+                ph[u] = tw[(m * s) & (2 * C::N - 1)];
+                jj[u] = m & (C::N - 1);
+            } else {
+                ph[u] = tw[ws.ph];
+                jj[u] = ws.j;
+                ws.next();
             }
         }
     }
+    __device__ __forceinline__ void run()
+    {
+        const double sg = part ? -1.0 : 1.0;
+        while (m0 <= mtop) {
+#pragma unroll
+            for (int u = 0; u < MB; ++u) {
+                const int m = m0 + u * MSTEP;
+                if (m <= mtop) {
+                    const int j = jj[u], jn = POW2 ? (C::N - j) & (C::N - 1) : (j ? n - j : 0);
+                    const double2 z = zs[j], y = zs[jn];
+                    if constexpr (sizeof(XT) == 8) {
+                        const double2 Fp = make_double2(fma(sg, y.x, z.x), fma(-sg, y.y, z.y));
+                        *reinterpret_cast<double2*>(X + m * mrow) = cmul(part ? make_double2(ph[u].y, -ph[u].x) : ph[u], Fp);
+                    } else {
+                        const double2 Fa = make_double2(0.5 * (z.x + y.x), 0.5 * (z.y - y.y));
+                        const double2 Fb = make_double2(0.5 * (z.y + y.y), 0.5 * (y.x - z.x));
+                        store4<XT>(X + m * mrow, cmul(ph[u], Fa), cmul(ph[u], Fb));
+                    }
+                }
+            }
+            m0 += MB * MSTEP;
+            if (m0 <= mtop) fetch();
+        }
+    }
+};
+
+// data spectra of both maps (iterative map2alm), halfcomplex, all threads past the
+// barrier that completes Z
+template <int LOGM, typename XT, bool MULTI>
+__device__ __forceinline__ void keep_spectra(const FftArgs& a, const Item& it, const double2* lds)
+{
+    using C = P2<LOGM>;
+    constexpr int T = C::T;
+    const int seq = (int)threadIdx.x / T, tl = (int)threadIdx.x % T;
+    const double2* sb = lds + seq * C::SEQ;
+    const Seq sr = seq_of<MULTI>(it, seq);
+    const RingDev rg = a.rings[sr.ring];
+    const int n = rg.n, k = sr.dead ? a.nmaps : 2 * sr.pair;
+    for (int pos = tl; pos < n; pos += T) {
+        const int j = (pos == 0) ? 0 : (pos == n - 1 ? n / 2 : (pos + 1) / 2);
+        const int jn = j ? n - j : 0;
+        const double2 z = sb[j], y = sb[jn];
+        constexpr double h = 0.5 / PIXS<XT>;
+        const double2 Fa = make_double2(h * (z.x + y.x), h * (z.y - y.y));
+        const double2 Fb = make_double2(h * (z.y + y.y), h * (y.x - z.x));
+        const bool im = (pos != 0) && (pos != n - 1) && ((pos & 1) == 0);
+        if (k < a.nmaps) a.F[((int64_t)k * a.ncomp + it.comp) * a.npix + rg.first + pos] = im ? Fa.y : Fa.x;
+        if (k + 1 < a.nmaps) a.F[((int64_t)(k + 1) * a.ncomp + it.comp) * a.npix + rg.first + pos] = im ? Fb.y : Fb.x;
+    }
 }
 
-// Fold of one ring's X rows into conj(Z_j), j < n, at lds + seq * SEQ after
-// clearing the first nclear LDS slots: every m up to the ring's cut lands on bin
-// m mod n and its mirror, several terms per bin, so added atomically; lanes over
-// (m, pair, part), the map-b lane handing its term to the map-a lane.  Ends with
-// a barrier.
+// Fold of one ring's X rows into conj(Z_j), j < n, at lds + seq * SEQ.  Rings whose
+// cut lies below n take one direct and one mirror term per bin at most (fold_direct,
+// lanes over (bin, pair)).  On the others (short rings near the poles) every m up to
+// the cut lands on bin m mod n and its mirror, several terms per bin: the first nclear
+// slots are cleared and the terms added atomically, lanes over (m, pair, part), the
+// map-b lane handing its term to the map-a lane.  Ends with a barrier.
 template <int LOGM, typename XT, bool MULTI = false>
-__device__ __forceinline__ void blue_fold(const FftArgs& a, const Item it, double2* lds, int nclear)
+__device__ __forceinline__ void fold(const FftArgs& a, const Item it, double2* lds, int nclear)
 {
     using C = P2<LOGM>;
     constexpr int S = C::S;
+    const int64_t mrow = (int64_t)a.nring * a.ldx;
+    {
+        const int sq = (int)threadIdx.x & (S - 1);
+        const Seq sr = seq_of<MULTI>(it, sq);
+        const RingDev rg = a.rings[sr.ring];
+        const int lmax = min(a.lmax, rg.mcut);  // rows past the ring's cutoff are zero
+        if (MULTI ? it.direct : lmax < rg.n) {
+            double2* zs = lds + sq * C::SEQ;
+            const XT* X = static_cast<const XT*>(a.X) + (int64_t)it.comp * a.xcomp + (int64_t)sr.ring * a.ldx + 4 * sr.pair;
+            fold_direct<XT>(a, X, mrow, a.tw + a.lens[rg.len].tw, rg.n, rg.s, lmax, (int)threadIdx.x >> C::LOGS,
+                            C::NTH >> C::LOGS, [zs](int j, double2 z) { zs[j] = make_double2(z.x, -z.y); });
+            __syncthreads();
+            return;
+        }
+    }
     for (int e = (int)threadIdx.x; e < nclear; e += C::NTH) lds[e] = make_double2(0.0, 0.0);
     __syncthreads();
     const int part = (int)threadIdx.x & 1;
@@ -424,7 +580,6 @@ __device__ __forceinline__ void blue_fold(const FftArgs& a, const Item it, doubl
     const int n = rg.n, lmax = min(a.lmax, rg.mcut);  // rows past the ring's cutoff are zero
     const XT* X = static_cast<const XT*>(a.X) + (int64_t)it.comp * a.xcomp + (int64_t)sr.ring * a.ldx +
                   4 * sr.pair + 2 * part;
-    const int64_t mrow = (int64_t)a.nring * a.ldx;
     MStep ws(mi, MSTEP, n, rg.s);
     for (int m0 = mi; m0 <= lmax; m0 += MB * MSTEP) {
         double2 tv[MB], p[MB];
@@ -467,7 +622,7 @@ template <int LOGN, typename XT, bool MULTI>
 __device__ __forceinline__ void fwd_item(const FftArgs& a, const Item it, double2* lds)
 {
     using C = P2<LOGN>;
-    constexpr int N = C::N, T = C::T, S = C::S;
+    constexpr int N = C::N, T = C::T;
     const double2* tw = a.tw + a.lens[a.rings[it.ring].len].tw;  // e^{-i pi t/N}, t < 2N
     const int seq = (int)threadIdx.x / T, tl = (int)threadIdx.x % T;
     double2* sb = lds + seq * C::SEQ;
@@ -485,11 +640,11 @@ __device__ __forceinline__ void fwd_item(const FftArgs& a, const Item it, double
         for (int r = 0; r < 8; ++r) v[r] = make_double2(pa[tl + r * T], pb[tl + r * T]);
 #pragma unroll
         for (int r = 0; r < 8; ++r)
-            v[r] = make_double2(k < a.nmaps ? v[r].x : 0.0, k + 1 < a.nmaps ? v[r].y : 0.0);
+            v[r] = make_double2(k < a.nmaps ? PIXS<XT> * v[r].x : 0.0, k + 1 < a.nmaps ? PIXS<XT> * v[r].y : 0.0);
     }
     run_passes<LOGN, 0>(v, w, sb, tl, tw);
 
-    // spectrum Z in natural order into LDS
+    // the spectrum Z in natural order into LDS
     using QL = Pass<LOGN, C::NP - 1>;
     __syncthreads();
 #pragma unroll
@@ -497,56 +652,11 @@ __device__ __forceinline__ void fwd_item(const FftArgs& a, const Item it, double
 #pragma unroll
         for (int r = 0; r < QL::R; ++r) sb[tl + T * b + r * (N / QL::R)] = v[b * QL::R + r];
     }
+    Unfold<LOGN, XT, MULTI, true> out(a, it, lds);
     __syncthreads();
 
-    if (a.F) {  // keep the data spectra of both maps (iterative map2alm), halfcomplex
-        for (int pos = tl; pos < N; pos += T) {
-            const int j = (pos == 0) ? 0 : (pos == N - 1 ? N / 2 : (pos + 1) / 2);
-            const int jn = (N - j) & (N - 1);
-            const double2 z = sb[j], y = sb[jn];
-            const double2 Fa = make_double2(0.5 * (z.x + y.x), 0.5 * (z.y - y.y));
-            const double2 Fb = make_double2(0.5 * (z.y + y.y), 0.5 * (y.x - z.x));
-            const bool im = (pos != 0) && (pos != N - 1) && ((pos & 1) == 0);
-            if (k < a.nmaps) a.F[((int64_t)k * a.ncomp + it.comp) * a.npix + first + pos] = im ? Fa.y : Fa.x;
-            if (k + 1 < a.nmaps)
-                a.F[((int64_t)(k + 1) * a.ncomp + it.comp) * a.npix + first + pos] = im ? Fb.y : Fb.x;
-        }
-    }
-
-    // unfold T_m = e^{-i m phi0} F_{m mod N}.  Lanes run over (m, pair, part):
-    // FP64 rows take two 16-byte parts per pair (map k, map k+1), FP32 rows one,
-    // so the lanes of a wave store contiguous row segments of all S pairs.
-    constexpr int LP = sizeof(XT) == 8 ? 1 : 0;  // log2 parts per pair
-    constexpr int MSTEP = C::NTH >> (LP + C::LOGS);
-    const int part = (int)threadIdx.x & ((1 << LP) - 1);
-    const int sq = ((int)threadIdx.x >> LP) & (S - 1);
-    const int mi = (int)threadIdx.x >> (LP + C::LOGS);
-    const double2* zs = lds + sq * C::SEQ;
-    const Seq so = seq_of<MULTI>(it, sq);
-    const RingDev rg = a.rings[so.ring];
-    XT* X = static_cast<XT*>(a.X) + (int64_t)it.comp * a.xcomp + (int64_t)so.ring * a.ldx + 4 * so.pair + 2 * part;
-    const int64_t mrow = (int64_t)a.nring * a.ldx;
-    const int s = rg.s, mtop = so.dead ? -1 : min(a.lmax, rg.mcut);
-    for (int m0 = mi; m0 <= mtop; m0 += MB * MSTEP) {
-        double2 ph[MB];
-#pragma unroll
-        for (int u = 0; u < MB; ++u) ph[u] = tw[((m0 + u * MSTEP) * s) & (2 * N - 1)];
-#pragma unroll
-        for (int u = 0; u < MB; ++u) {
-            const int m = m0 + u * MSTEP;
-            if (m <= mtop) {
-                const int j = m & (N - 1), jn = (N - j) & (N - 1);
-                const double2 z = zs[j], y = zs[jn];
-                const double2 Fa = make_double2(0.5 * (z.x + y.x), 0.5 * (z.y - y.y));
-                const double2 Fb = make_double2(0.5 * (z.y + y.y), 0.5 * (y.x - z.x));
-                if constexpr (sizeof(XT) == 8) {
-                    *reinterpret_cast<double2*>(X + m * mrow) = cmul(ph[u], part ? Fb : Fa);
-                } else {
-                    store4<XT>(X + m * mrow, cmul(ph[u], Fa), cmul(ph[u], Fb));
-                }
-            }
-        }
-    }
+    if (a.F) keep_spectra<LOGN, XT, MULTI>(a, it, lds);
+    out.run();
 }
 
 template <int LOGN, typename XT, bool MULTI>
@@ -554,89 +664,15 @@ __device__ __forceinline__ void inv_item(const FftArgs& a, const Item it, double
 {
     using C = P2<LOGN>;
     constexpr int N = C::N, T = C::T, S = C::S;
-    constexpr int MSTEP = C::NTH >> C::LOGS;  // = T
     const double2* tw = a.tw + a.lens[a.rings[it.ring].len].tw;
+    fold<LOGN, XT, MULTI>(a, it, lds, S * C::SEQ);
 
-    // Fold: C_j = sum_{m = j} c_m + sum_{m >= 1, -m = j} conj(c_m) of both maps,
-    // Z = C^a + i C^b, into LDS in natural order.  Lanes run over (m, pair) so a
-    // wave reads contiguous row segments of all S pairs.  d_m = c^a_m + i c^b_m is
-    // the direct term, e_m = conj(c^a_m) + i conj(c^b_m) the mirror term.
-    {
-        const int sq = (int)threadIdx.x & (S - 1);
-        const int mi = (int)threadIdx.x >> C::LOGS;
-        double2* zs = lds + sq * C::SEQ;
-        const Seq sr = seq_of<MULTI>(it, sq);
-        const RingDev rg = a.rings[sr.ring];
-        const int s = rg.s, lmax = min(a.lmax, rg.mcut);  // rows past the ring's cutoff are zero
-        const XT* X = static_cast<const XT*>(a.X) + (int64_t)it.comp * a.xcomp + (int64_t)sr.ring * a.ldx + 4 * sr.pair;
-        const int64_t mrow = (int64_t)a.nring * a.ldx;
-        if ((MULTI ? a.lmax : lmax) < N) {  // the same for every ring of the workgroup
-            // every bin has at most one direct and one mirror term: bins j = m
-            // take d_m (zero beyond lmax), then bins N - m add e_m
-            double2 e[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {  // m = mi + u T covers 0..N-1
-                const int m = mi + u * MSTEP;
-                double2 ta, tb;
-                load4<XT>(X + min(m, lmax) * mrow, ta, tb);
-                const double2 p = tw[(m * s) & (2 * N - 1)];
-                const double2 ph = make_double2(p.x, -p.y);  // e^{+i m phi0}
-                const double2 ca = cmul(ph, ta), cb = cmul(ph, tb);
-                const bool live = m <= lmax && (!a.mown || a.mown[min(m, lmax)]);
-                zs[m] = live ? make_double2(ca.x - cb.y, ca.y + cb.x) : make_double2(0.0, 0.0);
-                e[u] = (live && m >= 1) ? make_double2(ca.x + cb.y, cb.x - ca.y) : make_double2(0.0, 0.0);
-            }
-            __syncthreads();
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int m = mi + u * MSTEP;
-                if (m >= 1 && m <= lmax && (!a.mown || a.mown[m])) {
-                    double2& z = zs[N - m];
-                    z = make_double2(z.x + e[u].x, z.y + e[u].y);
-                }
-            }
-        } else {
-            // aliased rows (lmax >= N): several terms per bin, added atomically
-            for (int e = (int)threadIdx.x; e < S * C::SEQ; e += C::NTH) lds[e] = make_double2(0.0, 0.0);
-            __syncthreads();
-            for (int m0 = mi; m0 <= lmax; m0 += MB * MSTEP) {
-                double2 ta[MB], tb[MB], p[MB];
-#pragma unroll
-                for (int u = 0; u < MB; ++u) {
-                    const int m = m0 + u * MSTEP;
-                    load4<XT>(X + min(m, lmax) * mrow, ta[u], tb[u]);
-                    p[u] = tw[(m * s) & (2 * N - 1)];
-                }
-#pragma unroll
-                for (int u = 0; u < MB; ++u) {
-                    const int m = m0 + u * MSTEP;
-                    if (m <= lmax && (!a.mown || a.mown[m])) {
-                        const double2 ph = make_double2(p[u].x, -p[u].y);
-                        const double2 ca = cmul(ph, ta[u]), cb = cmul(ph, tb[u]);
-                        double* z1 = reinterpret_cast<double*>(zs + (m & (N - 1)));
-                        atomicAdd(z1, ca.x - cb.y);
-                        atomicAdd(z1 + 1, ca.y + cb.x);
-                        if (m >= 1) {
-                            double* z2 = reinterpret_cast<double*>(zs + ((N - (m & (N - 1))) & (N - 1)));
-                            atomicAdd(z2, ca.x + cb.y);
-                            atomicAdd(z2 + 1, cb.x - ca.y);
-                        }
-                    }
-                }
-            }
-        }
-        __syncthreads();
-    }
-
-    // pass-0 inputs conj(Z_j) at bins j = tl + r T; the inverse DFT is conj(DFT(conj Z))
+    // pass-0 inputs conj(Z_j) at bins j = tl + r T: the inverse DFT is conj(DFT(conj Z))
     const int seq = (int)threadIdx.x / T, tl = (int)threadIdx.x % T;
     double2* sb = lds + seq * C::SEQ;
     double2 v[8], w[8];
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        const double2 z = sb[tl + r * T];
-        v[r] = make_double2(z.x, -z.y);
-    }
+    for (int r = 0; r < 8; ++r) v[r] = sb[tl + r * T];
     __syncthreads();  // pass 0 overwrites the buffer
     run_passes<LOGN, 0>(v, w, sb, tl, tw);
 
@@ -678,37 +714,38 @@ __device__ __forceinline__ void fwd_item_blue(const FftArgs& a, const Item it, d
     double2* sb = lds + seq * C::SEQ;
     const int k = sr.dead ? a.nmaps : 2 * sr.pair;
 
-    double2 u[8];
+    double2 u[NU<XT>];
     {
         const int64_t ms = (int64_t)a.ncomp * a.npix;
         const double* pa = a.maps_in + (int64_t)it.comp * a.npix + rg.first + min(k, a.nmaps - 1) * ms;
         const double* pb = a.maps_in + (int64_t)it.comp * a.npix + rg.first + min(k + 1, a.nmaps - 1) * ms;
-        double2 c[8];
+        double2 c[NU<XT>];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
+        for (int q = 0; q < NU<XT>; ++q) {
             const int i = min(tl + q * T, n - 1);
             u[q] = make_double2(pa[i], pb[i]);
             c[q] = chirp[i];
         }
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
+        for (int q = 0; q < NU<XT>; ++q) {
             const bool live = tl + q * T < n;
-            const double2 x = make_double2(k < a.nmaps ? u[q].x : 0.0, k + 1 < a.nmaps ? u[q].y : 0.0);
+            const double2 x = make_double2(k < a.nmaps ? PIXS<XT> * u[q].x : 0.0, k + 1 < a.nmaps ? PIXS<XT> * u[q].y : 0.0);
             u[q] = live ? cmul(x, c[q]) : make_double2(0.0, 0.0);
         }
     }
-    blue_core<LOGM>(u, sb, tl, twM, bhat);
+    blue_core<LOGM, CUT<XT>>(u, sb, tl, twM, bhat);
 
-    // spectrum y_j = w_j u[k] (j = tl + k T < n) into LDS in natural order
+    // the spectrum, y_j = w_j u[k] (j = tl + k T < n), into LDS in natural order
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
+    for (int q = 0; q < NU<XT>; ++q) {
         const int j = tl + q * T;
         if (j < n) sb[j] = cmul(chirp[j], u[q]);
     }
+    Unfold<LOGM, XT, MULTI, false> out(a, it, lds);
     __syncthreads();
-
-    blue_spectrum_out<LOGM, XT, MULTI>(a, it, lds);
+    if (a.F) keep_spectra<LOGM, XT, MULTI>(a, it, lds);
+    out.run();
 }
 
 template <int LOGM, typename XT, bool MULTI>
@@ -716,7 +753,7 @@ __device__ __forceinline__ void inv_item_blue(const FftArgs& a, const Item it, d
 {
     using C = P2<LOGM>;
     constexpr int T = C::T, S = C::S;
-    blue_fold<LOGM, XT, MULTI>(a, it, lds, S * C::SEQ);
+    fold<LOGM, XT, MULTI>(a, it, lds, S * C::SEQ);
 
     const int seq = (int)threadIdx.x / T, tl = (int)threadIdx.x % T;
     const Seq sr = seq_of<MULTI>(it, seq);
@@ -729,29 +766,29 @@ __device__ __forceinline__ void inv_item_blue(const FftArgs& a, const Item it, d
 
     // Bluestein on conj(Z): pass-0 values conj(Z_i) w_i
     double2* sb = lds + seq * C::SEQ;
-    double2 u[8];
+    double2 u[NU<XT>];
     {
-        double2 c[8];
+        double2 c[NU<XT>];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) c[q] = chirp[min(tl + q * T, n - 1)];
+        for (int q = 0; q < NU<XT>; ++q) c[q] = chirp[min(tl + q * T, n - 1)];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
+        for (int q = 0; q < NU<XT>; ++q) {
             const int i = tl + q * T;
             u[q] = i < n ? cmul(sb[i], c[q]) : make_double2(0.0, 0.0);
         }
     }
     __syncthreads();  // pass 0 overwrites the buffer
-    blue_core<LOGM>(u, sb, tl, twM, bhat);
+    blue_core<LOGM, CUT<XT>>(u, sb, tl, twM, bhat);
 
     // pixels: y_j = w_j u[k] = DFT(conj Z)_j; map k = Re(conj y), map k+1 = Im(conj y)
     const int k = sr.dead ? a.nmaps : 2 * sr.pair;
     const int64_t ms = (int64_t)a.ncomp * a.npix;
     double* oa = a.maps_out + (int64_t)it.comp * a.npix + rg.first + (int64_t)k * ms;
-    double2 c[8];
+    double2 c[NU<XT>];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) c[q] = chirp[min(tl + q * T, n - 1)];
+    for (int q = 0; q < NU<XT>; ++q) c[q] = chirp[min(tl + q * T, n - 1)];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
+    for (int q = 0; q < NU<XT>; ++q) {
         const int j = tl + q * T;
         const double2 y = cmul(c[q], u[q]);
         if (j < n) {

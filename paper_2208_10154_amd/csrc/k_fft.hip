@@ -265,59 +265,12 @@ __device__ __forceinline__ void ring_dft(double2* buf, int nseq, const FftLen* L
     __syncthreads();
 }
 
-// Walks m = m0, m0 + dm, ... for one thread, keeping j = m mod n and
-// ph = (m s) mod 2n (the phase e^{-i m phi0} = tw_n[ph]) up to date.
-struct MWalk {
-    int j, ph, dj, dph, n, two_n;
-    __device__ __forceinline__ MWalk(int m0, int dm, int n_, int s)
-    {
-        n = n_;
-        two_n = 2 * n_;
-        j = m0 % n;
-        ph = (int)(((int64_t)m0 * s) % two_n);
-        dj = dm % n;
-        dph = (int)(((int64_t)dm * s) % two_n);
-    }
-    __device__ __forceinline__ void next()
-    {
-        j += dj;
-        if (j >= n) j -= n;
-        ph += dph;
-        if (ph >= two_n) ph -= two_n;
-    }
-};
-
 __device__ __forceinline__ int64_t xidx(const FftArgs& a, int comp, int m, int ring, int col)
 {
     return (int64_t)comp * a.xcomp + ((int64_t)m * a.nring + ring) * a.ldx + col;
 }
 
-// the four columns (re a, im a, re b, im b) of one map pair at one (m, ring)
-__device__ __forceinline__ void store_x4(const FftArgs& a, int64_t idx, double2 ta, double2 tb)
-{
-    if (a.x32) {
-        *reinterpret_cast<float4*>(static_cast<float*>(a.X) + idx) =
-            make_float4((float)ta.x, (float)ta.y, (float)tb.x, (float)tb.y);
-    } else {
-        double2* p = reinterpret_cast<double2*>(static_cast<double*>(a.X) + idx);
-        p[0] = ta;
-        p[1] = tb;
-    }
-}
-__device__ __forceinline__ void load_x4(const FftArgs& a, int64_t idx, double2& ta, double2& tb)
-{
-    if (a.x32) {
-        const float4 f = *reinterpret_cast<const float4*>(static_cast<const float*>(a.X) + idx);
-        ta = make_double2(f.x, f.y);
-        tb = make_double2(f.z, f.w);
-    } else {
-        const double2* p = reinterpret_cast<const double2*>(static_cast<const double*>(a.X) + idx);
-        ta = p[0];
-        tb = p[1];
-    }
-}
-
-// Unfold the packed spectrum Z = A + i B (both Hermitian) of each sequence onto
+// Unfold half the packed spectrum Z = A + i B (both Hermitian) of each sequence onto
 // T_m = e^{-i m phi0} F_{m mod n} for m = 0..lmax and store m-major.  Lanes run
 // over (m, sequence, part): an FP64 row takes two 16-byte parts per map pair
 // (map a, map b), an FP32 row one, so a wave stores contiguous row segments of
@@ -334,7 +287,8 @@ __device__ __forceinline__ void unfold_store(const FftArgs& a, const double2* bu
     const int64_t xstep = (int64_t)dm * a.nring * a.ldx;
     int64_t xi = xidx(a, comp, m0, ring, col);
     const int mtop = min(a.lmax, a.rings[ring].mcut);
-    MWalk w(m0, dm, n, s);
+    const double sg = part ? -1.0 : 1.0;  // map b: -i of (Z - conj Z'), the -i in the phase
+    MStep w(m0, dm, n, s);
     for (int mb = m0; mb <= mtop; mb += MB * dm) {
         double2 t[MB];
         int jj[MB];
@@ -349,12 +303,13 @@ __device__ __forceinline__ void unfold_store(const FftArgs& a, const double2* bu
             if (mb + u * dm <= mtop) {
                 const int j = jj[u], jn = j ? n - j : 0;
                 const double2 z = buf[P(sq, j, ls)], y = buf[P(sq, jn, ls)];
-                const double2 Fa = make_double2(0.5 * (z.x + y.x), 0.5 * (z.y - y.y));
-                const double2 Fb = make_double2(0.5 * (z.y + y.y), 0.5 * (y.x - z.x));
                 if (a.x32) {
-                    store_x4(a, xi + u * xstep, cmul(t[u], Fa), cmul(t[u], Fb));
+                    const double2 Fa = make_double2(z.x + y.x, z.y - y.y), Fb = make_double2(z.y + y.y, y.x - z.x);
+                    store4<float>(static_cast<float*>(a.X) + xi + u * xstep, cmul(t[u], Fa), cmul(t[u], Fb));
                 } else {
-                    *reinterpret_cast<double2*>(static_cast<double*>(a.X) + xi + u * xstep) = cmul(t[u], part ? Fb : Fa);
+                    const double2 Fp = make_double2(fma(sg, y.x, z.x), fma(-sg, y.y, z.y));
+                    *reinterpret_cast<double2*>(static_cast<double*>(a.X) + xi + u * xstep) =
+                        cmul(part ? make_double2(t[u].y, -t[u].x) : t[u], Fp);
                 }
             }
         }
@@ -373,6 +328,18 @@ __device__ __forceinline__ void fold_load(const FftArgs& a, double2* buf, const 
                                           const double2* tw_n)
 {
     const int n = L->n, ls = L->lstride;
+    const int mtop = min(a.lmax, a.rings[ring].mcut);  // rows past the ring's cutoff are zero
+    const double sg = CONJ ? -1.0 : 1.0;
+    if (mtop < n) {
+        const int sq = (int)threadIdx.x & (L->nseq - 1);
+        const int j0 = (int)threadIdx.x >> L->lgseq, dj = NT >> L->lgseq;
+        const int64_t x0 = xidx(a, comp, 0, ring, 4 * (pair0 + sq)), mrow = (int64_t)a.nring * a.ldx;
+        const auto put = [=](int j, double2 z) { buf[P(sq, j, ls)] = make_double2(z.x, sg * z.y); };
+        if (a.x32) fold_direct<float>(a, static_cast<const float*>(a.X) + x0, mrow, tw_n, n, s, mtop, j0, dj, put);
+        else fold_direct<double>(a, static_cast<const double*>(a.X) + x0, mrow, tw_n, n, s, mtop, j0, dj, put);
+        __syncthreads();
+        return;
+    }
     for (int e = threadIdx.x; e < L->nseq * ls; e += NT) buf[e] = make_double2(0.0, 0.0);
     __syncthreads();
     const int part = (int)threadIdx.x & 1;
@@ -380,11 +347,9 @@ __device__ __forceinline__ void fold_load(const FftArgs& a, double2* buf, const 
     const int m0 = (int)threadIdx.x >> (1 + L->lgseq), dm = NT >> (1 + L->lgseq);
     const int col = 4 * (pair0 + sq) + 2 * part;
     const int64_t xstep = (int64_t)dm * a.nring * a.ldx;
-    const int mtop = min(a.lmax, a.rings[ring].mcut);  // rows past the ring's cutoff are zero
     const int64_t xlast = xidx(a, comp, mtop, ring, col);
     int64_t xi = xidx(a, comp, m0, ring, col);
-    const double sg = CONJ ? -1.0 : 1.0;
-    MWalk w(m0, dm, n, s);
+    MStep w(m0, dm, n, s);
     for (int mb = m0; mb <= mtop; mb += MB * dm) {
         double2 tv[MB], t[MB];
         int jj[MB];
@@ -514,7 +479,7 @@ __device__ __forceinline__ void gen_fwd(const FftArgs& a, const Item& it, double
             if (e < tot) {
                 const int sq = dn.div(e), i = e - sq * n;
                 const int k = 2 * (c.it.pair0 + sq);
-                lds[P(sq, i, ls)] = make_double2(k < a.nmaps ? re[q] : 0.0, k + 1 < a.nmaps ? im[q] : 0.0);
+                lds[P(sq, i, ls)] = make_double2(k < a.nmaps ? 0.5 * re[q] : 0.0, k + 1 < a.nmaps ? 0.5 * im[q] : 0.0);
             }
         }
     }
@@ -527,8 +492,8 @@ __device__ __forceinline__ void gen_fwd(const FftArgs& a, const Item& it, double
             const int j = (pos == 0) ? 0 : (pos == n - 1 ? n / 2 : (pos + 1) / 2);
             const int jn = j ? n - j : 0;
             const double2 z = lds[P(sq, j, ls)], y = lds[P(sq, jn, ls)];
-            const double2 Fa = make_double2(0.5 * (z.x + y.x), 0.5 * (z.y - y.y));
-            const double2 Fb = make_double2(0.5 * (z.y + y.y), 0.5 * (y.x - z.x));
+            const double2 Fa = make_double2(z.x + y.x, z.y - y.y);
+            const double2 Fb = make_double2(z.y + y.y, y.x - z.x);
             const bool im = (pos != 0) && (pos != n - 1) && ((pos & 1) == 0);
             const int k = 2 * (c.it.pair0 + sq);
             if (k < a.nmaps) a.F[((int64_t)k * a.ncomp + c.comp) * a.npix + c.rg.first + pos] = im ? Fa.y : Fa.x;
@@ -630,7 +595,7 @@ __global__ __launch_bounds__(NT, ELEMS == 16 ? 2 : 4) void k_residual(FftArgs a,
                 if (ii >= 0) r0[(int64_t)ii * a.nmaps + 1] = Rb.y;
             }
         }
-        res[q] = make_double2(Ra.x - Rb.y, Ra.y + Rb.x);  // pack as Ra + i Rb
+        res[q] = make_double2(0.5 * (Ra.x - Rb.y), 0.5 * (Ra.y + Rb.x));  // half of Ra + i Rb
     }
     __syncthreads();
 #pragma unroll

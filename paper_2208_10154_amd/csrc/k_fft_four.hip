@@ -26,7 +26,7 @@ constexpr int FOUR_Q = 4;  // k1 values per thread (j < 4 x 512)
 
 // z[q][k2] += e^{-2 pi i r k1 / n} (-i)^{r k2} Y_r[k1] for k1 = tl + 512 q < j, with
 // Y_r[k1] = w_{k1} u[q] the result of blue_core on the r-th decimated sequence
-__device__ __forceinline__ void four_accumulate(double2 (&z)[FOUR_Q][4], const double2 (&u)[8], int r, int tl,
+__device__ __forceinline__ void four_accumulate(double2 (&z)[FOUR_Q][4], const double2* u, int r, int tl,
                                                 int j, int n, const double2* chirp, const double2* twn)
 {
     constexpr int T = P2<12>::T;
@@ -74,7 +74,7 @@ __device__ __forceinline__ void fwd_item_four(const FftArgs& a, const Item it, d
         for (int k2 = 0; k2 < 4; ++k2) z[q][k2] = make_double2(0.0, 0.0);
     for (int r = 0; r < 4; ++r) {
         // pass-0 values x_s w_s of the sequence x_s = z_{4s + r}, s = tl + 512 q < j
-        double2 u[8], c[FOUR_Q];
+        double2 u[NU<XT>], c[FOUR_Q];
 #pragma unroll
         for (int q = 0; q < FOUR_Q; ++q) {
             const int sq = min(tl + q * T, j - 1);
@@ -83,16 +83,16 @@ __device__ __forceinline__ void fwd_item_four(const FftArgs& a, const Item it, d
         }
 #pragma unroll
         for (int q = 0; q < FOUR_Q; ++q) {
-            const double2 x = make_double2(k < a.nmaps ? u[q].x : 0.0, k + 1 < a.nmaps ? u[q].y : 0.0);
+            const double2 x = make_double2(k < a.nmaps ? PIXS<XT> * u[q].x : 0.0, k + 1 < a.nmaps ? PIXS<XT> * u[q].y : 0.0);
             u[q] = tl + q * T < j ? cmul(x, c[q]) : make_double2(0.0, 0.0);
         }
 #pragma unroll
-        for (int q = FOUR_Q; q < 8; ++q) u[q] = make_double2(0.0, 0.0);
-        blue_core<12>(u, lds, tl, twM, bhat);
+        for (int q = FOUR_Q; q < NU<XT>; ++q) u[q] = make_double2(0.0, 0.0);
+        blue_core<12, CUT<XT>>(u, lds, tl, twM, bhat);
         four_accumulate(z, u, r, tl, j, n, chirp, twn);
         __syncthreads();  // the next sequence's first pass overwrites the buffer
     }
-    // spectrum Z in natural order into LDS, then the output of k_fft_fwd_blue
+    // the spectrum Z in natural order into LDS, then the output of fwd_item_blue
 #pragma unroll
     for (int q = 0; q < FOUR_Q; ++q) {
         const int k1 = tl + q * T;
@@ -101,8 +101,10 @@ __device__ __forceinline__ void fwd_item_four(const FftArgs& a, const Item it, d
             for (int k2 = 0; k2 < 4; ++k2) lds[k1 + j * k2] = z[q][k2];
         }
     }
+    Unfold<12, XT, false, false> out(a, it, lds);
     __syncthreads();
-    blue_spectrum_out<12, XT>(a, it, lds);
+    if (a.F) keep_spectra<12, XT, false>(a, it, lds);
+    out.run();
 }
 
 template <typename XT>
@@ -121,7 +123,7 @@ __device__ __forceinline__ void inv_item_four(const FftArgs& a, const Item it, d
 
     // conj(Z) in LDS, then the four decimated sequences into registers (the
     // inverse DFT is conj(DFT(conj Z)))
-    blue_fold<12, XT>(a, it, lds, n);
+    fold<12, XT>(a, it, lds, n);
     double2 x[FOUR_Q][4];
 #pragma unroll
     for (int q = 0; q < FOUR_Q; ++q) {
@@ -139,21 +141,21 @@ __device__ __forceinline__ void inv_item_four(const FftArgs& a, const Item it, d
     for (int r = 0; r < 4; ++r) {
         // sequence r sits in x[.][0]: the registers rotate after each sequence (a
         // register array indexed by the loop counter would live in scratch memory)
-        double2 u[8];
+        double2 u[NU<XT>];
 #pragma unroll
         for (int q = 0; q < FOUR_Q; ++q) {
             const int sq = min(tl + q * T, j - 1);
             u[q] = tl + q * T < j ? cmul(x[q][0], chirp[sq]) : make_double2(0.0, 0.0);
         }
 #pragma unroll
-        for (int q = FOUR_Q; q < 8; ++q) u[q] = make_double2(0.0, 0.0);
-#pragma unroll
         for (int q = 0; q < FOUR_Q; ++q) {
             x[q][0] = x[q][1];
             x[q][1] = x[q][2];
             x[q][2] = x[q][3];
         }
-        blue_core<12>(u, lds, tl, twM, bhat);
+#pragma unroll
+        for (int q = FOUR_Q; q < NU<XT>; ++q) u[q] = make_double2(0.0, 0.0);
+        blue_core<12, CUT<XT>>(u, lds, tl, twM, bhat);
         four_accumulate(z, u, r, tl, j, n, chirp, twn);
         __syncthreads();
     }

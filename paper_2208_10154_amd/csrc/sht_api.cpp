@@ -446,7 +446,11 @@ int build_classes(sht_plan p)
         c.kind = kv.first.first;
         c.nseq = kv.first.second;
         c.nrings = (int)kv.second.size();
-        for (int r : kv.second) c.lds_rt = std::max(c.lds_rt, p->lens[p->rings[r].len].lds);
+        c.direct = 1;
+        for (int r : kv.second) {
+            c.lds_rt = std::max(c.lds_rt, p->lens[p->rings[r].len].lds);
+            if (std::min(p->lmax, p->rings[r].mcut) >= p->rings[r].n) c.direct = 0;
+        }
         c.lds = c.kind >= FFT_P2 ? p2_lds(c.kind & 15) : c.lds_rt;
         p->classes.push_back(c);
         all.insert(all.end(), kv.second.begin(), kv.second.end());
@@ -1182,13 +1186,13 @@ int create_plan(sht_plan* out, int nside, int lmax, int spin, int nmaps, int par
     build_rings(p);
     p->nrc = (p->rn + RCHUNK - 1) / RCHUNK;
     int rc = build_fft(p);
-    if (!rc) rc = build_classes(p);
     if (!rc && nparts > 1) rc = upload(p, p->d_own, p->own);
     if (!rc && nparts > 1) rc = upload(p, p->d_mlist, mlist);
     if (!rc && p->nown == 0) rc = fail(SHT_ERR_ARG, "this part owns no order m (more parts than m pairs)");
     if (!rc) rc = build_seeds(p, p->s0, 0);
     if (!rc && spin == 2) rc = build_seeds(p, p->s2, 2);
     if (!rc) rc = build_mcut(p);
+    if (!rc) rc = build_classes(p);
     if (!rc) {
         p->chunk = default_chunk(p);
         rc = prep(p);
