@@ -50,6 +50,9 @@ constexpr int M_TR = 32;       // map2alm: rings per chunk (= RCHUNK, the skip g
 constexpr int LDS_M2A0 = 2 * 2 * M_TR * (HALF + 1), LDS_M2A2 = 2 * LDS_M2A0;
 constexpr int LDS_A2M0 = 2 * 2 * HALF * (64 + 1), LDS_A2M2 = 2 * 4 * HALF * (32 + 1);
 static_assert(M_TR == RCHUNK, "ring chunks and skip-table entries coincide");
+// The bodies below also serve the launches of both spins.  They take their arguments by
+// value: by reference the compiler formed some row addresses twice, and others in vector
+// registers (up to 4% more instructions in alm2map).
 
 // ============================================================================
 // map2alm, spin 0: A_l = sum_{north rings} lambda_l (T_N +- T_S), raw sums into
@@ -57,7 +60,7 @@ static_assert(M_TR == RCHUNK, "ring chunks and skip-table entries coincide");
 // chunks of 32; wave w owns NU column tiles of 16 and all 64 rows.
 // ============================================================================
 template <typename T, int NU, int NW>
-__device__ __forceinline__ void m2a_spin0(const LegArgs& a, int block, int nblocks, T* lam, double* ctile)
+__device__ __forceinline__ void m2a_spin0(const LegArgs a, int block, int nblocks, T* lam, double* ctile)
 {
     constexpr int RS = HALF + 1;        // [ring][row/2]
     constexpr int CLS = M_TR * RS, BUF = 2 * CLS;
@@ -226,7 +229,7 @@ __global__ __launch_bounds__(NT, 2) void k_m2a_spin0(LegArgs a)
 // 2 (B only) computes one block row of the transform; the other stays zero.
 // ============================================================================
 template <typename T, int NU, int EB, int NW>
-__device__ __forceinline__ void m2a_spin2(const LegArgs& a, int block, int nblocks, T* fpm, double* ctile)
+__device__ __forceinline__ void m2a_spin2(const LegArgs a, int block, int nblocks, T* fpm, double* ctile)
 {
     constexpr int RS = HALF + 1;
     constexpr int CLS = M_TR * RS, FOFF = 2 * CLS, BUF = 4 * CLS;
@@ -411,7 +414,7 @@ __global__ __launch_bounds__(NT, 2) void k_m2a_spin2(LegArgs a)
 constexpr int A0_TR = 64;
 
 template <typename T, int NU, int NW>
-__device__ __forceinline__ void a2m_spin0(const LegArgs& a, int block, int nblocks, T* lam, double (*ctile)[CoefTile<2>::N])
+__device__ __forceinline__ void a2m_spin0(const LegArgs a, int block, int nblocks, T* lam, double (*ctile)[CoefTile<2>::N])
 {
     constexpr int RS = A0_TR + 1;       // [row/2][ring]
     constexpr int CLS = HALF * RS, BUF = 2 * CLS;
@@ -585,7 +588,7 @@ constexpr int A2_TR = 32;
 // EB = 1 (E only) or 2 (B only) drops the other block's loads and products:
 // the half-block transforms of pixel-domain E/B separation (Sec. 2.3).
 template <typename T, int NU, int EB, int NW>
-__device__ __forceinline__ void a2m_spin2(const LegArgs& a, int block, int nblocks, T* fpm, double (*ctile)[CoefTile<4>::N])
+__device__ __forceinline__ void a2m_spin2(const LegArgs a, int block, int nblocks, T* fpm, double (*ctile)[CoefTile<4>::N])
 {
     constexpr int RS = A2_TR + 1;
     constexpr int CLS = HALF * RS, FOFF = 2 * CLS, BUF = 4 * CLS;

@@ -53,6 +53,9 @@ constexpr int M_TR = 32;
 // values of the recursion tile in LDS (both buffers, three planes) per kernel
 constexpr int LDS_M2A0 = 2 * 3 * 2 * HALF * KP, LDS_M2A2 = 2 * LDS_M2A0;
 constexpr int LDS_A2M0 = 2 * 3 * 2 * 64 * KP, LDS_A2M2 = 2 * 3 * 4 * 32 * KP;
+// The bodies below also serve the launches of both spins.  They take their arguments by
+// value: by reference the compiler formed some row addresses twice, and others in vector
+// registers (up to 4% more instructions in alm2map).
 
 // an operand split into three bf16 pieces
 struct S3 {
@@ -130,6 +133,28 @@ struct Rows {
     {
         const v2u v = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
         return ((uint64_t)v.y << 32) | v.x;
+    }
+};
+
+// Waits for every vector load of the wave.  Ahead of a loop it leaves the loop's own loads
+// as the only ones in flight at its head: otherwise the wait there is the stricter of the
+// way in and the way round, and may include the youngest load of the round before, which
+// is not needed until the round's end (k_a2m_spin2_bf, us: 8 IQU sets at nside 512 4071 ->
+// 3685, nside 1024 x 4 13.71 -> 12.19 ms, 512 x 125 in two chunks 30.80 -> 30.22).
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0f70); }  // vmcnt(0)
+
+// Scalar offsets of the eight rows of a chunk, formed once ahead of every load.  Written
+// as products at the loads, some were partially redundant between the first load and the
+// loop's, merged behind the branch to the clamped addresses and kept in vector registers:
+// each of up to 24 loads per chunk then ran in a loop over the values its lanes might hold
+// (125 IQU sets at nside 512, ms: k_a2m_spin2_bf 31.97 -> 30.80, k_a2m_spin0_bf 10.51 ->
+// 9.90).
+struct RowSteps {
+    int of[8];
+    __device__ __forceinline__ explicit RowSteps(int step)
+    {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) of[e] = __builtin_amdgcn_readfirstlane(e * step);
     }
 };
 
@@ -237,7 +262,7 @@ __device__ __forceinline__ const float* fptr(const void* base, int64_t comp, int
 // LDS: [buffer][hi, lo][parity class][class row][ring (K)].
 // ============================================================================
 template <int NU, int NW>
-__device__ __forceinline__ void m2a_spin0_bf(const LegArgs& a, int block, int nblocks, __bf16* lam, double* ctile)
+__device__ __forceinline__ void m2a_spin0_bf(const LegArgs a, int block, int nblocks, __bf16* lam, double* ctile)
 {
     constexpr int CLS = HALF * KP, PL = 2 * CLS, BUF = 3 * PL;
     static_assert(2 * BUF == LDS_M2A0);
@@ -405,7 +430,7 @@ __global__ __launch_bounds__(NT, 2) void k_m2a_spin0_bf(LegArgs a)
 // LDS: [buffer][hi, lo][F+, F-][parity class][class row][ring (K)].
 // ============================================================================
 template <int NU, int EB, int NW>
-__device__ __forceinline__ void m2a_spin2_bf(const LegArgs& a, int block, int nblocks, __bf16* fpm, double* ctile)
+__device__ __forceinline__ void m2a_spin2_bf(const LegArgs a, int block, int nblocks, __bf16* fpm, double* ctile)
 {
     constexpr int CLS = HALF * KP, FOFF = 2 * CLS, PL = 2 * FOFF, BUF = 3 * PL;
     static_assert(2 * BUF == LDS_M2A2);
@@ -603,7 +628,7 @@ __global__ __launch_bounds__(NT, 2) void k_m2a_spin2_bf(LegArgs a)
 constexpr int A0_TR = 64;
 
 template <int NU, int NW>
-__device__ __forceinline__ void a2m_spin0_bf(const LegArgs& a, int block, int nblocks, __bf16* lam, double (*ctile)[CoefTile<2>::N])
+__device__ __forceinline__ void a2m_spin0_bf(const LegArgs a, int block, int nblocks, __bf16* lam, double (*ctile)[CoefTile<2>::N])
 {
     constexpr int CLS = A0_TR * KP, PL = 2 * CLS, BUF = 3 * PL;
     static_assert(2 * BUF == LDS_A2M0);
@@ -671,7 +696,7 @@ __device__ __forceinline__ void a2m_spin0_bf(const LegArgs& a, int block, int nb
         // cost no vector address arithmetic; the last chunk of an m, whose rows
         // may pass lmax, takes the clamped per-row addresses
         const Rows ab(static_cast<const uint64_t*>(a.A) + row0 * a.ldx, (int64_t)(L + 1 - lb) * a.ldx * 8);
-        const int rstep = 2 * (int)a.ldx * 8;
+        const RowSteps rstep(2 * (int)a.ldx * 8);
         auto load_a = [&](int c) {
             if (ab.ok && lfirst + TL * c + TL - 1 <= L) {
                 const int v0 = ((lfirst + TL * c + 2 * k0 - lb) * (int)a.ldx + col) * 8;
@@ -679,8 +704,8 @@ __device__ __forceinline__ void a2m_spin0_bf(const LegArgs& a, int block, int nb
                 for (int e = 0; e < 8; ++e)
 #pragma unroll
                     for (int u = 0; u < NU; ++u) {
-                        ar[0][u][e] = ab.ld64(v0 + 128 * u, e * rstep);
-                        ar[1][u][e] = ab.ld64(v0 + (int)a.ldx * 8 + 128 * u, e * rstep);
+                        ar[0][u][e] = ab.ld64(v0 + 128 * u, rstep.of[e]);
+                        ar[1][u][e] = ab.ld64(v0 + (int)a.ldx * 8 + 128 * u, rstep.of[e]);
                     }
                 return;
             }
@@ -791,7 +816,7 @@ constexpr int A2_TR = 32;
 
 // EB = 1 (E only) or 2 (B only): the half-block transforms, as in k_leg.hip
 template <int NU, int EB, int NW>
-__device__ __forceinline__ void a2m_spin2_bf(const LegArgs& a, int block, int nblocks, __bf16* fpm, double (*ctile)[CoefTile<4>::N])
+__device__ __forceinline__ void a2m_spin2_bf(const LegArgs a, int block, int nblocks, __bf16* fpm, double (*ctile)[CoefTile<4>::N])
 {
     constexpr int CLS = A2_TR * KP, FOFF = 2 * CLS, PL = 2 * FOFF, BUF = 3 * PL;
     static_assert(2 * BUF == LDS_A2M2);
@@ -859,7 +884,7 @@ __device__ __forceinline__ void a2m_spin2_bf(const LegArgs& a, int block, int nb
         const int64_t mbytes = (int64_t)(L + 1 - lb) * a.ldx * 8;
         const Rows eb(static_cast<const uint64_t*>(a.A) + a.acomp + row0 * a.ldx, mbytes);
         const Rows bb(static_cast<const uint64_t*>(a.A) + 2 * a.acomp + row0 * a.ldx, mbytes);
-        const int rstep = 2 * (int)a.ldx * 8;
+        const RowSteps rstep(2 * (int)a.ldx * 8);
         auto load_a_tile = [&](int c, int u) {
             if (eb.ok && lfirst + TL * c + TL - 1 <= L) {
                 const int ve = ((lfirst + TL * c + 2 * k0 + po - lb) * (int)a.ldx + col + 16 * u) * 8;
@@ -867,14 +892,14 @@ __device__ __forceinline__ void a2m_spin2_bf(const LegArgs& a, int block, int nb
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     if constexpr (EB != 2) {
-                        ar[0][u][e] = eb.ld64(ve, e * rstep);
-                        ar[1][u][e] = eb.ld64(vo, e * rstep);
+                        ar[0][u][e] = eb.ld64(ve, rstep.of[e]);
+                        ar[1][u][e] = eb.ld64(vo, rstep.of[e]);
                     } else {
                         ar[0][u][e] = ar[1][u][e] = 0ull;
                     }
                     if constexpr (EB != 1) {
-                        ar[2][u][e] = bb.ld64(ve, e * rstep);
-                        ar[3][u][e] = bb.ld64(vo, e * rstep);
+                        ar[2][u][e] = bb.ld64(ve, rstep.of[e]);
+                        ar[3][u][e] = bb.ld64(vo, rstep.of[e]);
                     } else {
                         ar[2][u][e] = ar[3][u][e] = 0ull;
                     }
@@ -918,6 +943,7 @@ __device__ __forceinline__ void a2m_spin2_bf(const LegArgs& a, int block, int nb
         seed_of(sd, min(1, nch - 1));
 #pragma unroll
         for (int u = 0; u < NU; ++u) load_a_tile(0, u);
+        wait_loads();
         __syncthreads();
         for (int c = 0; c < nch; ++c) {
             const int b = c & 1;
