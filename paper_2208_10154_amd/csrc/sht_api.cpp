@@ -778,6 +778,9 @@ LegArgs leg_args(sht_plan p, const SeedSet& S)
     a.rn = p->rn;
     a.nring = p->nring;
     a.spin = S.spin;
+    a.owned = p->nparts > 1 ? (const int*)p->d_mlist.p : nullptr;
+    a.nowned = p->nown;
+    a.nparts = p->nparts;
     return a;
 }
 
@@ -850,8 +853,8 @@ int run_to_mmajor(sht_plan p, const double* alm, int nm, int sel)
     return SHT_OK;
 }
 
-// a plan owning part of the m runs the alm2map kernels on its m list (the
-// map2alm kernels and the layout kernels find no tiles for the other m)
+// a plan owning part of the m runs the alm2map kernels on its m list (for map2alm see
+// LegArgs::owned; the layout kernels find no tiles for the other m)
 void own_list(sht_plan p, LegArgs& a)
 {
     if (p->nparts <= 1) return;

@@ -95,6 +95,12 @@ struct LegArgs {
     // ntiles their total
     const int* mlist;
     int nlist;
+    // a plan that owns part of the m: its m in increasing order, and the number of parts.
+    // The i-th of them is at least nparts (i - 1).  The alm2map kernels get it as mlist;
+    // the map2alm kernels of k_leg_reg.hip deal their work by it, those of k_leg.hip find
+    // no tiles for the other m
+    const int* owned;
+    int nowned, nparts;
     // > 1: each workgroup's reduction range (map2alm: ring chunks, alm2map: l
     // tiles) is split over ksplit workgroups that add into pre-zeroed outputs
     // (list mode, where one level's grid is too small to fill the chip)
