@@ -233,7 +233,10 @@ enum sht_stage {
 };
 
 /* Enable (1) or disable (0) per-stage timing: when enabled every stage's kernel
- * launches are bracketed by HIP events on the plan's stream.  Off by default. */
+ * launches are bracketed by HIP events on the plan's stream.  Off by default.
+ * Small calls of a spin-2 plan run both spins' Legendre contractions in one launch;
+ * while stages are timed they run one after the other (same kernels, same results),
+ * so their stage times add up to more than the call takes without the profiler. */
 int sht_plan_set_profiling(sht_plan plan, int enable);
 
 /* Synchronise the plan's stream and return, per stage (arrays of SHT_NSTAGE),

@@ -904,31 +904,31 @@ hipError_t launch_a2m_f32(const LegArgs& a, hipStream_t st)
 // One launch for both spins (a0: spin 0, a2: spin 2, all of E and B) where their blocks
 // fill the chip's 512 slots at most twelve times (nside 128, 30 sets: map2alm 203 -> 183
 // us, alm2map 230 -> 199); false: not launched.
-bool launch_leg_m2a_pair_f32(const LegArgs& a0, const LegArgs& a2, hipStream_t st)
+bool launch_leg_m2a_pair_f32(const LegArgs& a0, const LegArgs& a2, int spins, hipStream_t st)
 {
     const int c2 = a2.ntiles, c0 = a0.ntiles;
     if (a2.eb || a2.ldx != 64 || a0.ksplit > 1 || a2.ksplit > 1 || c0 + c2 > 6144 || c0 < 1 || c2 < 1) return false;
     LegArgs b2 = a2, b0 = a0;
     b2.ctiles = b0.ctiles = 1;
-    const int n2 = (c2 + 7) / 8 * 8;
-    const dim3 grid(n2 + c0), blk(NT);
-    if (narrow(a2) == 1) hipLaunchKernelGGL((k_m2a_pair32<1>), grid, blk, 0, st, b2, c2, n2, b0, c0);
-    else if (narrow(a2) == 2) hipLaunchKernelGGL((k_m2a_pair32<2>), grid, blk, 0, st, b2, c2, n2, b0, c0);
-    else hipLaunchKernelGGL((k_m2a_pair32<0>), grid, blk, 0, st, b2, c2, n2, b0, c0);
+    const PairGrid pg(c2, c0, spins);
+    const dim3 grid(pg.total), blk(NT);
+    if (narrow(a2) == 1) hipLaunchKernelGGL((k_m2a_pair32<1>), grid, blk, 0, st, b2, pg.n2, pg.first0, b0, c0);
+    else if (narrow(a2) == 2) hipLaunchKernelGGL((k_m2a_pair32<2>), grid, blk, 0, st, b2, pg.n2, pg.first0, b0, c0);
+    else hipLaunchKernelGGL((k_m2a_pair32<0>), grid, blk, 0, st, b2, pg.n2, pg.first0, b0, c0);
     return true;
 }
 
-bool launch_leg_a2m_pair_f32(const LegArgs& a0, const LegArgs& a2, hipStream_t st)
+bool launch_leg_a2m_pair_f32(const LegArgs& a0, const LegArgs& a2, int spins, hipStream_t st)
 {
     const int c2 = nm_rows(a2) * ((a2.rn + A2_TR - 1) / A2_TR), c0 = nm_rows(a0) * ((a0.rn + A0_TR - 1) / A0_TR);
     if (a2.eb || a2.ldx != 64 || a0.ksplit > 1 || a2.ksplit > 1 || c0 + c2 > 6144) return false;
     LegArgs b2 = a2, b0 = a0;
     b2.ctiles = b0.ctiles = 1;
-    const int n2 = (c2 + 7) / 8 * 8;
-    const dim3 grid(n2 + c0), blk(NT);
-    if (narrow(a2) == 1) hipLaunchKernelGGL((k_a2m_pair32<1>), grid, blk, 0, st, b2, c2, n2, b0, c0);
-    else if (narrow(a2) == 2) hipLaunchKernelGGL((k_a2m_pair32<2>), grid, blk, 0, st, b2, c2, n2, b0, c0);
-    else hipLaunchKernelGGL((k_a2m_pair32<0>), grid, blk, 0, st, b2, c2, n2, b0, c0);
+    const PairGrid pg(c2, c0, spins);
+    const dim3 grid(pg.total), blk(NT);
+    if (narrow(a2) == 1) hipLaunchKernelGGL((k_a2m_pair32<1>), grid, blk, 0, st, b2, pg.n2, pg.first0, b0, c0);
+    else if (narrow(a2) == 2) hipLaunchKernelGGL((k_a2m_pair32<2>), grid, blk, 0, st, b2, pg.n2, pg.first0, b0, c0);
+    else hipLaunchKernelGGL((k_a2m_pair32<0>), grid, blk, 0, st, b2, pg.n2, pg.first0, b0, c0);
     return true;
 }
 

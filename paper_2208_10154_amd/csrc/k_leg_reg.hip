@@ -1113,20 +1113,20 @@ hipError_t m2a_tile(const LegArgs& a, const M2aPick& k, int prec, hipStream_t st
 }
 
 template <int NC2, int NC0>
-void go_m2a_pair(const LegArgs& a0, const LegArgs& a2, hipStream_t st)
+void go_m2a_pair(const LegArgs& a0, const LegArgs& a2, int spins, hipStream_t st)
 {
     const int ncg2 = tiles_of(a2, NC2 / 2), ncg0 = tiles_of(a0, NC0);
-    const int n2 = (blocks_m2a(a2, 16 * SEG, ncg2) + 7) / 8 * 8, n0 = blocks_m2a(a0, 16 * SEG, ncg0);
-    hipLaunchKernelGGL((k_m2a_pair<NC2, NC0>), dim3(n2 + n0), dim3(64 * RWAVES), 0, st, a2, ncg2, n2, a0, ncg0);
+    const PairGrid pg(blocks_m2a(a2, 16 * SEG, ncg2), blocks_m2a(a0, 16 * SEG, ncg0), spins);
+    hipLaunchKernelGGL((k_m2a_pair<NC2, NC0>), dim3(pg.total), dim3(64 * RWAVES), 0, st, a2, ncg2, pg.first0, a0, ncg0);
 }
 
 template <int NC, int R>
-void go_a2m_pair(const LegArgs& a0, const LegArgs& a2, hipStream_t st)
+void go_a2m_pair(const LegArgs& a0, const LegArgs& a2, int spins, hipStream_t st)
 {
     const int nrt = (a2.rn + 16 * R - 1) / (16 * R);
     const int per2 = nrt * tiles_of(a2, NC / 2), per0 = nrt * tiles_of(a0, NC);
-    const int n2 = (blocks_for(a2, per2) + 7) / 8 * 8, n0 = blocks_for(a0, per0);
-    hipLaunchKernelGGL((k_a2m_pair<NC, R>), dim3(n2 + n0), dim3(64), 0, st, a2, per2, n2, a0, per0, nrt);
+    const PairGrid pg(blocks_for(a2, per2), blocks_for(a0, per0), spins);
+    hipLaunchKernelGGL((k_a2m_pair<NC, R>), dim3(pg.total), dim3(64), 0, st, a2, per2, pg.first0, a0, per0, nrt);
 }
 
 }  // namespace
@@ -1142,33 +1142,33 @@ hipError_t launch_leg_m2a_reg(const LegArgs& all, int prec, hipStream_t st)
 
 // Pairing pays while one spin alone leaves the chip part empty: map2alm where both spins
 // split their rings, alm2map up to 8192 waves (nside 64, 16 IQU sets).
-bool launch_leg_m2a_pair(const LegArgs& all0, const LegArgs& all2, int prec, hipStream_t st)
+bool launch_leg_m2a_pair(const LegArgs& all0, const LegArgs& all2, int prec, int spins, hipStream_t st)
 {
-    if (prec == 2) return launch_leg_m2a_pair_bf16(all0, all2, st);
-    if (prec == 1) return !leg_m2a_reg(all0, prec) && !leg_m2a_reg(all2, prec) && launch_leg_m2a_pair_f32(all0, all2, st);
+    if (prec == 2) return launch_leg_m2a_pair_bf16(all0, all2, spins, st);
+    if (prec == 1) return !leg_m2a_reg(all0, prec) && !leg_m2a_reg(all2, prec) && launch_leg_m2a_pair_f32(all0, all2, spins, st);
     const LegArgs a0 = on_owned(all0), a2 = on_owned(all2);
     const M2aPick k0 = pick_m2a(a0, prec), k2 = pick_m2a(a2, prec);
     if (!k0.split || !k2.split) return false;
-    if (k2.nc == 4) go_m2a_pair<4, 4>(a0, a2, st);
-    else if (k0.nc == 4) go_m2a_pair<16, 4>(a0, a2, st);
-    else go_m2a_pair<16, 16>(a0, a2, st);
+    if (k2.nc == 4) go_m2a_pair<4, 4>(a0, a2, spins, st);
+    else if (k0.nc == 4) go_m2a_pair<16, 4>(a0, a2, spins, st);
+    else go_m2a_pair<16, 16>(a0, a2, spins, st);
     return true;
 }
 
-bool launch_leg_a2m_pair(const LegArgs& a0, const LegArgs& a2, int prec, hipStream_t st)
+bool launch_leg_a2m_pair(const LegArgs& a0, const LegArgs& a2, int prec, int spins, hipStream_t st)
 {
-    if (prec == 2) return launch_leg_a2m_pair_bf16(a0, a2, st);
-    if (prec == 1) return launch_leg_a2m_pair_f32(a0, a2, st);
+    if (prec == 2) return launch_leg_a2m_pair_bf16(a0, a2, spins, st);
+    if (prec == 1) return launch_leg_a2m_pair_f32(a0, a2, spins, st);
     if (a2.eb) return false;
     const double waves = (double)nm_rows(a2) * ((a2.rn + 15) / 16);
     if (a2.ncols == 2) {
         if (waves > 8192.0) return false;
-        if (waves > 4096.0) go_a2m_pair<4, 2>(a0, a2, st);
-        else go_a2m_pair<4, 1>(a0, a2, st);
+        if (waves > 4096.0) go_a2m_pair<4, 2>(a0, a2, spins, st);
+        else go_a2m_pair<4, 1>(a0, a2, spins, st);
         return true;
     }
     if (waves * tiles_of(a2, 8) > 8192.0) return false;
-    go_a2m_pair<16, 1>(a0, a2, st);
+    go_a2m_pair<16, 1>(a0, a2, spins, st);
     return true;
 }
 

@@ -862,20 +862,35 @@ void own_list(sht_plan p, LegArgs& a)
     a.nlist = p->nown;
 }
 
+// Both spins of a small call in one launch; false: not launched.  With profiling on, one
+// spin after the other with the kernel of the pair, so that each stage has its own time
+// and the results are those of the single launch.
+using PairLaunch = bool (*)(const LegArgs&, const LegArgs&, int, int, hipStream_t);
+bool run_pair(sht_plan p, PairLaunch launch, const LegArgs& a0, const LegArgs& a2, int stage0, int stage2)
+{
+    if (!p->profiling) return launch(a0, a2, p->prec, PAIR_BOTH, p->stream);
+    {
+        StageTimer t(p, stage0);
+        if (!launch(a0, a2, p->prec, PAIR_SPIN0, p->stream)) {
+            t.drop();
+            return false;
+        }
+    }
+    StageTimer t(p, stage2);
+    return launch(a0, a2, p->prec, PAIR_SPIN2, p->stream);
+}
+
 // m-major rows -> ring Fourier coefficients of the selected components
 int run_leg_a2m(sht_plan p, int sel)
 {
-    if (sel_t(sel) && sel_pol(p, sel) && !sel_eb(sel)) {  // small calls: one launch, timed as spin 2
-        StageTimer t(p, SHT_STAGE_A2M_SPIN2);
+    if (sel_t(sel) && sel_pol(p, sel) && !sel_eb(sel)) {
         LegArgs a0 = leg_args(p, p->s0), a2 = leg_args(p, p->s2);
         a0.A = a2.A = ws_Aop(p);
         own_list(p, a0);
         own_list(p, a2);
-        if (launch_leg_a2m_pair(a0, a2, p->prec, p->stream)) {
-            HIPCHK(hipGetLastError());
-            return SHT_OK;
-        }
-        t.drop();
+        const bool both = run_pair(p, launch_leg_a2m_pair, a0, a2, SHT_STAGE_A2M_SPIN0, SHT_STAGE_A2M_SPIN2);
+        HIPCHK(hipGetLastError());
+        if (both) return SHT_OK;
     }
     if (sel_t(sel)) {
         StageTimer t(p, SHT_STAGE_A2M_SPIN0);
@@ -925,13 +940,10 @@ int run_m2a(sht_plan p, double* alm, int nm, int accumulate, int sel = SHT_COMP_
 {
     const double dsig = 4.0 * M_PI / (double)p->npix;
     const bool t = sel_t(sel), pol = sel_pol(p, sel);
-    bool both = false;
-    if (t && pol && !sel_eb(sel)) {  // small calls: one launch, timed as spin 2
-        StageTimer tm(p, SHT_STAGE_M2A_SPIN2);
-        both = launch_leg_m2a_pair(leg_args(p, p->s0), leg_args(p, p->s2), p->prec, p->stream);
-        HIPCHK(hipGetLastError());
-        if (!both) tm.drop();
-    }
+    const bool both = t && pol && !sel_eb(sel) &&
+                      run_pair(p, launch_leg_m2a_pair, leg_args(p, p->s0), leg_args(p, p->s2), SHT_STAGE_M2A_SPIN0,
+                               SHT_STAGE_M2A_SPIN2);
+    HIPCHK(hipGetLastError());
     if (t && !both) {
         StageTimer tm(p, SHT_STAGE_M2A_SPIN0);
         HIPCHK(launch_leg_m2a(leg_args(p, p->s0), p->prec, p->stream));
@@ -1055,14 +1067,9 @@ int run_level(sht_plan p, double* alm, int nm, int d)
         c[i].accumulate = 1;
         c[i].scale = dsig;
     }
-    auto pair = [&](int stage, bool (*launch)(const LegArgs&, const LegArgs&, int, hipStream_t)) {
-        if (nspin != 2 || p->prec != SHT_FP64) return false;  // the other precisions split reductions below
-        StageTimer t(p, stage);
-        if (launch(a[0], a[1], p->prec, p->stream)) return true;
-        t.drop();
-        return false;
-    };
-    const bool m2a_both = pair(SHT_STAGE_M2A_SPIN2, launch_leg_m2a_pair);
+    // the other precisions split reductions below
+    const bool may_pair = nspin == 2 && p->prec == SHT_FP64;
+    const bool m2a_both = may_pair && run_pair(p, launch_leg_m2a_pair, a[0], a[1], SHT_STAGE_M2A_SPIN0, SHT_STAGE_M2A_SPIN2);
     for (int i = 0; i < nspin && !m2a_both; ++i) {
         const int nt = a[i].ntiles;
         StageTimer t(p, i == 0 ? SHT_STAGE_M2A_SPIN0 : SHT_STAGE_M2A_SPIN2);
@@ -1080,7 +1087,7 @@ int run_level(sht_plan p, double* alm, int nm, int d)
         HIPCHK(launch_level_commit(c[0], 1, c[nspin - 1], nspin == 2 ? 2 : 0, p->prec, p->stream));
     }
     for (int i = 0; i < nspin; ++i) a[i].A = ws_Aop(p);  // the rows the commit wrote as the synthesis operand
-    const bool a2m_both = pair(SHT_STAGE_A2M_SPIN2, launch_leg_a2m_pair);
+    const bool a2m_both = may_pair && run_pair(p, launch_leg_a2m_pair, a[0], a[1], SHT_STAGE_A2M_SPIN0, SHT_STAGE_A2M_SPIN2);
     for (int i = 0; i < nspin && !a2m_both; ++i) {
         StageTimer t(p, i == 0 ? SHT_STAGE_A2M_SPIN0 : SHT_STAGE_A2M_SPIN2);
         const int tr = i == 0 ? 64 : 32;  // rings per alm2map tile

@@ -198,12 +198,23 @@ hipError_t launch_leg_a2m_bf16(const LegArgs& a, hipStream_t st);
 bool leg_m2a_reg(const LegArgs& a, int prec);
 hipError_t launch_leg_m2a_reg(const LegArgs& a, int prec, hipStream_t st);
 hipError_t launch_leg_a2m_reg(const LegArgs& a, hipStream_t st);
-// both spins of one call (a0: spin 0, a2: spin 2) in one launch; false: not launched
-bool launch_leg_m2a_pair(const LegArgs& a0, const LegArgs& a2, int prec, hipStream_t st);
-bool launch_leg_a2m_pair(const LegArgs& a0, const LegArgs& a2, int prec, hipStream_t st);
-bool launch_leg_m2a_pair_f32(const LegArgs& a0, const LegArgs& a2, hipStream_t st);
-bool launch_leg_a2m_pair_f32(const LegArgs& a0, const LegArgs& a2, hipStream_t st);
-bool launch_leg_m2a_pair_bf16(const LegArgs& a0, const LegArgs& a2, hipStream_t st);
-bool launch_leg_a2m_pair_bf16(const LegArgs& a0, const LegArgs& a2, hipStream_t st);
+// both spins of one call (a0: spin 0, a2: spin 2) in one launch; false: not launched.
+// spins: PAIR_BOTH, or one spin of the pair alone (same kernel and values), to time it
+enum { PAIR_SPIN0 = 1, PAIR_SPIN2 = 2, PAIR_BOTH = 3 };
+bool launch_leg_m2a_pair(const LegArgs& a0, const LegArgs& a2, int prec, int spins, hipStream_t st);
+bool launch_leg_a2m_pair(const LegArgs& a0, const LegArgs& a2, int prec, int spins, hipStream_t st);
+bool launch_leg_m2a_pair_f32(const LegArgs& a0, const LegArgs& a2, int spins, hipStream_t st);
+bool launch_leg_a2m_pair_f32(const LegArgs& a0, const LegArgs& a2, int spins, hipStream_t st);
+bool launch_leg_m2a_pair_bf16(const LegArgs& a0, const LegArgs& a2, int spins, hipStream_t st);
+bool launch_leg_a2m_pair_bf16(const LegArgs& a0, const LegArgs& a2, int spins, hipStream_t st);
+// blocks of a pair: n2 of spin 2 from block 0 on (in a grid of whole deals to the 8 XCDs,
+// if spin 0 follows), then n0 of spin 0, the first of them at block `first0`
+struct PairGrid {
+    int n2, first0, total;
+    PairGrid(int c2, int c0, int spins)
+        : n2(spins & PAIR_SPIN2 ? c2 : 0), first0((n2 + 7) / 8 * 8), total(spins & PAIR_SPIN0 ? first0 + c0 : n2)
+    {
+    }
+};
 
 }  // namespace sht
