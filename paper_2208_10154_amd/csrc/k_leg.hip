@@ -908,7 +908,7 @@ bool launch_leg_m2a_pair_f32(const LegArgs& a0, const LegArgs& a2, int spins, hi
 {
     const int c2 = a2.ntiles, c0 = a0.ntiles;
     if (a2.eb || a2.ldx != 64 || a0.ksplit > 1 || a2.ksplit > 1 || c0 + c2 > 6144 || c0 < 1 || c2 < 1) return false;
-    LegArgs b2 = a2, b0 = a0;
+    LegArgs b2 = by_tiles(a2), b0 = by_tiles(a0);
     b2.ctiles = b0.ctiles = 1;
     const PairGrid pg(c2, c0, spins);
     const dim3 grid(pg.total), blk(NT);
@@ -935,9 +935,10 @@ bool launch_leg_a2m_pair_f32(const LegArgs& a0, const LegArgs& a2, int spins, hi
 hipError_t launch_leg_m2a(const LegArgs& a, int prec, hipStream_t st)
 {
     if (a.ksplit <= 1 && leg_m2a_reg(a, prec)) return launch_leg_m2a_reg(a, prec, st);
-    if (prec == 2) return launch_leg_m2a_bf16(a, st);
-    if (prec == 0) return launch_m2a_t<double>(a, st);
-    return launch_m2a_t<float>(a, st);
+    const LegArgs b = by_tiles(a);
+    if (prec == 2) return launch_leg_m2a_bf16(b, st);
+    if (prec == 0) return launch_m2a_t<double>(b, st);
+    return launch_m2a_t<float>(b, st);
 }
 
 hipError_t launch_leg_a2m(const LegArgs& a, int prec, hipStream_t st)

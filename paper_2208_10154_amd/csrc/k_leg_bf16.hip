@@ -1143,7 +1143,7 @@ bool launch_leg_m2a_pair_bf16(const LegArgs& a0, const LegArgs& a2, int spins, h
 {
     const int c2 = a2.ntiles, c0 = a0.ntiles;
     if (a2.eb || a2.ldx != 64 || a0.ksplit > 1 || a2.ksplit > 1 || c0 + c2 > 2048 || c0 < 1 || c2 < 1) return false;
-    LegArgs b2 = a2, b0 = a0;
+    LegArgs b2 = by_tiles(a2), b0 = by_tiles(a0);
     b2.ctiles = b0.ctiles = 1;
     const PairGrid pg(c2, c0, spins);
     const dim3 grid(pg.total), blk(NT);

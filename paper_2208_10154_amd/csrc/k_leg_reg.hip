@@ -112,62 +112,62 @@ int blocks_for(const LegArgs& a, int per)
     return (n + g - 1) / g * g * per;
 }
 
-// map2alm: l tiles of rtl rows, fewer toward high m.  The m are dealt in groups of g
-// consecutive positions (of all m, or of the list), which all get as many blocks as the
-// first of them can have tiles.  A part plan deals its own m: it owns one or two residues
-// of m modulo the number of parts, so the deal by m mod 8 put its work on one or two XCDs
-// (nside 2048, 2 IQU sets, part 0 or 3 of 8: spin 2 49.7 -> 10.2 ms, spin 0 13.7 -> 2.9; of 4:
-// 49.9 -> 20.2, 13.7 -> 5.9).
-__host__ __device__ inline bool by_owned(const LegArgs& a) { return a.mlist && a.mlist == a.owned; }
-__host__ __device__ inline int deal_size(const LegArgs& a) { return a.mlist && !by_owned(a) ? 1 : m_group(a); }
-__host__ __device__ inline int deals(const LegArgs& a) { return (nm_rows(a) + deal_size(a) - 1) / deal_size(a); }
+// map2alm: l tiles of rtl rows, fewer toward high m.  The m, or the m that a part plan
+// owns, are dealt in groups of g consecutive positions, which all get as many blocks as
+// the first of them can have tiles.  (By the position, not by m itself: a part owns one or
+// two residues of m modulo the number of parts, so its work lay on one or two XCDs.  Nside
+// 2048, 2 IQU sets, part 0 or 3 of 8: spin 2 49.7 -> 10.2 ms, spin 0 13.7 -> 2.9; of 4:
+// 49.9 -> 20.2, 13.7 -> 5.9.)  Other lists, the few m of a level, give every m the same
+// number of blocks.
+__host__ __device__ inline int most_tiles(const LegArgs& a, int rtl) { return (a.lmax + rtl) / rtl; }
+__host__ __device__ inline int deal_log(const LegArgs& a) { return m_group(a) == 1 ? 0 : 3; }
 // number of deals whose first m can have more than nt tiles: whose lower bound (position
-// i: m = i, owned m: nparts (i - 1), other lists: 0) lies below lmax + 1 - nt rtl
+// i: m = i, owned m: mstep (i - 1)) lies below lmax + 1 - nt rtl
 __host__ __device__ inline int deals_above(const LegArgs& a, int rtl, int nt)
 {
-    const int x = a.lmax + 1 - nt * rtl, g = deal_size(a);
+    const int x = a.lmax + 1 - nt * rtl, lg = deal_log(a), up = (1 << lg) - 1;
     if (x <= 0) return 0;
-    if (!a.mlist) return (x + g - 1) / g;
-    if (!by_owned(a)) return deals(a);
-    const int e = ((x + a.nparts - 1) / a.nparts + g) / g;  // positions i < x / nparts + 1
-    return e < deals(a) ? e : deals(a);
+    if (!a.mstep) return (x + up) >> lg;
+    const int e = ((x + a.mstep - 1) / a.mstep + 1 + up) >> lg;  // positions i < x / mstep + 1
+    const int all = (nm_rows(a) + up) >> lg;
+    return e < all ? e : all;
 }
-__host__ __device__ inline int most_tiles(const LegArgs& a, int rtl) { return (a.lmax + rtl) / rtl; }
 int blocks_m2a(const LegArgs& a, int rtl, int ncg)
 {
+    if (a.mlist && !a.mstep) return a.nlist * most_tiles(a, rtl) * ncg;
     int n = 0;
     for (int nt = most_tiles(a, rtl); nt > 0; --nt) n += deals_above(a, rtl, nt - 1);
-    return n * deal_size(a) * ncg;
+    return (n << deal_log(a)) * ncg;
 }
 // the (m, l tile, column group) of this block; false past the m's tiles
 __device__ __forceinline__ bool m2a_task(const LegArgs& a, int b, int rtl, int ncg, int& m, int& lt, int& cg)
 {
-    const int g = deal_size(a), total = deals(a);
-    int rem = g == 8 ? b >> 3 : b, q = 0, nt = most_tiles(a, rtl);
-    while (nt > 1) {  // deals q .. e - 1 have nt tiles per m
-        const int e = deals_above(a, rtl, nt - 1), n = (e - q) * nt * ncg;
-        if (rem < n) break;
-        rem -= n;
-        q = e;
-        --nt;
+    int slot;
+    if (a.mlist && !a.mstep) {
+        const int per = most_tiles(a, rtl) * ncg, u = b / per;
+        if (u >= a.nlist) return false;
+        m = a.mlist[u];
+        slot = b - u * per;
+    } else {
+        const int lg = deal_log(a);
+        int rem = b >> lg, q = 0, nt = most_tiles(a, rtl);
+        while (nt > 1) {  // deals q .. e - 1 have nt tiles per m
+            const int e = deals_above(a, rtl, nt - 1), n = (e - q) * nt * ncg;
+            if (rem < n) break;
+            rem -= n;
+            q = e;
+            --nt;
+        }
+        const int d = rem / (nt * ncg);
+        slot = rem - d * nt * ncg;
+        m = ((q + d) << lg) + (b & ((1 << lg) - 1));
+        if (m >= nm_rows(a)) return false;
+        if (a.mlist) m = a.mlist[m];
     }
-    const int d = rem / (nt * ncg), slot = rem - d * nt * ncg;
-    const int unit = (q + d) * g + (g == 8 ? b & 7 : 0);
-    if (q + d >= total || unit >= nm_rows(a)) return false;
-    m = __builtin_amdgcn_readfirstlane(a.mlist ? a.mlist[unit] : unit);
+    m = __builtin_amdgcn_readfirstlane(m);
     lt = __builtin_amdgcn_readfirstlane(slot / ncg);
     cg = slot - lt * ncg;
     return lt < ntl(a, m, rtl);
-}
-// a part plan's map2alm on its own m
-LegArgs on_owned(const LegArgs& a)
-{
-    LegArgs b = a;
-    if (!a.mlist && a.owned) {
-        b.mlist = a.owned;
-        b.nlist = a.nowned;
-    }
-    return b;
 }
 
 // emitter of one recursion row: its values are A operands at once
@@ -1131,22 +1131,20 @@ void go_a2m_pair(const LegArgs& a0, const LegArgs& a2, int spins, hipStream_t st
 
 }  // namespace
 
-bool leg_m2a_reg(const LegArgs& a, int prec) { return pick_m2a(on_owned(a), prec).c != 0; }
+bool leg_m2a_reg(const LegArgs& a, int prec) { return pick_m2a(a, prec).c != 0; }
 
-hipError_t launch_leg_m2a_reg(const LegArgs& all, int prec, hipStream_t st)
+hipError_t launch_leg_m2a_reg(const LegArgs& a, int prec, hipStream_t st)
 {
-    const LegArgs a = on_owned(all);
     const M2aPick k = pick_m2a(a, prec);
     return a.spin == 0 ? m2a_tile<0>(a, k, prec, st) : m2a_tile<2>(a, k, prec, st);
 }
 
 // Pairing pays while one spin alone leaves the chip part empty: map2alm where both spins
 // split their rings, alm2map up to 8192 waves (nside 64, 16 IQU sets).
-bool launch_leg_m2a_pair(const LegArgs& all0, const LegArgs& all2, int prec, int spins, hipStream_t st)
+bool launch_leg_m2a_pair(const LegArgs& a0, const LegArgs& a2, int prec, int spins, hipStream_t st)
 {
-    if (prec == 2) return launch_leg_m2a_pair_bf16(all0, all2, spins, st);
-    if (prec == 1) return !leg_m2a_reg(all0, prec) && !leg_m2a_reg(all2, prec) && launch_leg_m2a_pair_f32(all0, all2, spins, st);
-    const LegArgs a0 = on_owned(all0), a2 = on_owned(all2);
+    if (prec == 2) return launch_leg_m2a_pair_bf16(a0, a2, spins, st);
+    if (prec == 1) return !leg_m2a_reg(a0, prec) && !leg_m2a_reg(a2, prec) && launch_leg_m2a_pair_f32(a0, a2, spins, st);
     const M2aPick k0 = pick_m2a(a0, prec), k2 = pick_m2a(a2, prec);
     if (!k0.split || !k2.split) return false;
     if (k2.nc == 4) go_m2a_pair<4, 4>(a0, a2, spins, st);

@@ -778,9 +778,6 @@ LegArgs leg_args(sht_plan p, const SeedSet& S)
     a.rn = p->rn;
     a.nring = p->nring;
     a.spin = S.spin;
-    a.owned = p->nparts > 1 ? (const int*)p->d_mlist.p : nullptr;
-    a.nowned = p->nown;
-    a.nparts = p->nparts;
     return a;
 }
 
@@ -853,13 +850,14 @@ int run_to_mmajor(sht_plan p, const double* alm, int nm, int sel)
     return SHT_OK;
 }
 
-// a plan owning part of the m runs the alm2map kernels on its m list (for map2alm see
-// LegArgs::owned; the layout kernels find no tiles for the other m)
+// a plan owning part of the m runs the Legendre kernels on its m list (the layout kernels
+// find no tiles for the other m)
 void own_list(sht_plan p, LegArgs& a)
 {
     if (p->nparts <= 1) return;
     a.mlist = (const int*)p->d_mlist.p;
     a.nlist = p->nown;
+    a.mstep = p->nparts;
 }
 
 // Both spins of a small call in one launch; false: not launched.  With profiling on, one
@@ -940,19 +938,19 @@ int run_m2a(sht_plan p, double* alm, int nm, int accumulate, int sel = SHT_COMP_
 {
     const double dsig = 4.0 * M_PI / (double)p->npix;
     const bool t = sel_t(sel), pol = sel_pol(p, sel);
-    const bool both = t && pol && !sel_eb(sel) &&
-                      run_pair(p, launch_leg_m2a_pair, leg_args(p, p->s0), leg_args(p, p->s2), SHT_STAGE_M2A_SPIN0,
-                               SHT_STAGE_M2A_SPIN2);
+    LegArgs a0 = leg_args(p, p->s0), a2 = leg_args(p, pol ? p->s2 : p->s0);
+    a2.eb = sel_eb(sel);
+    own_list(p, a0);
+    own_list(p, a2);
+    const bool both = t && pol && !a2.eb && run_pair(p, launch_leg_m2a_pair, a0, a2, SHT_STAGE_M2A_SPIN0, SHT_STAGE_M2A_SPIN2);
     HIPCHK(hipGetLastError());
     if (t && !both) {
         StageTimer tm(p, SHT_STAGE_M2A_SPIN0);
-        HIPCHK(launch_leg_m2a(leg_args(p, p->s0), p->prec, p->stream));
+        HIPCHK(launch_leg_m2a(a0, p->prec, p->stream));
     }
     if (pol && !both) {
         StageTimer tm(p, SHT_STAGE_M2A_SPIN2);
-        LegArgs a = leg_args(p, p->s2);
-        a.eb = sel_eb(sel);
-        HIPCHK(launch_leg_m2a(a, p->prec, p->stream));
+        HIPCHK(launch_leg_m2a(a2, p->prec, p->stream));
     }
     StageTimer tm(p, SHT_STAGE_ALM_LAYOUT);
     const int64_t csz = (int64_t)(p->lmax + 1) * (p->lmax + 1);

@@ -95,18 +95,26 @@ struct LegArgs {
     // ntiles their total
     const int* mlist;
     int nlist;
-    // a plan that owns part of the m: its m in increasing order, and the number of parts.
-    // The i-th of them is at least nparts (i - 1).  The alm2map kernels get it as mlist;
-    // the map2alm kernels of k_leg_reg.hip deal their work by it, those of k_leg.hip find
-    // no tiles for the other m
-    const int* owned;
-    int nowned, nparts;
     // > 1: each workgroup's reduction range (map2alm: ring chunks, alm2map: l
     // tiles) is split over ksplit workgroups that add into pre-zeroed outputs
     // (list mode, where one level's grid is too small to fill the chip)
     int ksplit;
     int ncols;              // columns holding map sets in this chunk (2 per map set); the rest pad
+    // > 0: mlist holds the m a part plan owns, in increasing order, the i-th at least
+    // mstep (i - 1) (the number of parts).  The map2alm kernels of k_leg_reg.hip deal their
+    // work by the list; those of k_leg.hip go without it (tiles holds the owned m only)
+    int mstep;
 };
+// a part plan's arguments for the kernels that take the owned m from `tiles`
+inline LegArgs by_tiles(const LegArgs& a)
+{
+    LegArgs b = a;
+    if (a.mstep) {
+        b.mlist = nullptr;
+        b.nlist = 0;
+    }
+    return b;
+}
 
 // Narrow tiles of the LDS kernels: a chunk of at most 8 (1) or 16 (2) map sets, the
 // first 16 or 32 columns of a 64-column tile.  The four waves then split the tile's
