@@ -99,6 +99,7 @@ struct sht_plan_s {
     std::vector<FftClass> classes;  // ring classes of the FFT launches
     int64_t ldx_cur = 0;            // row pitch of the m-major arrays for the chunk being run
     int nm_cur = 0;                 // map sets of the chunk being run
+    int pass = 0;                   // map sets per pass of a call (pass_width)
 
     // workspace
     void* ws = nullptr;
@@ -801,10 +802,30 @@ AlmArgs alm_args(sht_plan p, const SeedSet& S, int nmaps_chunk)
     return a;
 }
 
+// Map sets per pass of a call: the plan's chunk, or fewer where it is so wide that the one
+// grid of all ring classes (in threads) or the byte offsets inside one m's rows, which the
+// FP64 Legendre kernels keep per lane, would pass 32 bits (nside 16: 4.2 million maps)
+int pass_width(sht_plan p)
+{
+    const int64_t rows = std::max(p->nring, p->lmax + 1), top = (int64_t)1 << 32;
+    auto fits = [&](int nm) {
+        int64_t blocks = 0;
+        for (const FftClass& c : p->classes) {
+            const int64_t seqs = (int64_t)c.nrings * p->ncomp, per = 2 * c.nseq;
+            blocks += (seqs * ((nm + per - 1) / per) + 7) / 8 * 8;
+        }
+        return blocks * FFT_THREADS < top && rows * ldx_for(nm) * (int64_t)sizeof(double) <= top;
+    };
+    int nm = p->chunk;
+    while (nm > 64 && !fits(nm)) nm = (nm / 2 + 63) / 64 * 64;
+    return nm;
+}
+
 int prep(sht_plan p)
 {
     int rc = ensure_workspace(p);
     if (rc) return rc;
+    p->pass = pass_width(p);
     p->ldx_cur = ldx_for(p->chunk);
     p->nm_cur = p->chunk;
     return SHT_OK;
@@ -1319,8 +1340,8 @@ int sht_alm2map_sel(sht_plan p, int comps, const double* alm, double* map)
     if ((rc = prep(p))) return rc;
     const int64_t astride = (int64_t)p->ncomp * (p->lmax + 1) * (p->lmax + 1);
     const int64_t mstride = (int64_t)p->ncomp * p->npix;
-    for (int k0 = 0; k0 < p->nmaps; k0 += p->chunk) {
-        int nm = std::min(p->chunk, p->nmaps - k0);
+    for (int k0 = 0; k0 < p->nmaps; k0 += p->pass) {
+        int nm = std::min(p->pass, p->nmaps - k0);
         use_width(p, nm);
         if ((rc = run_a2m(p, alm + k0 * astride, nm, comps))) return rc;
         if ((rc = run_fft_inv(p, map + k0 * mstride, nm, comps))) return rc;
@@ -1386,8 +1407,8 @@ int sht_map2alm_sel(sht_plan p, int comps, const double* map, double* alm)
     if ((rc = prep(p))) return rc;
     const int64_t astride = (int64_t)p->ncomp * (p->lmax + 1) * (p->lmax + 1);
     const int64_t mstride = (int64_t)p->ncomp * p->npix;
-    for (int k0 = 0; k0 < p->nmaps; k0 += p->chunk) {
-        int nm = std::min(p->chunk, p->nmaps - k0);
+    for (int k0 = 0; k0 < p->nmaps; k0 += p->pass) {
+        int nm = std::min(p->pass, p->nmaps - k0);
         use_width(p, nm);
         FftArgs f = fft_args(p, nm);
         f.maps_in = map + k0 * mstride;
@@ -1421,8 +1442,8 @@ int sht_eb_split(sht_plan p, const double* map, double* alm, double* map_e, doub
     if ((rc = prep(p))) return rc;
     const int64_t astride = (int64_t)p->ncomp * (p->lmax + 1) * (p->lmax + 1);
     const int64_t mstride = (int64_t)p->ncomp * p->npix;
-    for (int k0 = 0; k0 < p->nmaps; k0 += p->chunk) {
-        int nm = std::min(p->chunk, p->nmaps - k0);
+    for (int k0 = 0; k0 < p->nmaps; k0 += p->pass) {
+        int nm = std::min(p->pass, p->nmaps - k0);
         use_width(p, nm);
         FftArgs f = fft_args(p, nm);
         f.maps_in = map + k0 * mstride;
@@ -1454,8 +1475,8 @@ int sht_map2alm_iter(sht_plan p, const double* map, double* alm, int niter, doub
     const int64_t astride = (int64_t)p->ncomp * (p->lmax + 1) * (p->lmax + 1);
     const int64_t mstride = (int64_t)p->ncomp * p->npix;
     std::vector<double> sums(niter + 1, 0.0), hn;
-    for (int k0 = 0; k0 < p->nmaps; k0 += p->chunk) {
-        int nm = std::min(p->chunk, p->nmaps - k0);
+    for (int k0 = 0; k0 < p->nmaps; k0 += p->pass) {
+        int nm = std::min(p->pass, p->nmaps - k0);
         use_width(p, nm);
         double* a = alm + k0 * astride;
         FftArgs f = fft_args(p, nm);
@@ -1522,8 +1543,8 @@ int sht_map2alm_immediate(sht_plan p, const double* map, double* alm, int niter,
         for (double v : hn) sums[n] += v;
         return SHT_OK;
     };
-    for (int k0 = 0; k0 < p->nmaps; k0 += p->chunk) {
-        int nm = std::min(p->chunk, p->nmaps - k0);
+    for (int k0 = 0; k0 < p->nmaps; k0 += p->pass) {
+        int nm = std::min(p->pass, p->nmaps - k0);
         use_width(p, nm);
         double* a = alm + k0 * astride;
         FftArgs f = fft_args(p, nm);
