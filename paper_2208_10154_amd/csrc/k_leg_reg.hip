@@ -1131,7 +1131,13 @@ void go_a2m_pair(const LegArgs& a0, const LegArgs& a2, int spins, hipStream_t st
 
 }  // namespace
 
-bool leg_m2a_reg(const LegArgs& a, int prec) { return pick_m2a(a, prec).c != 0; }
+// A part plan takes these kernels where its own m and all m both ask for them: where the
+// whole plan runs the LDS kernels (short chains, wide batches) a part's few waves would pick
+// the split form, 12 us more (nside 64, lmax 128, 400 T maps, part 0 of 4: 161 -> 173 us).
+bool leg_m2a_reg(const LegArgs& a, int prec)
+{
+    return pick_m2a(a, prec).c != 0 && (!a.mstep || pick_m2a(by_tiles(a), prec).c != 0);
+}
 
 hipError_t launch_leg_m2a_reg(const LegArgs& a, int prec, hipStream_t st)
 {
@@ -1146,7 +1152,7 @@ bool launch_leg_m2a_pair(const LegArgs& a0, const LegArgs& a2, int prec, int spi
     if (prec == 2) return launch_leg_m2a_pair_bf16(a0, a2, spins, st);
     if (prec == 1) return !leg_m2a_reg(a0, prec) && !leg_m2a_reg(a2, prec) && launch_leg_m2a_pair_f32(a0, a2, spins, st);
     const M2aPick k0 = pick_m2a(a0, prec), k2 = pick_m2a(a2, prec);
-    if (!k0.split || !k2.split) return false;
+    if (!k0.split || !k2.split || !leg_m2a_reg(a0, prec) || !leg_m2a_reg(a2, prec)) return false;
     if (k2.nc == 4) go_m2a_pair<4, 4>(a0, a2, spins, st);
     else if (k0.nc == 4) go_m2a_pair<16, 4>(a0, a2, spins, st);
     else go_m2a_pair<16, 16>(a0, a2, spins, st);
