@@ -46,9 +46,8 @@ struct FftArgs {
     double* norms;          // optional per map-set/comp residual sum of squares (K_RES)
     int64_t npix;
     int ncomp;
-    int comp0;              // first component index handled by this launch (blockIdx.y adds to it)
+    int comp0;              // first component index handled by this launch
     int nmaps;              // map sets in the chunk
-    int npairs;             // padded map-set pairs (ldx / 4)
     int lmax;
     int nring;
     int64_t ldx;            // columns of X (2 * padded map sets)

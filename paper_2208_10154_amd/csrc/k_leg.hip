@@ -844,14 +844,18 @@ hipError_t launch_m2a_t(const LegArgs& a, hipStream_t st)
             if (a.eb == 1) hipLaunchKernelGGL((k_m2a_spin2<T, 2, 1>), grid, blk, 0, st, b);
             else if (a.eb == 2) hipLaunchKernelGGL((k_m2a_spin2<T, 2, 2>), grid, blk, 0, st, b);
             else hipLaunchKernelGGL((k_m2a_spin2<T, 2, 0>), grid, blk, 0, st, b);
-        } else if (narrow(a) == 1) {
-            if (a.eb == 1) hipLaunchKernelGGL((k_m2a_spin2<T, 1, 1, 1>), grid, blk, 0, st, b);
-            else if (a.eb == 2) hipLaunchKernelGGL((k_m2a_spin2<T, 1, 2, 1>), grid, blk, 0, st, b);
-            else hipLaunchKernelGGL((k_m2a_spin2<T, 1, 0, 1>), grid, blk, 0, st, b);
-        } else if (narrow(a) == 2) {
-            if (a.eb == 1) hipLaunchKernelGGL((k_m2a_spin2<T, 1, 1, 2>), grid, blk, 0, st, b);
-            else if (a.eb == 2) hipLaunchKernelGGL((k_m2a_spin2<T, 1, 2, 2>), grid, blk, 0, st, b);
-            else hipLaunchKernelGGL((k_m2a_spin2<T, 1, 0, 2>), grid, blk, 0, st, b);
+        } else if (narrow(a) && (a.eb || sizeof(T) == 4)) {  // FP64 of both E and B: k_leg_reg.hip
+            const bool one = narrow(a) == 1;
+            if (a.eb == 1) {
+                if (one) hipLaunchKernelGGL((k_m2a_spin2<T, 1, 1, 1>), grid, blk, 0, st, b);
+                else hipLaunchKernelGGL((k_m2a_spin2<T, 1, 1, 2>), grid, blk, 0, st, b);
+            } else if (a.eb == 2) {
+                if (one) hipLaunchKernelGGL((k_m2a_spin2<T, 1, 2, 1>), grid, blk, 0, st, b);
+                else hipLaunchKernelGGL((k_m2a_spin2<T, 1, 2, 2>), grid, blk, 0, st, b);
+            } else if constexpr (sizeof(T) == 4) {
+                if (one) hipLaunchKernelGGL((k_m2a_spin2<T, 1, 0, 1>), grid, blk, 0, st, b);
+                else hipLaunchKernelGGL((k_m2a_spin2<T, 1, 0, 2>), grid, blk, 0, st, b);
+            }
         } else {
             if (a.eb == 1) hipLaunchKernelGGL((k_m2a_spin2<T, 1, 1>), grid, blk, 0, st, b);
             else if (a.eb == 2) hipLaunchKernelGGL((k_m2a_spin2<T, 1, 2>), grid, blk, 0, st, b);

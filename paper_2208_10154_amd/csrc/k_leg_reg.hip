@@ -170,21 +170,21 @@ __device__ __forceinline__ bool m2a_task(const LegArgs& a, int b, int rtl, int n
     return lt < ntl(a, m, rtl);
 }
 
-// emitter of one recursion row: its values are A operands at once
-template <typename T, int C>
+// FP32: emitter of one recursion row, whose values are A operands at once
+template <int C>
 struct RowToMfma {
-    using MF = Mfma<T>;
+    using MF = Mfma<float>;
     typename MF::acc (&acc)[C];
-    const T (&b)[2][C];   // T_N + T_S, T_N - T_S (spin 2: [Q | Y])
-    const T (&bs)[2][C];  // spin 2: the same of [Y | Q]
+    const float (&b)[2][C];   // T_N + T_S, T_N - T_S (spin 2: [Q | Y])
+    const float (&bs)[2][C];  // spin 2: the same of [Y | Q]
     template <int R>
-    __device__ __forceinline__ void put(T v)
+    __device__ __forceinline__ void put(float v)
     {
 #pragma unroll
         for (int c = 0; c < C; ++c) acc[c] = MF::run(v, b[R & 1][c], acc[c]);
     }
     template <int R>
-    __device__ __forceinline__ void put(T p, T q)
+    __device__ __forceinline__ void put(float p, float q)
     {
 #pragma unroll
         for (int c = 0; c < C; ++c) acc[c] = MF::run(p, b[R & 1][c], acc[c]);
@@ -199,14 +199,13 @@ __device__ __forceinline__ double zero_unless(bool live, double v)
 {
     return __hiloint2double(live ? __double2hiint(v) : 0, __double2loint(v));
 }
-// A operand from a recursion value
-__device__ __forceinline__ void operand(double& o, bool live, double v) { o = zero_unless(live, v); }
-__device__ __forceinline__ void operand(float& o, bool live, double v) { o = live ? (float)v : 0.0f; }
+// FP32 A operand from a recursion value
+__device__ __forceinline__ float operand32(bool live, double v) { return live ? (float)v : 0.0f; }
 
 // rec_row (same recursion, same values) with the row masked in the operand's format;
 // rows past lmax need no mask: their coefficients are zero
-template <int R, typename T, int C>
-__device__ __forceinline__ void rec_row_reg(Rec<0>& f, const double (&c)[3], RowToMfma<T, C>& em)
+template <int R, int C>
+__device__ __forceinline__ void rec_row_reg(Rec<0>& f, const double (&c)[3], RowToMfma<C>& em)
 {
     if constexpr (R > 1) {
         double v = fma(-c[0], f.t, c[0]) * f.v1 - c[1] * f.v0;
@@ -220,12 +219,10 @@ __device__ __forceinline__ void rec_row_reg(Rec<0>& f, const double (&c)[3], Row
         f.v0 = f.v1;
         f.v1 = v;
     }
-    T o;
-    operand(o, f.k == 0, R == 0 ? f.v0 : f.v1);
-    em.template put<R>(o);
+    em.template put<R>(operand32(f.k == 0, R == 0 ? f.v0 : f.v1));
 }
-template <int R, typename T, int C>
-__device__ __forceinline__ void rec_row_reg(Rec<2>& f, const double (&c)[3], RowToMfma<T, C>& em)
+template <int R, int C>
+__device__ __forceinline__ void rec_row_reg(Rec<2>& f, const double (&c)[3], RowToMfma<C>& em)
 {
     if constexpr (R > 1) {
         const double ax = fma(-c[0], f.t, c[0]), be = c[1], ga = c[2];
@@ -245,10 +242,7 @@ __device__ __forceinline__ void rec_row_reg(Rec<2>& f, const double (&c)[3], Row
         f.b0 = f.b1;
         f.b1 = fm;
     }
-    T p, q;
-    operand(p, f.k == 0, R == 0 ? f.a0 : f.a1);
-    operand(q, f.k == 0, R == 0 ? f.b0 : f.b1);
-    em.template put<R>(p, q);
+    em.template put<R>(operand32(f.k == 0, R == 0 ? f.a0 : f.a1), operand32(f.k == 0, R == 0 ? f.b0 : f.b1));
 }
 
 // ============================================================================
@@ -373,7 +367,7 @@ __global__ __launch_bounds__(64, 2) void k_m2a_reg32(LegArgs a, int ncg)
             __builtin_amdgcn_sched_barrier(0);
             static_for<0, SEG>([&](auto ti) {
                 constexpr int t = decltype(ti)::v;
-                RowToMfma<T, C> em{acc[t], b, bs};
+                RowToMfma<C> em{acc[t], b, bs};
                 rec_row_reg<t>(f, cf[t], em);
             });
         };
@@ -1043,9 +1037,10 @@ M2aPick pick_m2a(const LegArgs& a, int prec)
     // set-up costs about eight of its groups of 8 rings
     const double rec = f64 ? 0.35 : (a.spin == 2 ? 1.35 : 1.5), setup = 1.0 + 64.0 / a.rn;
     const double lds = f64 ? 1.53 : (a.spin == 2 ? 1.58 : 1.7);  // per tile of the LDS kernels
-    // columns the LDS kernels compute; their narrow forms take 0.45 (16 columns) and 0.7
-    // (32) of a full tile's time
-    const double wide = narrow(a) == 1 ? 29.0 : narrow(a) == 2 ? 45.0 : a.ldx == 64 ? 64.0 : (a.ncols + 127) / 128 * 128.0;
+    // columns the LDS kernels compute; their narrow forms (FP32) take 0.45 (16 columns) and
+    // 0.7 (32) of a full tile's time
+    const int nw = f64 ? 0 : narrow(a);
+    const double wide = nw == 1 ? 29.0 : nw == 2 ? 45.0 : a.ldx == 64 ? 64.0 : (a.ncols + 127) / 128 * 128.0;
     double least = lds * (wide / (a.spin == 2 ? 8 : 16)) * l_tiles(a, 64) * 0.5;
     M2aPick best{16, 0, 8, false};
     for (int c = 1; c <= (f64 ? 2 : 4); c *= 2) {

@@ -746,7 +746,6 @@ FftArgs fft_args(sht_plan p, int nmaps_chunk)
     a.comp0 = 0;
     a.nmaps = nmaps_chunk;
     a.ldx = p->ldx_cur;
-    a.npairs = (int)(a.ldx / 4);
     a.lmax = p->lmax;
     a.nring = p->nring;
     a.xcomp = xcomp_elems(p);
