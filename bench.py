@@ -227,6 +227,21 @@ def leg_family(kernel: str) -> str:
     return "bf" if "_bf" in kernel else "fp"
 
 
+def record_key(stage: str, prec: str) -> str:
+    """Name a Legendre stage ("m2a_spin2", ...) has in the committed counter records."""
+    return "k_" + stage + {"fp64": "<double>", "fp32": "<float>", "bf16x3": "_bf"}[prec]
+
+
+def launched_kernel(stage: str, prec: str) -> str:
+    """The kernel a Legendre stage launches for a wide batch such as the benchmark's chunk:
+    the register-operand kernels (k_leg_reg.hip) in FP64 and for FP32 map2alm, the kernels
+    with the recursion tile in LDS otherwise."""
+    direction, spin = stage[:3], stage[-1]
+    reg = {("m2a", "fp64"): "k_m2a_reg64", ("a2m", "fp64"): "k_a2m_reg", ("m2a", "fp32"): "k_m2a_reg32"}
+    name = reg.get((direction, prec))
+    return f"{name}<{spin}>" if name else record_key(stage, prec)
+
+
 def leg_source_hash(family: str = "fp") -> str:
     import hashlib
     h = hashlib.sha256()
@@ -237,8 +252,8 @@ def leg_source_hash(family: str = "fp") -> str:
 
 
 def counter_record(path: str, kernel: str, nside: int, lmax: int, per_launch_maps: int):
-    """The committed counter record of `kernel`, if it was taken on the kernel's
-    current sources at this workload (else None)."""
+    """The committed counter record under the key `kernel` (record_key), if it was taken
+    on the kernel's current sources at this workload (else None)."""
     try:
         with open(path) as fh:
             rec = json.load(fh)
@@ -274,17 +289,17 @@ def roofline(args, prec, res):
     flops_per_step = leg_flops(args.nside, args.lmax, spin, args.nmaps)
     achieved = flops_per_step * args.steps / (ms * 1e-3) / 1e12
     peak = PEAK_TFLOPS[prec]
-    kname = "k_" + name + {"fp64": "<double>", "fp32": "<float>", "bf16x3": "_bf"}[prec]
+    key = record_key(name, prec)
     out = {
-        "kernel": kname,
+        "kernel": launched_kernel(name, prec),
         "bound": "mfma", "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s",
         "frac": round(achieved / peak, 4),
-        "traffic": measured_traffic(kname, args.nside, args.lmax, args.chunk),
+        "traffic": measured_traffic(key, args.nside, args.lmax, args.chunk),
         "launches": launches, "avg_launch_ms": round(ms / launches, 3),
         "flops_per_launch": flops_per_step * args.steps / launches,
         "achieved_counts": "folded flops (all rings of a hemisphere) per launch / live launch time",
     }
-    e = counter_record(MFMA_FILE, kname, args.nside, args.lmax, args.chunk)
+    e = counter_record(MFMA_FILE, key, args.nside, args.lmax, args.chunk)
     if e and args.nmaps % args.chunk == 0:
         ex = e["mfma_insts_per_launch"] * e["flops_per_inst"] / (ms / launches * 1e-3) / 1e12
         out["executed"] = {"flops_per_launch": e["mfma_insts_per_launch"] * e["flops_per_inst"],
@@ -384,7 +399,7 @@ def iteration_leg(args):
     stream = torch.cuda.current_stream()
     for prec in args.iter_precisions.split(","):
         p.set_precision(prec)
-        p.map2alm_iter(maps, out, 0)  # warm-up (work lists, iteration buffers)
+        p.map2alm_iter(maps, out, 0)  # warm-up (iteration buffers)
         torch.cuda.synchronize()
         times, resid = {}, {}
         for k in (0, 9, niter):  # the N_iter = 3 run last, so `out` holds its result
@@ -478,7 +493,7 @@ def immediate_leg(args):
     res = {}
     for prec in args.imm_precisions.split(","):
         p.set_precision(prec)
-        p.map2alm_immediate(maps, out, 1)  # warm-up (schedule, work lists, iteration buffers)
+        p.map2alm_immediate(maps, out, 1)  # warm-up (schedule, iteration buffers)
         torch.cuda.synchronize()
         r = {}
         for mode, fn in (("traditional", p.map2alm_iter), ("immediate", p.map2alm_immediate)):

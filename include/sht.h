@@ -56,7 +56,11 @@ enum sht_status {
 };
 
 /* Precision of the Legendre contraction.  The recursion (with its exponent
- * rescaling), dsigma, the FFTs and the iteration residual are FP64 in all modes. */
+ * rescaling), dsigma, the FFTs and the iteration residual are FP64 in all modes.
+ * The lower precisions pay for batches of some tens of map sets and up; a few map sets run
+ * fastest in FP64, whose kernels spend the least beside the recursion (nside 512, lmax 1535,
+ * IQU, alm2map + map2alm: 1 set 3.2 ms against 10.4 ms in split BF16, 8 sets 7.4 against
+ * 11.3, 125 sets 102 against 68). */
 enum sht_precision {
     SHT_FP64 = 0,   /* FP64 MFMA, FP64 ring Fourier coefficients */
     SHT_FP32 = 1,   /* FP32 MFMA, FP32 ring Fourier coefficients */

@@ -260,7 +260,7 @@ class Executor:
         g = self._graphs.get(key)
         if g is None:
             plan.set_nmaps(width)
-            fn(slot_in, slot_out, stream=s)  # warm-up: work lists, workspace
+            fn(slot_in, slot_out, stream=s)  # warm-up: workspace
             s.synchronize()
             g = torch.cuda.CUDAGraph()
             with torch.cuda.graph(g, stream=s):
