@@ -638,16 +638,28 @@ __global__ __launch_bounds__(NT) void k_bluestein_init(const FftLen* lens, const
     }
 }
 
-// One class of the runtime-length code whose LDS or registers the shared launch below
-// does not hold (16 values per thread)
+// One class of the runtime-length code: 16 values per thread, whose LDS and registers the
+// shared launch below does not hold, or 2 by wide batches (APART)
 template <bool FWD, int ELEMS>
-__global__ __launch_bounds__(NT, 2) void k_fft_gen(FftArgs a, FftWork w, int cnt)
+__global__ __launch_bounds__(NT, ELEMS == 16 ? 2 : 4) void k_fft_gen(FftArgs a, FftWork w, int cnt)
 {
     extern __shared__ double2 lds[];
     Item it;
     if (!work_item(w, cnt, blockIdx.x, a.comp0, it)) return;
     if constexpr (FWD) gen_fwd<ELEMS>(a, it, lds);
     else gen_inv<ELEMS>(a, it, lds);
+}
+
+// Rings of 64 pixels by workgroups of their own 128 threads (APART); the shared launch
+// starts 512 and ends three quarters of them
+template <bool FWD, typename XT>
+__global__ __launch_bounds__(P2<6>::NTH, 4) void k_fft_64(FftArgs a, FftWork w, int cnt)
+{
+    extern __shared__ double2 lds[];
+    Item it;
+    if (!work_item(w, cnt, blockIdx.x, a.comp0, it)) return;
+    if constexpr (FWD) fwd_item<6, XT, false>(a, it, lds);
+    else inv_item<6, XT, false>(a, it, lds);
 }
 
 // All other classes in one launch: the workgroups of class c are blocks start[c] ..
@@ -726,6 +738,25 @@ hipError_t allow_lds(const void* f, size_t bytes)
     return bytes > 65536 ? hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) : hipSuccess;
 }
 
+template <typename F>
+hipError_t launch_class(F fn, const FftArgs& a, const FftWork& w, int cnt, int threads, int lds, hipStream_t st)
+{
+    const size_t sh = (size_t)lds * sizeof(double2);
+    const hipError_t e = allow_lds((const void*)fn, sh);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(fn, dim3(cnt), dim3(threads), sh, st, a, w, cnt);
+    return hipGetLastError();
+}
+
+// The shortest kinds (2 values per thread, 64 pixels) leave the shared launch where a class
+// has this many workgroups, and where it is the plan's only class: each does so little that
+// finding its class, the threads past its own and the registers of the longest kind show.
+// us forward + inverse, shared -> apart (FP64): nside 8 x 2000 IQU sets 99 + 92 -> 81 + 75,
+// 4 x 5000 103 + 100 -> 82 + 79, 12 x 1000 80 + 78 -> 74 + 72, 16 x 5000 T maps 153 + 166 ->
+// 149 + 154.  Below it the second launch costs what it saves: 16 x 2500 T maps (2176
+// workgroups of 64-pixel rings) 75 + 73 -> 78 + 82.
+constexpr int APART = 4096;
+
 template <bool FWD, typename XT>
 hipError_t launch_rings(const FftArgs& a, const FftClass* cls, int ncls, int ncompl, hipStream_t st)
 {
@@ -754,12 +785,16 @@ hipError_t launch_rings(const FftArgs& a, const FftClass* cls, int ncls, int nco
         }
         const FftWork w = work_of(a, c, multi ? pack : ONE_RING);
         const int cnt = work_count(w, ncompl);
-        if (c.kind == FFT_GEN16) {
-            const size_t sh = (size_t)c.lds * sizeof(double2);
-            hipError_t e = allow_lds((const void*)k_fft_gen<FWD, 16>, sh);
+        const bool apart = !multi && (ncls == 1 || cnt >= APART);
+        if (c.kind == FFT_GEN16 || (c.kind == FFT_GEN2 && apart)) {
+            const auto fn = c.kind == FFT_GEN2 ? k_fft_gen<FWD, 2> : k_fft_gen<FWD, 16>;
+            const hipError_t e = launch_class(fn, a, w, cnt, NT, c.lds, st);
             if (e != hipSuccess) return e;
-            hipLaunchKernelGGL((k_fft_gen<FWD, 16>), dim3(cnt), dim3(NT), sh, st, a, w, cnt);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
+            continue;
+        }
+        if (c.kind == FFT_P2 + 6 && !multi && cnt >= APART) {
+            const hipError_t e = launch_class(k_fft_64<FWD, XT>, a, w, cnt, P2<6>::NTH, c.lds, st);
+            if (e != hipSuccess) return e;
             continue;
         }
         if (n == MAX_CLASSES) return hipErrorInvalidValue;
