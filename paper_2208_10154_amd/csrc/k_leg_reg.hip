@@ -1013,11 +1013,24 @@ A2mPick pick_a2m(const LegArgs& a)
     return best;
 }
 
+// The same counted row by row: chains below two tiles are mostly remainders.
+double l_tiles_exact(const LegArgs& a, int tl)
+{
+    const double n = a.lmax + 1, q = (a.lmax + 1) / tl;
+    return nm_rows(a) / n * (q + 1.0) * (n - 0.5 * q * tl);
+}
+
 // map2alm: C tiles of NC columns per wave and TS rows per run, rings split over a
 // block's waves or not; c = 0: the LDS kernels of k_leg.hip, which share a recursion tile
 // between 64 to 256 columns, pad the batch to their width and the l range to 64 rows
 // instead of 128 (narrow lmax, wide batches; FP32 batches that leave the chip idle here).
-//  * Few waves: split (below 2048; at nside 64, 16 IQU sets 41 against 53 us).
+//  * Few waves: split or the LDS kernels.  Split while its blocks (128 rows x 16 columns)
+//    leave the chip room, and past that while it does less work than the LDS kernels, which
+//    pad 64-row tiles to 64 or 128 columns but share the recursion.  The lines are those of
+//    least regret over 1090 shapes of nside 2 to 512, 5 to 1500 maps (0.3% of the call's time
+//    on average; always split 3.4%, always LDS 16%).  Whole calls, split / LDS us: nside 16,
+//    lmax 16, 800 IQU sets 131 / 91; nside 16, lmax 47, 300 T maps 49 / 36; nside 64, lmax
+//    191, 16 IQU sets 81 / 99; nside 128, lmax 383, 8 IQU sets 168 / 350.
 //  * One or two 4-column tiles: runs of 16 rows where that leaves 1024 waves (nside 512, 1
 //    IQU set: 830 us against 1385 for 8-row runs and 1400 for 16 columns).
 struct M2aPick { int nc, c, ts; bool split; };
@@ -1031,7 +1044,15 @@ M2aPick pick_m2a(const LegArgs& a, int prec)
         return {4, 1, 8, l_tiles(a, 128) * t4 < 2048.0};
     }
     const double lt = l_tiles(a, 128);
-    if (f64 && lt * t < 2048.0) return {16, 1, 8, true};
+    if (f64 && lt * t < 2048.0) {
+        const double blocks = l_tiles_exact(a, 128) * t;
+        // 256-column tiles (spin 0) take the LDS kernel longer
+        const double room = a.spin == 2 ? 1400.0 : a.ldx % 256 == 0 ? 950.0 : 550.0;
+        const double wide = a.ldx == 64 ? 64.0 : (a.ncols + 127) / 128 * 128.0;
+        const double lds = l_tiles_exact(a, 64) * 0.5 * wide / (a.spin == 2 ? 8 : 16);
+        if (blocks < room || (0.88 + 14.0 / a.rn) * blocks < lds) return {16, 1, 8, true};
+        return {16, 0, 8, false};
+    }
     if (!f64 && lt * t < 4096.0) return {16, 0, 8, false};
     // per tile: MFMAs, and the recursion of a wave (FP32 halves only the MFMAs); a wave's
     // set-up costs about eight of its groups of 8 rings
@@ -1140,14 +1161,16 @@ hipError_t launch_leg_m2a_reg(const LegArgs& a, int prec, hipStream_t st)
     return a.spin == 0 ? m2a_tile<0>(a, k, prec, st) : m2a_tile<2>(a, k, prec, st);
 }
 
-// Pairing pays while one spin alone leaves the chip part empty: map2alm where both spins
-// split their rings, alm2map up to 8192 waves (nside 64, 16 IQU sets).
+// Pairing pays while one spin alone leaves the chip part empty: map2alm where spin 2 splits
+// its rings (spin 0 then splits too, also where it would not by itself: nside 32, lmax 95, 48
+// IQU sets, 75 us with spin 0 in the LDS kernel, 68 as a pair), alm2map up to 8192 waves
+// (nside 64, 16 IQU sets).
 bool launch_leg_m2a_pair(const LegArgs& a0, const LegArgs& a2, int prec, int spins, hipStream_t st)
 {
     if (prec == 2) return launch_leg_m2a_pair_bf16(a0, a2, spins, st);
     if (prec == 1) return !leg_m2a_reg(a0, prec) && !leg_m2a_reg(a2, prec) && launch_leg_m2a_pair_f32(a0, a2, spins, st);
     const M2aPick k0 = pick_m2a(a0, prec), k2 = pick_m2a(a2, prec);
-    if (!k0.split || !k2.split || !leg_m2a_reg(a0, prec) || !leg_m2a_reg(a2, prec)) return false;
+    if (!k2.split || !leg_m2a_reg(a2, prec) || (k0.c != 0 && !k0.split)) return false;
     if (k2.nc == 4) go_m2a_pair<4, 4>(a0, a2, spins, st);
     else if (k0.nc == 4) go_m2a_pair<16, 4>(a0, a2, spins, st);
     else go_m2a_pair<16, 16>(a0, a2, spins, st);
