@@ -1050,7 +1050,10 @@ M2aPick pick_m2a(const LegArgs& a, int prec)
         const double room = a.spin == 2 ? 1400.0 : a.ldx % 256 == 0 ? 950.0 : 550.0;
         const double wide = a.ldx == 64 ? 64.0 : (a.ncols + 127) / 128 * 128.0;
         const double lds = l_tiles_exact(a, 64) * 0.5 * wide / (a.spin == 2 ? 8 : 16);
-        if (blocks < room || (0.88 + 14.0 / a.rn) * blocks < lds) return {16, 1, 8, true};
+        // the few orders of a level: the LDS kernels split their rings too, with a pass to clear
+        // the sums (nside 8, lmax 23, 3000 T maps, immediate iteration: 538 us split, 575 not)
+        const bool level = a.mlist && !a.mstep;
+        if (level || blocks < room || (0.88 + 14.0 / a.rn) * blocks < lds) return {16, 1, 8, true};
         return {16, 0, 8, false};
     }
     if (!f64 && lt * t < 4096.0) return {16, 0, 8, false};

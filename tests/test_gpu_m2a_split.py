@@ -59,3 +59,23 @@ def test_fewer_maps_take_no_longer():
     for p in plans:
         p.close()
     assert best[0] <= 1.1 * best[1], best
+
+
+@pytest.mark.parametrize("spin,nside,lmax,n", [(0, 8, 23, 3000), (2, 16, 47, 601)])
+def test_wide_immediate_levels(spin, nside, lmax, n):
+    """the levels of a wide immediate iteration (few orders, many columns) against chunks of 32"""
+    import torch
+    from paper_2208_10154_amd import sht
+    note(f"immediate spin={spin} nside={nside} lmax={lmax} nmaps={n}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    out = []
+    for chunk in (n, 32):
+        p = sht.Plan(nside, lmax, spin, n, chunk=chunk)
+        if not out:
+            maps = torch.randn(p.map_shape(), generator=g, dtype=torch.float64, device="cuda")
+        out.append(torch.full(p.alm_shape(), torch.nan, dtype=torch.float64, device="cuda"))
+        p.map2alm_immediate(maps, out[-1], 2)
+        p.sync()
+        p.close()
+    assert ((out[0] - out[1]).norm(dim=-1) <= 1e-12 * out[1].norm(dim=-1)).all()
